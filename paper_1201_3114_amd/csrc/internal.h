@@ -88,6 +88,8 @@ struct KernelShape {
     int wg;        // threads per workgroup
     int tile;      // LDS bytes per chain per refill
     int wps;       // resident waves per SIMD (persistent kernel)
+    int g = 1;     // lanes per chain, where the device has room (lanes_per_chain)
+    int simds = 0; // SIMDs of the device
 };
 
 struct DevInfo {
@@ -96,9 +98,16 @@ struct DevInfo {
 };
 
 constexpr int WAVE_LANES = 64;  // lanes of a gfx950 wavefront
+constexpr int CU_SIMDS = 4;     // SIMDs of a compute unit
+
+// Words of the plain path's and the streams' tag accumulator: three tag words, then the word in
+// which a launch with several lanes per chain is told whether the device has room for it.
+constexpr size_t TAG_WORDS = 3, TAG_WIDE = 3;
+int lanes_per_chain(uint64_t chains, int m, uint32_t integ, int simds);
 
 // ---- kernel launchers (kernels.hip) --------------------------------------------------
 hipError_t launch_fill_u64(unsigned long long *p, size_t n, hipStream_t s);
+// Clears the tag accumulator (TAG_WORDS and the word after them) and runs the message.
 hipError_t launch_plain(const KernelShape &sh, const lz_key &key, const lz_params &prm, int decrypt,
                         const uint8_t *in, uint8_t *out, uint64_t n, unsigned long long *tag_acc,
                         hipStream_t s, uint64_t block_base = 0);
@@ -119,11 +128,12 @@ struct BatchDev {
     uint32_t n_msg;
     uint32_t n_tail;
     uint64_t n_full;              // total full blocks
-    uint64_t n_tasks;
     unsigned long long *tag_acc;  // 3 per message
-    unsigned long long *counter;  // work-queue head
+    unsigned long long *counter;  // work-queue head, the word after the tags
+    unsigned long long *wide;     // claim_kernel's answer (several lanes per chain)
     int32_t *const *status_ref;   // decrypt: device slot holding the address of the per-message statuses
 };
+// Clears the tags and the counter and runs the batch.
 hipError_t launch_batch(const KernelShape &sh, const DevInfo &dev, const lz_params &prm, const BatchDev &b,
                         hipStream_t s);
 hipError_t launch_batch_finalize(const BatchDev &b, int decrypt, hipStream_t s);

@@ -81,6 +81,15 @@ __device__ __forceinline__ void lorenz_field(double x, double y, double z, doubl
     fz = (x * y) - (BETA * z);
 }
 
+// v + 2 u: 2 u is exact, so the one rounding of the fused form is that of the sum.  In assembly because the
+// compiler's choice, v_fmac_f64, is a 4-byte instruction, which moves the 8-byte ones after it in
+// the step loop off their fetch words.
+__device__ __forceinline__ double twice_plus(double u, double v) {
+    double r;
+    asm("v_fma_f64 %0, %1, 2.0, %2" : "=v"(r) : "v"(u), "v"(v));
+    return r;
+}
+
 // Format variant: classical Runge-Kutta 4, r += dt/6 ((k1 + k4) + 2 (k2 + k3)).
 __device__ __forceinline__ void rk4_step(double &x, double &y, double &z, double dt, double h2, double h6) {
     double ax, ay, az, bx, by, bz, cx, cy, cz, dx, dy, dz;
@@ -88,9 +97,9 @@ __device__ __forceinline__ void rk4_step(double &x, double &y, double &z, double
     lorenz_field(x + h2 * ax, y + h2 * ay, z + h2 * az, bx, by, bz);
     lorenz_field(x + h2 * bx, y + h2 * by, z + h2 * bz, cx, cy, cz);
     lorenz_field(x + dt * cx, y + dt * cy, z + dt * cz, dx, dy, dz);
-    x = x + h6 * ((ax + dx) + 2.0 * (bx + cx));
-    y = y + h6 * ((ay + dy) + 2.0 * (by + cy));
-    z = z + h6 * ((az + dz) + 2.0 * (bz + cz));
+    x = x + h6 * twice_plus(bx + cx, ax + dx);
+    y = y + h6 * twice_plus(by + cy, ay + dy);
+    z = z + h6 * twice_plus(bz + cz, az + dz);
 }
 
 template <int I>
@@ -120,6 +129,140 @@ __device__ __forceinline__ void lorenz_steps(double (&x)[M], double (&y)[M], dou
 #pragma unroll
         for (int m = 0; m < M; ++m) step<I>(x[m], y[m], z[m], dt, h2, h6);
     }
+}
+
+// ---- one chain over the lanes of a quad -----------------------------------------------
+//
+// With one wave on a SIMD a vector instruction takes four clocks, dependent or not, so a step costs
+// its instruction count: 14 with a chain per lane.  In a quad, lane 0 holds x, lane 1 y, lane 2 z
+// and lane 3 the constant sigma; with per-lane constants (m, c, k, s) every lane computes
+//
+//     q = m v + c            (-x, rho, 0)       t = s P1 + q    (y - x, rho - z, y)
+//     u = k v                (0, y, beta z)     t = t P2        (sigma (y-x), x (rho-z), x y)
+//     P1 = v of lanes 1,2,1                     t = t - u       (dx, dy, dz)
+//     P2 = v of lanes 3,0,0                     v = v + dt t
+//
+// 7 binary64 instructions and 4 32-bit moves between lanes, 11 in all.  Each lane's value goes through the same
+// roundings as in euler_step: the factors m, s and k are 0, 1 or -1 except k = beta, so the products
+// they form are exact (a zero's sign may differ, its value not).  Measured with one wave per SIMD:
+// 44.6 clocks per step against 56.6 with a chain per lane.  A wave holds 16 chains instead of 64.
+//
+// The loops are written in assembly for two reasons: a lane's value must stay in a register pair
+// whose halves the moves can name, and every instruction in them is 8 bytes long.  One 4-byte
+// instruction shifts all that follow across the 8-byte fetch words, which costs 25% (70.5 clocks per
+// step instead of 56.6 for the one-lane loop).  Two instructions lie between the write of v and the
+// first move that reads it through DPP, which must not follow within two wait states.
+
+template <int G>
+struct LaneRole {};
+
+template <>
+struct LaneRole<4> {
+    double m, c, k, s;
+    __device__ explicit LaneRole(int lane) {
+        const int r = lane & 3;
+        m = r == 0 ? -1.0 : 0.0;
+        c = r == 1 ? RHO : 0.0;
+        k = r == 1 ? 1.0 : (r == 2 ? BETA : 0.0);
+        s = r == 3 ? 0.0 : (r == 1 ? -1.0 : 1.0);
+    }
+};
+template <>
+struct LaneRole<1> {
+    __device__ explicit LaneRole(int) {}
+};
+
+// The value of `v` in the lane that DPP control CTRL names.
+template <int CTRL>
+__device__ __forceinline__ double dpp_f64(double v) {
+    const long long b = __double_as_longlong(v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)b, CTRL, 0xF, 0xF, true);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)((unsigned long long)b >> 32), CTRL, 0xF, 0xF, true);
+    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+
+// A counted loop of STEP, 60 steps an iteration (a divisor of the default 3000), then the rest.
+#define LZ_STEP_LOOP(STEP)                                                     \
+    "s_nop 4\n"                                                                \
+    "s_cmp_eq_u32 %[q], 0\n"                                                   \
+    "s_cbranch_scc1 2f\n"                                                      \
+    ".p2align 6\n"                                                             \
+    "1:\n"                                                                     \
+    ".rept 60\n" STEP ".endr\n"                                                \
+    "s_sub_u32 %[q], %[q], 1\n"                                                \
+    "s_cmp_lg_u32 %[q], 0\n"                                                   \
+    "s_cbranch_scc1 1b\n"                                                      \
+    "2:\n"                                                                     \
+    "s_cmp_eq_u32 %[r], 0\n"                                                   \
+    "s_cbranch_scc1 4f\n"                                                      \
+    ".p2align 6\n"                                                             \
+    "3:\n" STEP                                                                \
+    "s_sub_u32 %[r], %[r], 1\n"                                                \
+    "s_cmp_lg_u32 %[r], 0\n"                                                   \
+    "s_cbranch_scc1 3b\n"                                                      \
+    "4:\n"                                                                     \
+    "s_nop 1\n"
+
+// The vector field of the value in v[LO:HI] into OUT (P1 in v[60:61], P2 in v[62:63]).
+#define LZ_QUAD_FIELD(LO, HI, OUT)                                                             \
+    "v_fma_f64 %[q0], %[m], v[" LO ":" HI "], %[c]\n"                                          \
+    "v_mul_f64 %[u], %[k], v[" LO ":" HI "]\n"                                                 \
+    "v_mov_b32_dpp v60, v" LO " quad_perm:[1,2,1,3] row_mask:0xf bank_mask:0xf\n"              \
+    "v_mov_b32_dpp v61, v" HI " quad_perm:[1,2,1,3] row_mask:0xf bank_mask:0xf\n"              \
+    "v_mov_b32_dpp v62, v" LO " quad_perm:[3,0,0,3] row_mask:0xf bank_mask:0xf\n"              \
+    "v_mov_b32_dpp v63, v" HI " quad_perm:[3,0,0,3] row_mask:0xf bank_mask:0xf\n"              \
+    "v_fma_f64 " OUT ", %[s], v[60:61], %[q0]\n"                                               \
+    "v_mul_f64 " OUT ", " OUT ", v[62:63]\n"                                                   \
+    "v_add_f64 " OUT ", " OUT ", -%[u]\n"
+
+// n_it steps of the chain whose coordinates x, y, z all lanes of the quad hold.
+template <int I>
+__device__ __forceinline__ void quad_steps(double &x, double &y, double &z, double dt, uint32_t n_it,
+                                           const LaneRole<4> &role, int lane) {
+    const int lr = lane & 3;
+    double v = lr == 0 ? x : (lr == 1 ? y : (lr == 2 ? z : SIGMA));
+    uint32_t q = n_it / 60, r = n_it % 60;
+    double q0, u, t, p1, p2;
+    if constexpr (I == LZ_INTEGRATOR_RK4) {
+        // the field four times (9 instructions each) and the 11 operations of rk4_step between them:
+        // 47 instructions a step against 65
+        const double h2 = dt * 0.5, h6 = dt / 6.0;
+        double a, b, d, w;
+        asm volatile(LZ_STEP_LOOP(
+                         LZ_QUAD_FIELD("56", "57", "%[a]")
+                         "v_mul_f64 v[58:59], %[a], %[h2]\n"
+                         "v_add_f64 v[58:59], v[56:57], v[58:59]\n"
+                         LZ_QUAD_FIELD("58", "59", "%[b]")
+                         "v_mul_f64 v[58:59], %[b], %[h2]\n"
+                         "v_add_f64 v[58:59], v[56:57], v[58:59]\n"
+                         LZ_QUAD_FIELD("58", "59", "%[t]")
+                         "v_mul_f64 v[58:59], %[t], %[dt]\n"
+                         "v_add_f64 v[58:59], v[56:57], v[58:59]\n"
+                         "v_add_f64 %[b], %[b], %[t]\n"
+                         LZ_QUAD_FIELD("58", "59", "%[d]")
+                         "v_add_f64 %[a], %[a], %[d]\n"
+                         "v_fma_f64 %[a], 2.0, %[b], %[a]\n"
+                         "v_mul_f64 %[a], %[a], %[h6]\n"
+                         "v_add_f64 v[56:57], v[56:57], %[a]\n")
+                     : "+{v[56:57]}"(v), "=&{v[58:59]}"(w), "=&{v[60:61]}"(p1), "=&{v[62:63]}"(p2), [q0] "=&v"(q0),
+                       [u] "=&v"(u), [t] "=&v"(t), [a] "=&v"(a), [b] "=&v"(b), [d] "=&v"(d), [q] "+s"(q), [r] "+s"(r)
+                     : [m] "v"(role.m), [c] "v"(role.c), [k] "v"(role.k), [s] "v"(role.s), [dt] "s"(dt), [h2] "v"(h2),
+                       [h6] "v"(h6)
+                     : "scc");
+    } else {
+        static_assert(I == LZ_INTEGRATOR_EULER, "the quad form of this integrator is no shorter than the one-lane form");
+        asm volatile(LZ_STEP_LOOP(
+                         LZ_QUAD_FIELD("56", "57", "%[t]")
+                         "v_mul_f64 %[t], %[t], %[dt]\n"
+                         "v_add_f64 v[56:57], v[56:57], %[t]\n")
+                     : "+{v[56:57]}"(v), "=&{v[60:61]}"(p1), "=&{v[62:63]}"(p2), [q0] "=&v"(q0), [u] "=&v"(u),
+                       [t] "=&v"(t), [q] "+s"(q), [r] "+s"(r)
+                     : [m] "v"(role.m), [c] "v"(role.c), [k] "v"(role.k), [s] "v"(role.s), [dt] "s"(dt)
+                     : "scc");
+    }
+    x = dpp_f64<0x00>(v);  // quad_perm [0,0,0,0], [1,1,1,1], [2,2,2,2]
+    y = dpp_f64<0x55>(v);
+    z = dpp_f64<0xAA>(v);
 }
 
 // State of the M chains of one lane.
@@ -156,9 +299,9 @@ __device__ __forceinline__ void init_chain(Chains<M> &c, int m, const double (&r
 __device__ __forceinline__ uint32_t mod_k(uint32_t v, uint32_t k) { return k == 4 ? (v & 3u) : v % 3u; }
 
 // Steps 1-3 of Section 3.2 for one byte of each of the M chains.
-template <int M, int I>
+template <int M, int I, int G>
 __device__ __forceinline__ void crypt_byte(Chains<M> &c, const uint32_t (&bin)[M], uint32_t (&bout)[M], double dt,
-                                           uint32_t n_it) {
+                                           uint32_t n_it, const LaneRole<G> &role, int lane) {
     uint32_t R1[M], R2[M], p[M];
 #pragma unroll
     for (int m = 0; m < M; ++m) {
@@ -184,7 +327,8 @@ __device__ __forceinline__ void crypt_byte(Chains<M> &c, const uint32_t (&bin)[M
         c.z[m] = s == 2 ? moved : c.z[m];
     }
     // Step 2 (cont.): r <- F^(n_it)(r)
-    lorenz_steps<M, I>(c.x, c.y, c.z, dt, n_it);
+    if constexpr (G == 4) quad_steps<I>(c.x[0], c.y[0], c.z[0], dt, n_it, role, lane);
+    else lorenz_steps<M, I>(c.x, c.y, c.z, dt, n_it);
 #pragma unroll
     for (int m = 0; m < M; ++m) {
         // Step 3: mu_i <- (mu_i + R_i) mod 3 with R_i from the old alpha_i, Omega_i
@@ -234,7 +378,7 @@ __device__ __forceinline__ unsigned long long wave_xor_u64(unsigned long long v)
     return v;
 }
 
-// Per-wave LDS layout: tile rows (64*M x stride), then the chain table.
+// Per-wave LDS layout: tile rows (one per chain of the wave x stride), then the chain table.
 struct WaveLds {
     uint8_t *tile;
     const uint8_t **in;
@@ -245,19 +389,19 @@ struct WaveLds {
 // Row stride of the LDS tile: an odd number of 4-byte words past a multiple of 64 banks
 // (tile is a multiple of 16), so the 64 lanes reading their own rows hit distinct banks.
 __host__ __device__ constexpr size_t tile_stride(int tile) { return (size_t)tile + 4; }
-__host__ __device__ constexpr size_t wave_lds_bytes(int m, int tile) {
-    return (size_t)WAVE * m * (tile_stride(tile) + 2 * sizeof(void *) + sizeof(uint32_t));
+__host__ __device__ constexpr size_t wave_lds_bytes(int rows, int tile) {
+    return (size_t)rows * (tile_stride(tile) + 2 * sizeof(void *) + sizeof(uint32_t));
 }
 
-template <int M>
+template <int ROWS>
 __device__ __forceinline__ WaveLds wave_lds(char *base, int tile) {
     WaveLds w;
     w.tile = reinterpret_cast<uint8_t *>(base);
-    char *p = base + (size_t)WAVE * M * tile_stride(tile);
+    char *p = base + (size_t)ROWS * tile_stride(tile);
     w.in = reinterpret_cast<const uint8_t **>(p);
-    p += (size_t)WAVE * M * sizeof(void *);
+    p += (size_t)ROWS * sizeof(void *);
     w.out = reinterpret_cast<uint8_t **>(p);
-    p += (size_t)WAVE * M * sizeof(void *);
+    p += (size_t)ROWS * sizeof(void *);
     w.cnt = reinterpret_cast<uint32_t *>(p);
     return w;
 }
@@ -266,24 +410,28 @@ __device__ __forceinline__ WaveLds wave_lds(char *base, int tile) {
 // input and output through LDS.  on_stop(m) is called right after chain m's
 // last byte (or before the loop when cnt[m] == 0), with c holding that chain's
 // state; chains past their end keep running on zero bytes but their results
-// are neither stored nor used.
-template <int M, int I, typename OnStop>
+// are neither stored nor used.  G lanes hold the same chain and the same arguments; they write the
+// same bytes to its row, and on_stop runs in each of them.
+template <int M, int I, int G, typename OnStop>
 __device__ __forceinline__ void wave_run(Chains<M> &c, const WaveLds &w, int tile, const uint8_t *const (&in)[M],
                                          uint8_t *const (&out)[M], const uint32_t (&cnt)[M], double dt,
                                          uint32_t n_it, int lane, OnStop on_stop) {
+    static_assert(G == 1 || M == 1, "a chain over several lanes is one chain per lane group");
+    const LaneRole<G> role(lane);
+    const int ch = lane / G;  // the lane's chain among the wave's (row m * WAVE + ch)
     uint32_t mx = 0;
 #pragma unroll
     for (int m = 0; m < M; ++m) {
-        w.in[m * WAVE + lane] = in[m];
-        w.out[m * WAVE + lane] = out[m];
-        w.cnt[m * WAVE + lane] = cnt[m];
+        w.in[m * WAVE + ch] = in[m];
+        w.out[m * WAVE + ch] = out[m];
+        w.cnt[m * WAVE + ch] = cnt[m];
         mx = cnt[m] > mx ? cnt[m] : mx;
         if (cnt[m] == 0) on_stop(m);
     }
     mx = wave_max_u32(mx);
     wave_sync();
     const size_t stride = tile_stride(tile);
-    const int rows = WAVE * M;
+    constexpr int rows = WAVE * M / G;
     for (uint32_t t0 = 0; t0 < mx; t0 += (uint32_t)tile) {
         // stage in: byte u of the wave tile -> row u / tile, column u % tile
         for (int u = lane; u < rows * tile; u += WAVE) {
@@ -297,11 +445,11 @@ __device__ __forceinline__ void wave_run(Chains<M> &c, const WaveLds &w, int til
             const uint32_t j = t0 + kk;
             uint32_t bin[M], bout[M];
 #pragma unroll
-            for (int m = 0; m < M; ++m) bin[m] = j < cnt[m] ? w.tile[(m * WAVE + lane) * stride + kk] : 0u;
-            crypt_byte<M, I>(c, bin, bout, dt, n_it);
+            for (int m = 0; m < M; ++m) bin[m] = j < cnt[m] ? w.tile[(m * WAVE + ch) * stride + kk] : 0u;
+            crypt_byte<M, I, G>(c, bin, bout, dt, n_it, role, lane);
 #pragma unroll
             for (int m = 0; m < M; ++m) {
-                if (j < cnt[m]) w.tile[(m * WAVE + lane) * stride + kk] = (uint8_t)bout[m];
+                if (j < cnt[m]) w.tile[(m * WAVE + ch) * stride + kk] = (uint8_t)bout[m];
                 if (j + 1 == cnt[m]) on_stop(m);
             }
         }
@@ -314,6 +462,29 @@ __device__ __forceinline__ void wave_run(Chains<M> &c, const WaveLds &w, int til
         }
         wave_sync();
     }
+}
+
+// ---- room for wide launches ------------------------------------------------------------
+//
+// Spreading chains over lanes costs more instructions per chain in all (3.2 times as many at G = 4), which is free
+// only on SIMDs that would idle.  A launch that may run wide is preceded by claim_kernel, which adds
+// its waves to the device's count of waves in flight and lets it run wide if all of them together are
+// at most one per SIMD; otherwise the launch runs one chain per lane (the waves it then does not need
+// end at once).  Calls that overlap on several streams so take the idle SIMDs first and then run as
+// densely as before, whatever runs beside them: every kernel of the cipher counts its waves.
+__device__ uint32_t g_waves;
+
+// Adds the waves of a workgroup that no claim counted (n > 0) or takes them off at its end (n < 0).
+__device__ __forceinline__ void count_waves(int n) {
+    if (threadIdx.x == 0) atomicAdd(&g_waves, (uint32_t)n);
+}
+
+// Clears n words (the tag accumulators), and decides whether the launch of `waves` waves that
+// follows on the stream runs wide: *wide = 1 or 0.
+__global__ void claim_kernel(unsigned long long *p, size_t n, unsigned long long *wide, uint32_t waves, uint32_t simds) {
+    const size_t t = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    for (size_t i = t; i < n; i += (size_t)gridDim.x * blockDim.x) p[i] = 0;
+    if (t == 0) *wide = atomicAdd(&g_waves, waves) + waves <= simds ? 1 : 0;
 }
 
 // ---- plain path: one message ---------------------------------------------------------
@@ -329,6 +500,7 @@ struct PlainArgs {
     uint64_t n, nb;
     uint64_t block_base;  // index of the first block (0 for a whole message)
     unsigned long long *tag_acc;
+    const unsigned long long *wide;  // G > 1: claim_kernel's answer
     StreamExtra x;        // read only by the stream instance (X = true)
 };
 
@@ -350,16 +522,18 @@ __device__ __forceinline__ void save_slot(ChainSlot &s, const Chains<1> &c) {
     s.om[0] = (uint8_t)c.om0[0]; s.om[1] = (uint8_t)c.om1[0]; s.om[2] = (uint8_t)c.om2[0];
 }
 
-// X: the stream instance (M = 1), whose lanes nb and nb + 1 may carry a.x's head and tail.
-template <int M, int I, bool X>
-__global__ __launch_bounds__(256) void plain_kernel(PlainArgs a) {
-    static_assert(!X || M == 1, "the stream instance runs one chain per lane");
-    extern __shared__ char lds[];
+// X: the stream instance (M = 1), whose chains nb and nb + 1 may be a.x's head and tail.  G lanes
+// carry each chain.
+template <int M, int I, bool X, int G>
+__device__ __forceinline__ void plain_body(const PlainArgs &a, char *lds) {
+    static_assert(!X || M == 1, "the stream instance runs one chain per lane group");
+    constexpr int ROWS = WAVE * M / G;
     const int lane = threadIdx.x % WAVE;
     const int wid = threadIdx.x / WAVE;
     const int wpw = blockDim.x / WAVE;
-    const WaveLds w = wave_lds<M>(lds + (size_t)wid * wave_lds_bytes(M, a.tile), a.tile);
-    const uint64_t base = ((uint64_t)blockIdx.x * wpw + wid) * WAVE * M;
+    const WaveLds w = wave_lds<ROWS>(lds + (size_t)wid * wave_lds_bytes(ROWS, a.tile), a.tile);
+    const uint64_t base = ((uint64_t)blockIdx.x * wpw + wid) * ROWS;
+    if (base >= a.nb + (X ? 2 : 0)) return;  // no chain
 
     Chains<M> c;
     const uint8_t *in[M];
@@ -370,13 +544,13 @@ __global__ __launch_bounds__(256) void plain_kernel(PlainArgs a) {
     double r0[3] = {a.r0[0], a.r0[1], a.r0[2]}, ap[3] = {a.ap[0], a.ap[1], a.ap[2]};
     uint8_t mu[3] = {a.mu[0], a.mu[1], a.mu[2]}, om[3] = {a.om[0], a.om[1], a.om[2]},
             k[3] = {a.k[0], a.k[1], a.k[2]};
-    // stream instance: 1 = this lane is the head chain, 2 = the tail chain
+    // stream instance: 1 = this lane's chain is the head, 2 = the tail
     const uint32_t n_head = X && a.x.head_slot ? 1u : 0u;
-    const uint64_t g0 = base + lane;
+    const uint64_t g0 = base + lane / G;
     const uint32_t role = !X || g0 < a.nb ? 0u : (g0 == a.nb && n_head ? 1u : (g0 == a.nb + n_head && a.x.tail_slot ? 2u : 0u));
 #pragma unroll
     for (int m = 0; m < M; ++m) {
-        const uint64_t g = base + (uint64_t)m * WAVE + lane;
+        const uint64_t g = base + (uint64_t)m * WAVE + lane / G;
         valid[m] = g < a.nb;
         const uint64_t off = g * a.block_len;
         cnt[m] = (valid[m] && off < a.n) ? (uint32_t)(a.n - off < a.block_len ? a.n - off : a.block_len) : 0u;
@@ -399,7 +573,7 @@ __global__ __launch_bounds__(256) void plain_kernel(PlainArgs a) {
             out[0] = a.x.tail_out;
         }
     }
-    wave_run<M, I>(c, w, (int)a.tile, in, out, cnt, a.dt, a.n_it, lane, [&](int m) __attribute__((always_inline)) {
+    wave_run<M, I, G>(c, w, (int)a.tile, in, out, cnt, a.dt, a.n_it, lane, [&](int m) __attribute__((always_inline)) {
         if constexpr (X) {
             if (role == 2 || (role == 1 && !a.x.head_complete)) {
                 save_slot(role == 2 ? *a.x.tail_slot : *a.x.head_slot, c);
@@ -413,15 +587,29 @@ __global__ __launch_bounds__(256) void plain_kernel(PlainArgs a) {
     unsigned long long t0 = 0, t1 = 0, t2 = 0;
 #pragma unroll
     for (int m = 0; m < M; ++m)
-        if (valid[m]) { t0 ^= d0[m]; t1 ^= d1[m]; t2 ^= d2[m]; }
+        if (valid[m] && lane % G == 0) { t0 ^= d0[m]; t1 ^= d1[m]; t2 ^= d2[m]; }
     t0 = wave_xor_u64(t0);
     t1 = wave_xor_u64(t1);
     t2 = wave_xor_u64(t2);
-    if (lane == 0 && base < a.nb + (X ? 2 : 0)) {
+    if (lane == 0) {
         atomicXor(&a.tag_acc[0], t0);
         atomicXor(&a.tag_acc[1], t1);
         atomicXor(&a.tag_acc[2], t2);
     }
+}
+
+template <int M, int I, bool X, int G>
+__global__ __launch_bounds__(256) void plain_kernel(PlainArgs a) {
+    extern __shared__ char lds[];
+    const int waves = blockDim.x / WAVE;
+    if constexpr (G == 1) {
+        count_waves(waves);
+        plain_body<M, I, X, 1>(a, lds);
+    } else {
+        if (*a.wide) plain_body<M, I, X, G>(a, lds);
+        else plain_body<M, I, X, 1>(a, lds);
+    }
+    count_waves(-waves);
 }
 
 // Encrypt: tag bytes to out_tag.  Decrypt: compare with stored tag, status,
@@ -468,25 +656,26 @@ __device__ __forceinline__ uint32_t find_msg(const uint64_t *prefix, uint32_t n_
     return lo;
 }
 
-template <int M, int I>
-__global__ __launch_bounds__(256) void batch_kernel(BatchArgs a) {
-    extern __shared__ char lds[];
+template <int M, int I, int G>
+__device__ __forceinline__ void batch_body(const BatchArgs &a, char *lds) {
+    constexpr int ROWS = WAVE * M / G;
     const int lane = threadIdx.x % WAVE;
     const int wid = threadIdx.x / WAVE;
-    const WaveLds w = wave_lds<M>(lds + (size_t)wid * wave_lds_bytes(M, a.tile), a.tile);
-    const uint64_t per_task = (uint64_t)WAVE * M;
+    const WaveLds w = wave_lds<ROWS>(lds + (size_t)wid * wave_lds_bytes(ROWS, a.tile), a.tile);
+    const uint64_t per_task = ROWS;
     const uint64_t n_chains = a.b.n_full + a.b.n_tail;
+    const uint64_t n_tasks = (n_chains + per_task - 1) / per_task;
 
     // No lane-conditional region may sit inside this loop: the compiler is free to merge such
     // regions across the back edge, which leaves lanes re-entering the loop without the others.
     // Every lane therefore takes part in the task grab (lane 0 adds 1, the others 0) and in the
-    // tag update (a lane past the end XORs 0).
+    // tag update (a lane past the end, or not the first of its chain's lanes, XORs 0).
     for (;;) {
         const unsigned long long grab = atomicAdd(a.b.counter, lane == 0 ? 1ull : 0ull);
         const unsigned long long task =
             ((unsigned long long)__builtin_amdgcn_readfirstlane((uint32_t)(grab >> 32)) << 32) |
             __builtin_amdgcn_readfirstlane((uint32_t)grab);
-        if (task >= a.b.n_tasks) break;
+        if (task >= n_tasks) break;
 
         Chains<M> c;
         const uint8_t *in[M];
@@ -496,7 +685,7 @@ __global__ __launch_bounds__(256) void batch_kernel(BatchArgs a) {
         unsigned long long d0[M], d1[M], d2[M];
 #pragma unroll
         for (int m = 0; m < M; ++m) {
-            const uint64_t g = task * per_task + (uint64_t)m * WAVE + lane;
+            const uint64_t g = task * per_task + (uint64_t)m * WAVE + lane / G;
             valid[m] = g < n_chains;
             uint32_t i = 0;
             uint64_t b = 0;
@@ -523,7 +712,7 @@ __global__ __launch_bounds__(256) void batch_kernel(BatchArgs a) {
             init_chain<M>(c, m, r0, ap, mu, om, k, b, md.decrypt);
             d0[m] = d1[m] = d2[m] = 0;
         }
-        wave_run<M, I>(c, w, (int)a.tile, in, out, cnt, a.dt, a.n_it, lane, [&](int m) __attribute__((always_inline)) {
+        wave_run<M, I, G>(c, w, (int)a.tile, in, out, cnt, a.dt, a.n_it, lane, [&](int m) __attribute__((always_inline)) {
             d0[m] = digest_word(c.x[m]);
             d1[m] = digest_word(c.y[m]);
             d2[m] = digest_word(c.z[m]);
@@ -532,11 +721,26 @@ __global__ __launch_bounds__(256) void batch_kernel(BatchArgs a) {
 #pragma unroll
         for (int m = 0; m < M; ++m) {
             unsigned long long *t = &a.b.tag_acc[3 * (size_t)msg[m]];
-            atomicXor(t + 0, valid[m] ? d0[m] : 0ull);
-            atomicXor(t + 1, valid[m] ? d1[m] : 0ull);
-            atomicXor(t + 2, valid[m] ? d2[m] : 0ull);
+            const bool own = valid[m] && lane % G == 0;
+            atomicXor(t + 0, own ? d0[m] : 0ull);
+            atomicXor(t + 1, own ? d1[m] : 0ull);
+            atomicXor(t + 2, own ? d2[m] : 0ull);
         }
     }
+}
+
+template <int M, int I, int G>
+__global__ __launch_bounds__(256) void batch_kernel(BatchArgs a) {
+    extern __shared__ char lds[];
+    const int waves = blockDim.x / WAVE;
+    if constexpr (G == 1) {
+        count_waves(waves);
+        batch_body<M, I, 1>(a, lds);
+    } else {
+        if (*a.b.wide) batch_body<M, I, G>(a, lds);
+        else batch_body<M, I, 1>(a, lds);
+    }
+    count_waves(-waves);
 }
 
 // One workgroup per message: tag out (encrypt) or tag check, status and zeroing (decrypt).
@@ -569,14 +773,17 @@ struct TickArgs {
     uint32_t n_it, block_len, tile;
 };
 
-template <int M, int I>
+// A tick has the device to itself as a rule, so a short one runs wide without a claim.
+template <int M, int I, int G>
 __global__ __launch_bounds__(256) void tick_kernel(TickArgs a) {
     extern __shared__ char lds[];
+    constexpr int ROWS = WAVE * M / G;
     const int lane = threadIdx.x % WAVE;
     const int wid = threadIdx.x / WAVE;
     const int wpw = blockDim.x / WAVE;
-    const WaveLds w = wave_lds<M>(lds + (size_t)wid * wave_lds_bytes(M, a.tile), a.tile);
-    const uint64_t base = ((uint64_t)blockIdx.x * wpw + wid) * WAVE * M;
+    count_waves(wpw);
+    const WaveLds w = wave_lds<ROWS>(lds + (size_t)wid * wave_lds_bytes(ROWS, a.tile), a.tile);
+    const uint64_t base = ((uint64_t)blockIdx.x * wpw + wid) * ROWS;
 
     Chains<M> c;
     const uint8_t *in[M];
@@ -585,7 +792,7 @@ __global__ __launch_bounds__(256) void tick_kernel(TickArgs a) {
     bool valid[M];
 #pragma unroll
     for (int m = 0; m < M; ++m) {
-        const uint64_t e = base + (uint64_t)m * WAVE + lane;
+        const uint64_t e = base + (uint64_t)m * WAVE + lane / G;
         valid[m] = e < a.t.n_list;
         slot[m] = valid[m] ? a.t.list[e] : 0u;
         cnt[m] = 0;
@@ -620,7 +827,7 @@ __global__ __launch_bounds__(256) void tick_kernel(TickArgs a) {
         in[m] = md.in + off;
         out[m] = md.out + off;
     }
-    wave_run<M, I>(c, w, (int)a.tile, in, out, cnt, a.dt, a.n_it, lane, [&](int m) __attribute__((always_inline)) {
+    wave_run<M, I, G>(c, w, (int)a.tile, in, out, cnt, a.dt, a.n_it, lane, [&](int m) __attribute__((always_inline)) {
         if (!valid[m]) return;
         ChainSlot &s = a.t.slots[slot[m]];
         s.r[0] = c.x[m]; s.r[1] = c.y[m]; s.r[2] = c.z[m];
@@ -628,9 +835,10 @@ __global__ __launch_bounds__(256) void tick_kernel(TickArgs a) {
         s.mu[0] = (uint8_t)c.mu0[m]; s.mu[1] = (uint8_t)c.mu1[m]; s.mu[2] = (uint8_t)c.mu2[m];
         s.om[0] = (uint8_t)c.om0[m]; s.om[1] = (uint8_t)c.om1[m]; s.om[2] = (uint8_t)c.om2[m];
     });
+    count_waves(-wpw);
 #pragma unroll
     for (int m = 0; m < M; ++m) {
-        if (!valid[m]) continue;
+        if (!valid[m] || lane % G != 0) continue;
         ChainSlot &s = a.t.slots[slot[m]];
         s.fresh = 0;
         s.pos += cnt[m];
@@ -735,21 +943,32 @@ __global__ void install_kernel(ReqDesc *reqs, ChainSlot *slots, const ReqDesc *s
     }
 }
 
+template <int V>
+using Int = std::integral_constant<int, V>;
+
 template <int M, typename F>
 hipError_t dispatch_i(uint32_t integ, F f) {
     switch (integ) {
-        case LZ_INTEGRATOR_EULER: return f(std::integral_constant<int, M>{}, std::integral_constant<int, 0>{});
-        case LZ_INTEGRATOR_EULER_FMA: return f(std::integral_constant<int, M>{}, std::integral_constant<int, 1>{});
-        case LZ_INTEGRATOR_RK4: return f(std::integral_constant<int, M>{}, std::integral_constant<int, 2>{});
+        case LZ_INTEGRATOR_EULER: return f(Int<M>{}, Int<0>{}, Int<1>{});
+        case LZ_INTEGRATOR_EULER_FMA: return f(Int<M>{}, Int<1>{}, Int<1>{});
+        case LZ_INTEGRATOR_RK4: return f(Int<M>{}, Int<2>{}, Int<1>{});
         default: return hipErrorInvalidValue;
     }
 }
 
-// Calls f(M, I) with the compile-time chains-per-lane and integrator of the launch.
+// The launches with several lanes per chain (lanes_per_chain names no others).
 template <typename F>
-hipError_t dispatch(int m, uint32_t integ, F f) {
+hipError_t dispatch_wide(int g, uint32_t integ, F f) {
+    if (g == 4 && integ == LZ_INTEGRATOR_EULER) return f(Int<1>{}, Int<0>{}, Int<4>{});
+    if (g == 4 && integ == LZ_INTEGRATOR_RK4) return f(Int<1>{}, Int<2>{}, Int<4>{});
+    return hipErrorInvalidValue;
+}
+
+// Calls f(M, I, G) with the compile-time chains per lane, integrator and lanes per chain of the launch.
+template <typename F>
+hipError_t dispatch(int m, int g, uint32_t integ, F f) {
     switch (m) {
-        case 1: return dispatch_i<1>(integ, f);
+        case 1: return g == 1 ? dispatch_i<1>(integ, f) : dispatch_wide(g, integ, f);
         case 2: return dispatch_i<2>(integ, f);
         case 4: return dispatch_i<4>(integ, f);
         default: return hipErrorInvalidValue;
@@ -758,7 +977,19 @@ hipError_t dispatch(int m, uint32_t integ, F f) {
 
 }  // namespace
 
-size_t lds_bytes(const KernelShape &sh) { return (size_t)(sh.wg / WAVE) * wave_lds_bytes(sh.m, sh.tile); }
+// a wide launch keeps the LDS of one chain per lane: it may have to run that way
+size_t lds_bytes(const KernelShape &sh) { return (size_t)(sh.wg / WAVE) * wave_lds_bytes(WAVE * sh.m, sh.tile); }
+
+// Lanes per chain of a launch of `chains` chains with m per lane on `simds` SIMDs.  Four, as long as
+// the chains then make up at most one wave per SIMD: such a launch takes one chain's serial time, and
+// a step takes 44.6 clocks instead of 56.6 (RK4: 190 instead of 262).  With more chains a second wave would
+// share a SIMD, and 2 x 44.6 clocks are more than the 56.6 of one chain per lane.  The fused Euler
+// map has 9 instructions in either form.  Measured: 64 KiB in 14.5 ms (one chain per lane 18.3), 3 MB in
+// 14.6 (18.5), 256 KiB of the RK4 format in 60.7 (92.0), 2048 sequential messages in 230 (292).
+int lanes_per_chain(uint64_t chains, int m, uint32_t integ, int simds) {
+    if (m != 1 || integ == LZ_INTEGRATOR_EULER_FMA) return 1;
+    return chains * 4 <= (uint64_t)simds * WAVE ? 4 : 1;
+}
 
 bool shape_valid(const KernelShape &sh, const DevInfo &dev) {
     if (sh.m != 1 && sh.m != 2 && sh.m != 4) return false;
@@ -797,23 +1028,41 @@ PlainArgs plain_args(const KernelShape &sh, const lz_key &key, const lz_params &
     a.nb = nb;
     a.block_base = block_base;
     a.tag_acc = tag_acc;
+    a.wide = tag_acc + TAG_WIDE;
     return a;
 }
 
+// Workgroups of a launch of `chains` chains.
+uint64_t grid_of(const KernelShape &sh, uint64_t chains) {
+    const uint64_t per_wg = (uint64_t)sh.wg * sh.m / sh.g;
+    return (chains + per_wg - 1) / per_wg;
+}
+
 }  // namespace
+
+hipError_t launch_claim(const KernelShape &sh, uint64_t grid, unsigned long long *p, size_t n,
+                        unsigned long long *wide, hipStream_t s) {
+    const unsigned blocks = (unsigned)((n + 255) / 256 < 1024 ? (n + 255) / 256 : 1024);
+    hipLaunchKernelGGL(claim_kernel, dim3(blocks ? blocks : 1), dim3(256), 0, s, p, n, wide,
+                       (uint32_t)(grid * sh.wg / WAVE), (uint32_t)sh.simds);
+    return hipGetLastError();
+}
 
 hipError_t launch_plain(const KernelShape &sh, const lz_key &key, const lz_params &prm, int decrypt,
                         const uint8_t *in, uint8_t *out, uint64_t n, unsigned long long *tag_acc, hipStream_t s,
                         uint64_t block_base) {
     const uint64_t nb = n == 0 ? 1 : (n + prm.block_len - 1) / prm.block_len;
     const PlainArgs a = plain_args(sh, key, prm, decrypt, in, out, n, nb, tag_acc, block_base);
-    const uint64_t per_wg = (uint64_t)sh.wg * sh.m;
-    const uint64_t grid = (a.nb + per_wg - 1) / per_wg;
+    const uint64_t grid = grid_of(sh, nb);
+    const hipError_t e = sh.g > 1 ? launch_claim(sh, grid, tag_acc, TAG_WORDS, tag_acc + TAG_WIDE, s)
+                                  : launch_fill_u64(tag_acc, TAG_WORDS, s);
+    if (e != hipSuccess) return e;
     const size_t lds = lds_bytes(sh);
-    return dispatch(sh.m, prm.integrator, [&](auto mc, auto ic) {
+    return dispatch(sh.m, sh.g, prm.integrator, [&](auto mc, auto ic, auto gc) {
         constexpr int M = decltype(mc)::value;
         constexpr int I = decltype(ic)::value;
-        hipLaunchKernelGGL((plain_kernel<M, I, false>), dim3((unsigned)grid), dim3(sh.wg), lds, s, a);
+        constexpr int G = decltype(gc)::value;
+        hipLaunchKernelGGL((plain_kernel<M, I, false, G>), dim3((unsigned)grid), dim3(sh.wg), lds, s, a);
         return hipGetLastError();
     });
 }
@@ -821,16 +1070,23 @@ hipError_t launch_plain(const KernelShape &sh, const lz_key &key, const lz_param
 hipError_t launch_stream_step(const KernelShape &shape, const lz_key &key, const lz_params &prm, int decrypt,
                               const uint8_t *in, uint8_t *out, uint64_t full, uint64_t block_base,
                               const StreamExtra &x, unsigned long long *tag_acc, hipStream_t s) {
-    const KernelShape sh{1, shape.wg, shape.tile, shape.wps};
-    PlainArgs a = plain_args(sh, key, prm, decrypt, in, out, full * prm.block_len, full, tag_acc, block_base);
-    a.x = x;
     const uint64_t lanes = full + (x.head_slot ? 1 : 0) + (x.tail_slot ? 1 : 0);
     if (lanes == 0) return hipSuccess;
-    const uint64_t grid = (lanes + sh.wg - 1) / sh.wg;
+    KernelShape sh{1, shape.wg, shape.tile, shape.wps};
+    sh.simds = shape.simds;
+    sh.g = lanes_per_chain(lanes, 1, prm.integrator, sh.simds);
+    PlainArgs a = plain_args(sh, key, prm, decrypt, in, out, full * prm.block_len, full, tag_acc, block_base);
+    a.x = x;
+    const uint64_t grid = grid_of(sh, lanes);
+    if (sh.g > 1) {
+        const hipError_t e = launch_claim(sh, grid, nullptr, 0, tag_acc + TAG_WIDE, s);
+        if (e != hipSuccess) return e;
+    }
     const size_t lds = lds_bytes(sh);
-    return dispatch_i<1>(prm.integrator, [&](auto, auto ic) {
+    return dispatch(1, sh.g, prm.integrator, [&](auto, auto ic, auto gc) {
         constexpr int I = decltype(ic)::value;
-        hipLaunchKernelGGL((plain_kernel<1, I, true>), dim3((unsigned)grid), dim3(sh.wg), lds, s, a);
+        constexpr int G = decltype(gc)::value;
+        hipLaunchKernelGGL((plain_kernel<1, I, true, G>), dim3((unsigned)grid), dim3(sh.wg), lds, s, a);
         return hipGetLastError();
     });
 }
@@ -859,13 +1115,18 @@ hipError_t launch_batch(const KernelShape &sh, const DevInfo &dev, const lz_para
     const uint64_t waves = (uint64_t)dev.cus * 4 * sh.wps;
     const uint64_t wpw = (uint64_t)sh.wg / WAVE;
     uint64_t grid = (waves + wpw - 1) / wpw;
-    const uint64_t need = (b.n_tasks + wpw - 1) / wpw;
+    const uint64_t need = grid_of(sh, b.n_full + b.n_tail);
     if (need < grid) grid = need ? need : 1;
+    const size_t words = 3 * (size_t)b.n_msg + 1;  // tags and the work-queue counter
+    const hipError_t e = sh.g > 1 ? launch_claim(sh, grid, b.tag_acc, words, b.wide, s)
+                                  : launch_fill_u64(b.tag_acc, words, s);
+    if (e != hipSuccess) return e;
     const size_t lds = lds_bytes(sh);
-    return dispatch(sh.m, prm.integrator, [&](auto mc, auto ic) {
+    return dispatch(sh.m, sh.g, prm.integrator, [&](auto mc, auto ic, auto gc) {
         constexpr int M = decltype(mc)::value;
         constexpr int I = decltype(ic)::value;
-        hipLaunchKernelGGL((batch_kernel<M, I>), dim3((unsigned)grid), dim3(sh.wg), lds, s, a);
+        constexpr int G = decltype(gc)::value;
+        hipLaunchKernelGGL((batch_kernel<M, I, G>), dim3((unsigned)grid), dim3(sh.wg), lds, s, a);
         return hipGetLastError();
     });
 }
@@ -888,13 +1149,13 @@ hipError_t launch_tick(const KernelShape &sh, const lz_params &prm, const TickDe
     a.n_it = prm.n_it;
     a.block_len = prm.block_len;
     a.tile = (uint32_t)sh.tile;
-    const uint64_t per_wg = (uint64_t)sh.wg * sh.m;
-    const uint64_t grid = (t.n_list + per_wg - 1) / per_wg;
+    const uint64_t grid = grid_of(sh, t.n_list);
     const size_t lds = lds_bytes(sh);
-    return dispatch(sh.m, prm.integrator, [&](auto mc, auto ic) {
+    return dispatch(sh.m, sh.g, prm.integrator, [&](auto mc, auto ic, auto gc) {
         constexpr int M = decltype(mc)::value;
         constexpr int I = decltype(ic)::value;
-        hipLaunchKernelGGL((tick_kernel<M, I>), dim3((unsigned)grid), dim3(sh.wg), lds, s, a);
+        constexpr int G = decltype(gc)::value;
+        hipLaunchKernelGGL((tick_kernel<M, I, G>), dim3((unsigned)grid), dim3(sh.wg), lds, s, a);
         return hipGetLastError();
     });
 }
@@ -913,7 +1174,7 @@ hipError_t launch_unit_theta(const uint8_t *p, const uint8_t *o3, size_t n, doub
 
 hipError_t launch_unit_lorenz(const lz_params &prm, double *r, size_t n, uint32_t steps, hipStream_t s) {
     const size_t blocks = (n + 255) / 256;
-    return dispatch_i<1>(prm.integrator, [&](auto, auto ic) {
+    return dispatch_i<1>(prm.integrator, [&](auto, auto ic, auto) {
         constexpr int I = decltype(ic)::value;
         hipLaunchKernelGGL((unit_lorenz_kernel<I>), dim3((unsigned)blocks), dim3(256), 0, s, r, n, prm.dt, steps);
         return hipGetLastError();

@@ -12,8 +12,7 @@ namespace lz {
 namespace {
 
 constexpr size_t SCRATCH_WORDS = LZ_NOALLOC_SCRATCH_BYTES / sizeof(unsigned long long);
-constexpr size_t TAG_WORDS = 3;  // XOR accumulator of the block digests (x, y, z words)
-static_assert(TAG_WORDS <= SCRATCH_WORDS, "the tag accumulator must fit the scratch array");
+static_assert(TAG_WORDS + 1 <= SCRATCH_WORDS, "the tag accumulator must fit the scratch array");
 
 // One copy per GPU, held until the process ends.  Host code never passes this name to a kernel or
 // a copy: it reaches the memory only through the address hipGetSymbolAddress gave for the device.
@@ -22,6 +21,7 @@ static __device__ __align__(256) unsigned long long scratch[SCRATCH_WORDS];
 struct DevScratch {
     unsigned long long *ptr;  // this device's copy of `scratch`
     int lds_per_wg_max;
+    int simds;
     bool ready;
 };
 
@@ -38,7 +38,10 @@ int device_scratch(int dev, DevScratch *out) {
         if (!p) return fail(LZ_E_HIP, "hipGetSymbolAddress returned no address for the scratch array");
         int lds = 0;
         LZ_HIP(hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev));
+        int cus = 0;
+        LZ_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
         d.ptr = static_cast<unsigned long long *>(p);
+        d.simds = cus * CU_SIMDS;
         d.lds_per_wg_max = lds;
         d.ready = true;
     }
@@ -63,7 +66,8 @@ extern "C" int lz_decrypt_noalloc(const lz_params *prm, const uint8_t *pw, size_
     if (n_pw == 0 || n_pw > LZ_MAX_PASSWORD) return fail(LZ_E_INVAL, "password length must be 1..64");
     if (n_c < LZ_TAG_BYTES) return fail(LZ_E_INVAL, "ciphertext shorter than the 24-byte tag");
     const size_t n = n_c - LZ_TAG_BYTES;
-    if (int rc = check_blocks(p, n, nullptr)) return rc;
+    uint64_t nb = 0;
+    if (int rc = check_blocks(p, n, &nb)) return rc;
     if (!d_P && n) return fail(LZ_E_INVAL, "NULL plaintext buffer");
     lz_key key;
     if (int rc = key_setup(pw, n_pw, p, key)) return rc;
@@ -76,10 +80,11 @@ extern "C" int lz_decrypt_noalloc(const lz_params *prm, const uint8_t *pw, size_
     // the plain path's default shape (one chain per lane, 4 waves per workgroup, 128-byte tiles)
     KernelShape sh{1, 256, 128, 4};
     if (lds_bytes(sh) > (size_t)d.lds_per_wg_max) sh = KernelShape{1, 64, 32, 4};
+    sh.simds = d.simds;
+    sh.g = lanes_per_chain(nb, sh.m, p.integrator, sh.simds);
 
     hipStream_t s = static_cast<hipStream_t>(stream);
-    // the accumulator keeps the previous call's value: clear it with a kernel (no memset node under capture)
-    LZ_HIP(launch_fill_u64(d.ptr, TAG_WORDS, s));
+    // the accumulator keeps the previous call's value: launch_plain clears it with a kernel (no memset node under capture)
     LZ_HIP(launch_plain(sh, key, p, 1, d_C, d_P, n, d.ptr, s));
     LZ_HIP(launch_plain_finalize(1, d.ptr, d_C + n, nullptr, d_status, d_P, n, s));
     return LZ_OK;

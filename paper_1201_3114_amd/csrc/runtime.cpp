@@ -85,7 +85,9 @@ lz_launch to_launch(const KernelShape &s) {
 // least two waves of them.
 KernelShape plain_shape(const lz_ctx *c, uint64_t nb) {
     KernelShape sh = c->shape;
-    if (sh.m > 1 && nb < (uint64_t)sh.m * c->dev.cus * 4 * WAVE_LANES * 2) sh.m = 1;
+    if (sh.m > 1 && nb < (uint64_t)sh.m * c->dev.cus * CU_SIMDS * WAVE_LANES * 2) sh.m = 1;
+    sh.simds = c->dev.cus * CU_SIMDS;
+    sh.g = lanes_per_chain(nb, sh.m, c->prm.integrator, sh.simds);
     return sh;
 }
 
@@ -179,7 +181,7 @@ extern "C" int lz_context_create(int device, const lz_params *prm, lz_ctx **out)
     // one chain per lane, 4 waves per workgroup, 128-byte tiles (one L2 line per chain per refill)
     c->shape = KernelShape{1, 256, 128, 4};
     if (!shape_valid(c->shape, c->dev)) c->shape = KernelShape{1, 64, 32, 4};
-    hipError_t e = hipMalloc(&c->ws_tag, 4 * sizeof(unsigned long long));
+    hipError_t e = hipMalloc(&c->ws_tag, (TAG_WORDS + 1) * sizeof(unsigned long long));
     if (e == hipSuccess) e = hipMalloc(&c->ws_status, sizeof(int32_t));
     if (e == hipSuccess) e = hipHostMalloc(&c->host_status, sizeof(int32_t), hipHostMallocDefault);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&c->last_event, hipEventDisableTiming);
@@ -243,7 +245,6 @@ extern "C" int lz_encrypt_key(lz_ctx *c, const lz_key *key, const uint8_t *d_P, 
     hipStream_t s = (hipStream_t)stream;
     LZ_HIP(hipSetDevice(c->device));
     if (int rc = order_after(s, c->last_stream, c->last_event, c->has_last)) return rc;
-    LZ_HIP(launch_fill_u64(c->ws_tag, 3, s));
     LZ_HIP(launch_plain(plain_shape(c, nb), *key, c->prm, 0, d_P, d_C, n, c->ws_tag, s));
     LZ_HIP(launch_plain_finalize(0, c->ws_tag, nullptr, d_C + n, nullptr, nullptr, n, s));
     return record(s, c->last_stream, c->last_event, c->has_last);
@@ -261,7 +262,6 @@ extern "C" int lz_decrypt_key(lz_ctx *c, const lz_key *key, const uint8_t *d_C, 
     LZ_HIP(hipSetDevice(c->device));
     if (int rc = order_after(s, c->last_stream, c->last_event, c->has_last)) return rc;
     int32_t *st = d_status ? d_status : c->ws_status;
-    LZ_HIP(launch_fill_u64(c->ws_tag, 3, s));
     LZ_HIP(launch_plain(plain_shape(c, nb), *key, c->prm, 1, d_C, d_P, n, c->ws_tag, s));
     LZ_HIP(launch_plain_finalize(1, c->ws_tag, d_C + n, nullptr, st, d_P, n, s));
     if (d_status) return record(s, c->last_stream, c->last_event, c->has_last);
@@ -380,7 +380,7 @@ int batch_create(lz_ctx *c, const lz_params &prm, int decrypt, size_t n_msg, con
     const size_t o_tail = align_up(o_prefix + (n_msg + 1) * sizeof(uint64_t), 256);
     const size_t o_slot = align_up(o_tail + std::max<size_t>(tails.size(), 1) * sizeof(uint32_t), 256);
     const size_t o_tag = o_slot + 256;
-    const size_t total = o_tag + (3 * n_msg + 1) * sizeof(unsigned long long);
+    const size_t total = o_tag + (3 * n_msg + 2) * sizeof(unsigned long long);  // tags, counter, wide
     hipError_t e = hipMalloc(&b->dmem, total);
     if (e != hipSuccess) {
         batch_free(b);
@@ -406,10 +406,11 @@ int batch_create(lz_ctx *c, const lz_params &prm, int decrypt, size_t n_msg, con
     d.n_msg = (uint32_t)n_msg;
     d.n_tail = (uint32_t)tails.size();
     d.n_full = prefix[n_msg];
-    const uint64_t per_task = 64ull * sh.m;
-    d.n_tasks = (d.n_full + d.n_tail + per_task - 1) / per_task;
+    sh.simds = c->dev.cus * CU_SIMDS;
+    sh.g = lanes_per_chain(d.n_full + d.n_tail, sh.m, prm.integrator, sh.simds);
     d.tag_acc = reinterpret_cast<unsigned long long *>(base + o_tag);
     d.counter = d.tag_acc + 3 * n_msg;
+    d.wide = d.counter + 1;
     d.status_ref = b->status_slot;
 
     // capture [reset, persistent kernel, finalize]
@@ -421,11 +422,10 @@ int batch_create(lz_ctx *c, const lz_params &prm, int decrypt, size_t n_msg, con
     }
     e = hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal);
     if (e == hipSuccess) {
-        hipError_t e1 = launch_fill_u64(d.tag_acc, 3 * n_msg + 1, cap);
-        hipError_t e2 = e1 == hipSuccess ? launch_batch(sh, c->dev, prm, d, cap) : e1;
-        hipError_t e3 = e2 == hipSuccess ? launch_batch_finalize(d, b->decrypt, cap) : e2;
+        hipError_t e1 = launch_batch(sh, c->dev, prm, d, cap);
+        hipError_t e2 = e1 == hipSuccess ? launch_batch_finalize(d, b->decrypt, cap) : e1;
         e = hipStreamEndCapture(cap, &b->graph);
-        if (e3 != hipSuccess) e = e3;
+        if (e2 != hipSuccess) e = e2;
     }
     if (e == hipSuccess) e = hipGraphInstantiate(&b->exec, b->graph, nullptr, nullptr, 0);
     hipStreamDestroy(cap);

@@ -170,6 +170,7 @@ struct TickSlot {
     uint64_t bytes = 0;
     uint64_t seq = 0;     // tick sequence number (1, 2, ...)
     uint32_t waves = 0;   // waves per SIMD of the tick's chains, at most
+    int g = 1;            // lanes per chain of the tick
     bool late = false;    // queued while the tick before it ran: its start shows whether in time
 };
 
@@ -203,9 +204,9 @@ struct lz_server {
     uint64_t hbm_fixed = 0;
     uint64_t tick_seq = 0, done_seq = 0;  // last tick queued, last tick completed (ticks complete in order)
     // late admission (server thread only): a tick's duration per wave per SIMD (a running mean of
-    // the measured ticks), when the last completed tick was seen to end, and when the next step
+    // the measured ticks with one lane per chain, and of those with several), when the last completed tick was seen to end, and when the next step
     // may start
-    double tick_ns_per_wave = 0, late_margin_ns = LATE_MARGIN_START_NS;
+    double tick_ns_per_wave[2] = {0, 0}, late_margin_ns = LATE_MARGIN_START_NS;
     uint64_t tick_end_ns = 0, next_step_ns = 0;
     // shared with submitters / pollers
     std::mutex mu;
@@ -301,7 +302,8 @@ int complete_tick(lz_server *s, TickSlot &t) {
     const bool timed = hipEventElapsedTime(&ms, t.ev_start, t.ev_end) == hipSuccess;
     if (timed && t.waves) {
         const double per = (double)ms * 1e6 / t.waves;
-        s->tick_ns_per_wave = s->tick_ns_per_wave > 0 ? 0.75 * s->tick_ns_per_wave + 0.25 * per : per;
+        double &mean = s->tick_ns_per_wave[t.g > 1];
+        mean = mean > 0 ? 0.75 * mean + 0.25 * per : per;
     }
     {
         std::lock_guard<std::mutex> g(s->mu);  // stats are read by lz_server_stats_get on other threads
@@ -545,11 +547,14 @@ int server_step(lz_server *s) {
         td.done_count = t.d_done;
         td.done_queue = t.d_done + 2;
         LZ_HIP(hipEventRecord(t.ev_start, st));
-        LZ_HIP(launch_tick(s->shape, s->ctx->prm, td, st));
+        KernelShape sh = s->shape;
+        sh.g = lanes_per_chain(n_list, sh.m, s->ctx->prm.integrator, (int)(s->simd_chains / WAVE_LANES));
+        LZ_HIP(launch_tick(sh, s->ctx->prm, td, st));
         LZ_HIP(hipEventRecord(t.ev_end, st));
         t.bytes = tick_bytes;
         t.seq = seq;
         t.waves = (uint32_t)((n_list + s->simd_chains - 1) / s->simd_chains);
+        t.g = sh.g;
         t.late = s->ts[s->cur ^ 1].in_flight;
         s->tick_seq = seq;
         t.in_flight = true;
@@ -562,7 +567,7 @@ int server_step(lz_server *s) {
         // the tick queued above started when the previous one ended: the next step waits until
         // shortly before it is expected to end, so that the tick after it takes the requests
         // that arrive meanwhile (and not one tick later)
-        const double est = s->tick_ns_per_wave * t.waves;
+        const double est = s->tick_ns_per_wave[t.g > 1] * t.waves;
         if (t.in_flight && est > s->late_margin_ns)
             s->next_step_ns = s->tick_end_ns + (uint64_t)(est - s->late_margin_ns);
     }

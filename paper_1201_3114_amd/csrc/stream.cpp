@@ -32,7 +32,7 @@ struct lz_stream {
     lz_key key;
     uint64_t pos;        // bytes consumed so far
     bool finished;
-    void *dmem;          // two ChainSlots, then 3 tag words (+1 pad), then the status word
+    void *dmem;          // two ChainSlots, then TAG_WORDS tag words and the one after them, then the status word
     ChainSlot *slot[2];  // slot[cur] holds the pending partial block's checkpoint
     int cur;
     unsigned long long *tag;
@@ -92,7 +92,7 @@ extern "C" int lz_stream_open(lz_ctx *c, int decrypt, const uint8_t *pw, size_t 
         delete st;
         return rc;
     }
-    const size_t bytes = 2 * sizeof(ChainSlot) + 4 * sizeof(unsigned long long) + sizeof(int32_t);
+    const size_t bytes = 2 * sizeof(ChainSlot) + (TAG_WORDS + 1) * sizeof(unsigned long long) + sizeof(int32_t);
     hipError_t e = hipMalloc(&st->dmem, bytes);
     if (e == hipSuccess) e = hipMemset(st->dmem, 0, bytes);
     if (e == hipSuccess) e = hipHostMalloc(&st->h_status, sizeof(int32_t), hipHostMallocDefault);
@@ -107,7 +107,7 @@ extern "C" int lz_stream_open(lz_ctx *c, int decrypt, const uint8_t *pw, size_t 
     st->slot[1] = reinterpret_cast<ChainSlot *>(base + sizeof(ChainSlot));
     st->cur = 0;
     st->tag = reinterpret_cast<unsigned long long *>(base + 2 * sizeof(ChainSlot));
-    st->status = reinterpret_cast<int32_t *>(base + 2 * sizeof(ChainSlot) + 4 * sizeof(unsigned long long));
+    st->status = reinterpret_cast<int32_t *>(base + 2 * sizeof(ChainSlot) + (TAG_WORDS + 1) * sizeof(unsigned long long));
     *out = st;
     return LZ_OK;
 }
@@ -139,7 +139,9 @@ int stream_step(lz_stream *st, const uint8_t *d_in, size_t n, uint8_t *d_out, hi
         x.tail_cnt = (uint32_t)rem;
         x.tail_block = (pos0 + o) / B;
     }
-    LZ_HIP(launch_stream_step(c->shape, st->key, c->prm, st->decrypt, d_in + h, d_out + h, full, (pos0 + h) / B, x,
+    KernelShape sh = c->shape;
+    sh.simds = c->dev.cus * CU_SIMDS;
+    LZ_HIP(launch_stream_step(sh, st->key, c->prm, st->decrypt, d_in + h, d_out + h, full, (pos0 + h) / B, x,
                               st->tag, s));
     if (rem > 0) st->cur ^= 1;
     st->pos = pos0 + n;
