@@ -9,6 +9,12 @@
 // LDS with lane-contiguous (coalesced) global loads, the lanes consume their
 // own chain's bytes from LDS, write the output bytes back in place, and the
 // wave stores the tile with lane-contiguous global stores.
+//
+// A call with fewer chains than the chip has lanes takes its chains' serial
+// time, which is the number of instructions of one step times four clocks.  For
+// these a chain spreads over the 4 lanes of a quad or the 16 of a row, one
+// coordinate per lane or bank (G = 4, 16 below): the three coordinates'
+// operations share instructions.
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -168,6 +174,17 @@ struct LaneRole<4> {
     }
 };
 template <>
+struct LaneRole<16> {
+    double m, k, s, one;
+    __device__ explicit LaneRole(int lane) {
+        const int r = (lane >> 2) & 3;
+        m = r == 0 ? -1.0 : 0.0;
+        k = r == 1 ? 1.0 : (r == 2 ? BETA : 0.0);
+        s = r == 3 ? 0.0 : (r == 1 ? -1.0 : 1.0);
+        one = 1.0;
+    }
+};
+template <>
 struct LaneRole<1> {
     __device__ explicit LaneRole(int) {}
 };
@@ -265,6 +282,75 @@ __device__ __forceinline__ void quad_steps(double &x, double &y, double &z, doub
     z = dpp_f64<0xAA>(v);
 }
 
+// ---- one chain over a row of 16 lanes -------------------------------------------------
+//
+// A row's binary64 instruction can read one lane of the row in all lanes (row_newbcast), so an
+// increment travels and is added in one v_fmac_f64, where a quad needs two moves and the addition.
+// Bank 0 (lanes 0-3 of the row) computes x, bank 1 y, bank 2 z; bank 3 holds zeros.  Each bank keeps
+// what it needs of the coordinates, all advanced by the same increments t = dt (dx, dy, dz) and so
+// equal to the last bit:
+//
+//     w  = (x, y, z)      s1 = (y, z, y)      c = (sigma, x, x)      s2 = (-x, rho, 0)
+//     t = s s1 + s2       (y - x, rho - z, y)          w  += t
+//     t = t c             (sigma (y-x), x (rho-z), xy) s2 -= t                  bank 0
+//     t = t - u           (dx, dy, dz)                 s1 += t of bank 1        banks 0, 2
+//     t = t dt                                         c  += t of bank 0        banks 1, 2
+//                                                      u   = (0, y, beta z)
+//                                                      s1 += t of bank 2        bank 1
+//
+// 10 instructions (8 for the fused Euler map, whose increments carry dt in the v_fmac_f64) in this order,
+// which keeps two instructions between a write and a DPP instruction that reads it, s1's two
+// masked additions among them.  Measured with one wave per SIMD: 40.6 clocks per step, against 44.6 in a quad.  A
+// wave holds 4 chains.
+
+template <int I>
+__device__ __forceinline__ void row_steps(double &x, double &y, double &z, double dt, uint32_t n_it,
+                                          const LaneRole<16> &role, int lane) {
+    const int r = (lane >> 2) & 3;
+    double w = r == 0 ? x : (r == 1 ? y : (r == 2 ? z : 0.0));
+    double s1 = r == 1 ? z : (r == 3 ? 0.0 : y);
+    double c = r == 0 ? SIGMA : (r == 3 ? 0.0 : x);
+    double s2 = r == 0 ? -x : (r == 1 ? RHO : 0.0);
+    double u = role.k * w, t;
+    uint32_t q = n_it / 60, rest = n_it % 60;
+    if constexpr (I == LZ_INTEGRATOR_EULER_FMA) {
+        const double dtv = dt, mdt = role.m * dt;
+        asm volatile(LZ_STEP_LOOP(
+                         "v_fma_f64 %[t], %[s], %[s1], %[s2]\n"
+                         "v_fma_f64 %[t], %[t], %[c], -%[u]\n"
+                         "v_fma_f64 %[w], %[dt], %[t], %[w]\n"
+                         "v_fma_f64 %[s2], %[mdt], %[t], %[s2]\n"
+                         "v_fmac_f64_dpp %[s1], %[t], %[dt] row_newbcast:4 row_mask:0xf bank_mask:0x5\n"
+                         "v_fmac_f64_dpp %[c], %[t], %[dt] row_newbcast:0 row_mask:0xf bank_mask:0x6\n"
+                         "v_mul_f64 %[u], %[k], %[w]\n"
+                         "v_fmac_f64_dpp %[s1], %[t], %[dt] row_newbcast:8 row_mask:0xf bank_mask:0x2\n")
+                     : [w] "+v"(w), [s1] "+v"(s1), [c] "+v"(c), [s2] "+v"(s2), [u] "+v"(u), [t] "=&v"(t), [q] "+s"(q),
+                       [r] "+s"(rest)
+                     : [k] "v"(role.k), [s] "v"(role.s), [dt] "v"(dtv), [mdt] "v"(mdt)
+                     : "scc");
+    } else {
+        static_assert(I == LZ_INTEGRATOR_EULER, "this integrator has no row form");
+        asm volatile(LZ_STEP_LOOP(
+                         "v_fma_f64 %[t], %[s], %[s1], %[s2]\n"
+                         "v_mul_f64 %[t], %[t], %[c]\n"
+                         "v_add_f64 %[t], %[t], -%[u]\n"
+                         "v_mul_f64 %[t], %[t], %[dt]\n"
+                         "v_add_f64 %[w], %[w], %[t]\n"
+                         "v_fma_f64 %[s2], %[m], %[t], %[s2]\n"
+                         "v_fmac_f64_dpp %[s1], %[t], %[one] row_newbcast:4 row_mask:0xf bank_mask:0x5\n"
+                         "v_fmac_f64_dpp %[c], %[t], %[one] row_newbcast:0 row_mask:0xf bank_mask:0x6\n"
+                         "v_mul_f64 %[u], %[k], %[w]\n"
+                         "v_fmac_f64_dpp %[s1], %[t], %[one] row_newbcast:8 row_mask:0xf bank_mask:0x2\n")
+                     : [w] "+v"(w), [s1] "+v"(s1), [c] "+v"(c), [s2] "+v"(s2), [u] "+v"(u), [t] "=&v"(t), [q] "+s"(q),
+                       [r] "+s"(rest)
+                     : [k] "v"(role.k), [s] "v"(role.s), [m] "v"(role.m), [one] "v"(role.one), [dt] "s"(dt)
+                     : "scc");
+    }
+    x = dpp_f64<0x150>(w);  // row_newbcast of lanes 0, 4, 8
+    y = dpp_f64<0x154>(w);
+    z = dpp_f64<0x158>(w);
+}
+
 // State of the M chains of one lane.
 template <int M>
 struct Chains {
@@ -327,7 +413,8 @@ __device__ __forceinline__ void crypt_byte(Chains<M> &c, const uint32_t (&bin)[M
         c.z[m] = s == 2 ? moved : c.z[m];
     }
     // Step 2 (cont.): r <- F^(n_it)(r)
-    if constexpr (G == 4) quad_steps<I>(c.x[0], c.y[0], c.z[0], dt, n_it, role, lane);
+    if constexpr (G == 16) row_steps<I>(c.x[0], c.y[0], c.z[0], dt, n_it, role, lane);
+    else if constexpr (G == 4) quad_steps<I>(c.x[0], c.y[0], c.z[0], dt, n_it, role, lane);
     else lorenz_steps<M, I>(c.x, c.y, c.z, dt, n_it);
 #pragma unroll
     for (int m = 0; m < M; ++m) {
@@ -466,8 +553,8 @@ __device__ __forceinline__ void wave_run(Chains<M> &c, const WaveLds &w, int til
 
 // ---- room for wide launches ------------------------------------------------------------
 //
-// Spreading chains over lanes costs more instructions per chain in all (3.2 times as many at G = 4), which is free
-// only on SIMDs that would idle.  A launch that may run wide is preceded by claim_kernel, which adds
+// Spreading chains over lanes costs more instructions per chain in all (3.2 times as many at G = 4, 11.5
+// times at G = 16), which is free only on SIMDs that would idle.  A launch that may run wide is preceded by claim_kernel, which adds
 // its waves to the device's count of waves in flight and lets it run wide if all of them together are
 // at most one per SIMD; otherwise the launch runs one chain per lane (the waves it then does not need
 // end at once).  Calls that overlap on several streams so take the idle SIMDs first and then run as
@@ -959,6 +1046,8 @@ hipError_t dispatch_i(uint32_t integ, F f) {
 // The launches with several lanes per chain (lanes_per_chain names no others).
 template <typename F>
 hipError_t dispatch_wide(int g, uint32_t integ, F f) {
+    if (g == 16 && integ == LZ_INTEGRATOR_EULER) return f(Int<1>{}, Int<0>{}, Int<16>{});
+    if (g == 16 && integ == LZ_INTEGRATOR_EULER_FMA) return f(Int<1>{}, Int<1>{}, Int<16>{});
     if (g == 4 && integ == LZ_INTEGRATOR_EULER) return f(Int<1>{}, Int<0>{}, Int<4>{});
     if (g == 4 && integ == LZ_INTEGRATOR_RK4) return f(Int<1>{}, Int<2>{}, Int<4>{});
     return hipErrorInvalidValue;
@@ -980,15 +1069,20 @@ hipError_t dispatch(int m, int g, uint32_t integ, F f) {
 // a wide launch keeps the LDS of one chain per lane: it may have to run that way
 size_t lds_bytes(const KernelShape &sh) { return (size_t)(sh.wg / WAVE) * wave_lds_bytes(WAVE * sh.m, sh.tile); }
 
-// Lanes per chain of a launch of `chains` chains with m per lane on `simds` SIMDs.  Four, as long as
-// the chains then make up at most one wave per SIMD: such a launch takes one chain's serial time, and
-// a step takes 44.6 clocks instead of 56.6 (RK4: 190 instead of 262).  With more chains a second wave would
-// share a SIMD, and 2 x 44.6 clocks are more than the 56.6 of one chain per lane.  The fused Euler
-// map has 9 instructions in either form.  Measured: 64 KiB in 14.5 ms (one chain per lane 18.3), 3 MB in
-// 14.6 (18.5), 256 KiB of the RK4 format in 60.7 (92.0), 2048 sequential messages in 230 (292).
+// Lanes per chain of a launch of `chains` chains with m per lane on `simds` SIMDs: the most that still
+// make at most one wave per SIMD of all the chains.  Such a launch takes one chain's serial time, and
+// a step takes 40.6 clocks with 16 lanes (8 instructions instead of 9 for the fused Euler map), 44.6 with
+// 4 (RK4: 190 instead of 262) and 56.6 with one; with a second wave on a SIMD even two waves of 16 lanes'
+// 81 clocks would be more than the 56.6 of one chain per lane.  Four lanes gain nothing for the fused Euler map (9
+// instructions either way), 16 nothing for RK4, whose stages need copies of what the broadcasts add to.
+// Measured, 16 / 4 / 1 lanes: 64 KiB in 13.2 / 14.5 / 18.3 ms; 3 MB in - / 14.6 / 18.5; 256 KiB of the
+// RK4 format in - / 60.7 / 92.0; 2048 sequential messages in 211 / 230 / 292.
 int lanes_per_chain(uint64_t chains, int m, uint32_t integ, int simds) {
-    if (m != 1 || integ == LZ_INTEGRATOR_EULER_FMA) return 1;
-    return chains * 4 <= (uint64_t)simds * WAVE ? 4 : 1;
+    const uint64_t lanes = (uint64_t)simds * WAVE;
+    if (m != 1) return 1;
+    if (integ != LZ_INTEGRATOR_RK4 && chains * 16 <= lanes) return 16;
+    if (integ != LZ_INTEGRATOR_EULER_FMA && chains * 4 <= lanes) return 4;
+    return 1;
 }
 
 bool shape_valid(const KernelShape &sh, const DevInfo &dev) {

@@ -204,9 +204,9 @@ struct lz_server {
     uint64_t hbm_fixed = 0;
     uint64_t tick_seq = 0, done_seq = 0;  // last tick queued, last tick completed (ticks complete in order)
     // late admission (server thread only): a tick's duration per wave per SIMD (a running mean of
-    // the measured ticks with one lane per chain, and of those with several), when the last completed tick was seen to end, and when the next step
+    // the measured ticks, apart for 1, 4 and 16 lanes per chain), when the last completed tick was seen to end, and when the next step
     // may start
-    double tick_ns_per_wave[2] = {0, 0}, late_margin_ns = LATE_MARGIN_START_NS;
+    double tick_ns_per_wave[3] = {0, 0, 0}, late_margin_ns = LATE_MARGIN_START_NS;
     uint64_t tick_end_ns = 0, next_step_ns = 0;
     // shared with submitters / pollers
     std::mutex mu;
@@ -302,7 +302,7 @@ int complete_tick(lz_server *s, TickSlot &t) {
     const bool timed = hipEventElapsedTime(&ms, t.ev_start, t.ev_end) == hipSuccess;
     if (timed && t.waves) {
         const double per = (double)ms * 1e6 / t.waves;
-        double &mean = s->tick_ns_per_wave[t.g > 1];
+        double &mean = s->tick_ns_per_wave[t.g == 1 ? 0 : (t.g == 4 ? 1 : 2)];
         mean = mean > 0 ? 0.75 * mean + 0.25 * per : per;
     }
     {
@@ -567,7 +567,7 @@ int server_step(lz_server *s) {
         // the tick queued above started when the previous one ended: the next step waits until
         // shortly before it is expected to end, so that the tick after it takes the requests
         // that arrive meanwhile (and not one tick later)
-        const double est = s->tick_ns_per_wave[t.g > 1] * t.waves;
+        const double est = s->tick_ns_per_wave[t.g == 1 ? 0 : (t.g == 4 ? 1 : 2)] * t.waves;
         if (t.in_flight && est > s->late_margin_ns)
             s->next_step_ns = s->tick_end_ns + (uint64_t)(est - s->late_margin_ns);
     }
