@@ -55,6 +55,27 @@ struct ChainSlot {
     uint32_t pad2;
 };
 
+// A chain's checkpoint between two segments of a segment plan (plain and batched paths).
+struct ChainState {
+    double r[3];
+    double al[3];
+    uint8_t mu[3], om[3];
+    uint8_t pad[2];
+};
+
+// The waves of a launch beyond a multiple of the SIMDs, advanced in rounds (plan_segments).
+constexpr uint32_t SEG_MAX = 32;  // segments of a block at most
+struct SegPlan {
+    uint64_t chain0;             // first chain of the plan
+    uint32_t waves;              // its waves (0: no plan)
+    uint32_t segs, seg_len;      // segments per block and their bytes
+    uint32_t rounds;
+    uint32_t off[SEG_MAX + 1];   // tasks before segment s
+    ChainState *state;           // a checkpoint per chain of the plan
+};
+// Checkpoints of any plan on this many SIMDs: fewer than two waves per SIMD.
+constexpr size_t seg_state_bytes(int simds) { return (size_t)simds * 2 * 64 * sizeof(ChainState); }
+
 // The two partial-block chains of a stream update, carried by a plain launch as the
 // lanes after its nb whole blocks: the head finishes the pending partial block from
 // its checkpoint (its digest joins the tag when it completes the block, else the
@@ -104,13 +125,15 @@ constexpr int CU_SIMDS = 4;     // SIMDs of a compute unit
 // which a launch with several lanes per chain is told whether the device has room for it.
 constexpr size_t TAG_WORDS = 3, TAG_WIDE = 3;
 int lanes_per_chain(uint64_t chains, int m, uint32_t integ, int simds);
+SegPlan plan_segments(uint64_t chains, const uint32_t *lens, const lz_params &prm, int simds);
 
 // ---- kernel launchers (kernels.hip) --------------------------------------------------
 hipError_t launch_fill_u64(unsigned long long *p, size_t n, hipStream_t s);
-// Clears the tag accumulator (TAG_WORDS and the word after them) and runs the message.
+// Clears the tag accumulator (TAG_WORDS and the word after them) and runs the message, its last waves
+// by the segment plan if there is one.
 hipError_t launch_plain(const KernelShape &sh, const lz_key &key, const lz_params &prm, int decrypt,
-                        const uint8_t *in, uint8_t *out, uint64_t n, unsigned long long *tag_acc,
-                        hipStream_t s, uint64_t block_base = 0);
+                        const uint8_t *in, uint8_t *out, uint64_t n, unsigned long long *tag_acc, const SegPlan &plan,
+                        hipStream_t s);
 // One stream update: its full whole blocks from in / out at global block index
 // block_base, plus x's head and tail chains, in one launch of one chain per lane.
 hipError_t launch_stream_step(const KernelShape &shape, const lz_key &key, const lz_params &prm, int decrypt,
@@ -135,7 +158,7 @@ struct BatchDev {
 };
 // Clears the tags and the counter and runs the batch.
 hipError_t launch_batch(const KernelShape &sh, const DevInfo &dev, const lz_params &prm, const BatchDev &b,
-                        hipStream_t s);
+                        const SegPlan &plan, hipStream_t s);
 hipError_t launch_batch_finalize(const BatchDev &b, int decrypt, hipStream_t s);
 // One-thread kernel: *slot = status (ordered on s before a batch replay that reads the slot).
 hipError_t launch_set_status_ref(int32_t **slot, int32_t *status, hipStream_t s);
@@ -204,7 +227,8 @@ struct lz_ctx {
     lz::DevInfo dev;
     char arch[64];               // gcnArchName of the device
     double tuned_ms;             // last autotune: time of the winning shape's launch
-    unsigned long long *ws_tag;  // 3 words, plain path tag accumulator
+    unsigned long long *ws_tag;  // plain path tag accumulator (TAG_WORDS + 1)
+    lz::ChainState *ws_seg;      // plain path segment checkpoints (seg_state_bytes, on first use)
     int32_t *ws_status;          // plain path status (synchronous decrypt)
     int32_t *host_status;        // pinned
     hipStream_t last_stream;

@@ -699,6 +699,83 @@ __global__ __launch_bounds__(256) void plain_kernel(PlainArgs a) {
     count_waves(-waves);
 }
 
+// One round of a segment plan (see plan_segments): each wave advances 64 chains by one segment of
+// seg_len bytes from the checkpoint that an earlier round left.  The round's waves are tasks
+// first, first + 1, ... of the plan; task off[s] + w is segment s of wave w.
+__device__ __forceinline__ bool seg_task(const SegPlan &p, uint64_t first, uint32_t &seg, uint32_t &wave) {
+    const uint64_t t = first + (uint64_t)blockIdx.x * (blockDim.x / WAVE) + threadIdx.x / WAVE;
+    if (t >= p.off[p.segs]) return false;
+    seg = 0;
+    while (t >= p.off[seg + 1]) ++seg;
+    wave = (uint32_t)(t - p.off[seg]);
+    return true;
+}
+
+// Runs cnt bytes of the lane's chain from byte pos of its block of len bytes: from its start (pos = 0, c
+// initialised by the caller) or from `st`, to its end (then d holds the digest and the result is
+// true) or back to `st`.  A lane with cnt = 0 has nothing left to do.
+template <int I>
+__device__ __forceinline__ bool seg_run(Chains<1> &c, const WaveLds &w, uint32_t tile, const uint8_t *in, uint8_t *out,
+                                        uint32_t pos, uint32_t cnt, uint32_t len, ChainState &st, double dt,
+                                        uint32_t n_it, int lane, unsigned long long (&d)[3]) {
+    if (pos > 0 && cnt > 0) {
+        c.x[0] = st.r[0]; c.y[0] = st.r[1]; c.z[0] = st.r[2];
+        c.a0[0] = st.al[0]; c.a1[0] = st.al[1]; c.a2[0] = st.al[2];
+        c.mu0[0] = st.mu[0]; c.mu1[0] = st.mu[1]; c.mu2[0] = st.mu[2];
+        c.om0[0] = st.om[0]; c.om1[0] = st.om[1]; c.om2[0] = st.om[2];
+    }
+    const uint8_t *ins[1] = {in};
+    uint8_t *outs[1] = {out};
+    const uint32_t cnts[1] = {cnt};
+    wave_run<1, I, 1>(c, w, (int)tile, ins, outs, cnts, dt, n_it, lane, [&](int) __attribute__((always_inline)) {
+        if (cnt == 0) return;
+        if (pos + cnt == len) {
+            d[0] = digest_word(c.x[0]);
+            d[1] = digest_word(c.y[0]);
+            d[2] = digest_word(c.z[0]);
+        } else {
+            st.r[0] = c.x[0]; st.r[1] = c.y[0]; st.r[2] = c.z[0];
+            st.al[0] = c.a0[0]; st.al[1] = c.a1[0]; st.al[2] = c.a2[0];
+            st.mu[0] = (uint8_t)c.mu0[0]; st.mu[1] = (uint8_t)c.mu1[0]; st.mu[2] = (uint8_t)c.mu2[0];
+            st.om[0] = (uint8_t)c.om0[0]; st.om[1] = (uint8_t)c.om1[0]; st.om[2] = (uint8_t)c.om2[0];
+        }
+    });
+    return cnt > 0 && pos + cnt == len;
+}
+
+template <int I>
+__global__ __launch_bounds__(256) void plain_seg_kernel(PlainArgs a, SegPlan p, uint64_t first) {
+    extern __shared__ char lds[];
+    const int lane = threadIdx.x % WAVE;
+    count_waves(blockDim.x / WAVE);
+    uint32_t seg, wave;
+    if (seg_task(p, first, seg, wave)) {
+        const WaveLds w = wave_lds<WAVE>(lds + (size_t)(threadIdx.x / WAVE) * wave_lds_bytes(WAVE, a.tile), a.tile);
+        const uint64_t i = (uint64_t)wave * WAVE + lane, g = p.chain0 + i, off = g * a.block_len;
+        const uint32_t len = g < a.nb ? (uint32_t)(a.n - off < a.block_len ? a.n - off : a.block_len) : 0u;
+        const uint32_t pos = seg * p.seg_len;
+        const uint32_t cnt = pos < len ? (len - pos < p.seg_len ? len - pos : p.seg_len) : 0u;
+        const uint64_t at = cnt ? off + pos : 0;
+        Chains<1> c;
+        const double r0[3] = {a.r0[0], a.r0[1], a.r0[2]}, ap[3] = {a.ap[0], a.ap[1], a.ap[2]};
+        const uint8_t mu[3] = {a.mu[0], a.mu[1], a.mu[2]}, om[3] = {a.om[0], a.om[1], a.om[2]},
+                      k[3] = {a.k[0], a.k[1], a.k[2]};
+        init_chain<1>(c, 0, r0, ap, mu, om, k, a.block_base + (g < a.nb ? g : 0), a.decrypt);
+        unsigned long long d[3] = {0, 0, 0};
+        const bool done = seg_run<I>(c, w, a.tile, a.in + at, a.out + at, pos, cnt, len, p.state[i], a.dt, a.n_it, lane, d);
+        if (__any(done)) {
+            const unsigned long long t0 = wave_xor_u64(done ? d[0] : 0ull), t1 = wave_xor_u64(done ? d[1] : 0ull),
+                                     t2 = wave_xor_u64(done ? d[2] : 0ull);
+            if (lane == 0) {
+                atomicXor(&a.tag_acc[0], t0);
+                atomicXor(&a.tag_acc[1], t1);
+                atomicXor(&a.tag_acc[2], t2);
+            }
+        }
+    }
+    count_waves(-(int)(blockDim.x / WAVE));
+}
+
 // Encrypt: tag bytes to out_tag.  Decrypt: compare with stored tag, status,
 // and zero the body on failure (grid-stride over the body).
 __global__ void plain_finalize_kernel(int decrypt, const unsigned long long *tag_acc, const uint8_t *stored,
@@ -730,6 +807,7 @@ struct BatchArgs {
     BatchDev b;
     double dt;
     uint32_t n_it, block_len, tile;
+    uint64_t n_chains;  // of the persistent launch (the rest belong to a segment plan)
 };
 
 __device__ __forceinline__ uint32_t find_msg(const uint64_t *prefix, uint32_t n_msg, uint64_t g) {
@@ -743,6 +821,19 @@ __device__ __forceinline__ uint32_t find_msg(const uint64_t *prefix, uint32_t n_
     return lo;
 }
 
+// Chain g of the batch: message i, block b of len bytes.
+__device__ __forceinline__ void batch_chain(const BatchArgs &a, uint64_t g, uint32_t &i, uint64_t &b, uint32_t &len) {
+    if (g < a.b.n_full) {
+        i = find_msg(a.b.full_prefix, a.b.n_msg, g);
+        b = g - a.b.full_prefix[i];
+        len = a.block_len;
+    } else {
+        i = a.b.tail_msg[g - a.b.n_full];
+        b = a.b.msgs[i].nb - 1;
+        len = (uint32_t)(a.b.msgs[i].n - b * a.block_len);
+    }
+}
+
 template <int M, int I, int G>
 __device__ __forceinline__ void batch_body(const BatchArgs &a, char *lds) {
     constexpr int ROWS = WAVE * M / G;
@@ -750,7 +841,7 @@ __device__ __forceinline__ void batch_body(const BatchArgs &a, char *lds) {
     const int wid = threadIdx.x / WAVE;
     const WaveLds w = wave_lds<ROWS>(lds + (size_t)wid * wave_lds_bytes(ROWS, a.tile), a.tile);
     const uint64_t per_task = ROWS;
-    const uint64_t n_chains = a.b.n_full + a.b.n_tail;
+    const uint64_t n_chains = a.n_chains;
     const uint64_t n_tasks = (n_chains + per_task - 1) / per_task;
 
     // No lane-conditional region may sit inside this loop: the compiler is free to merge such
@@ -777,17 +868,7 @@ __device__ __forceinline__ void batch_body(const BatchArgs &a, char *lds) {
             uint32_t i = 0;
             uint64_t b = 0;
             uint32_t len = 0;
-            if (valid[m]) {
-                if (g < a.b.n_full) {
-                    i = find_msg(a.b.full_prefix, a.b.n_msg, g);
-                    b = g - a.b.full_prefix[i];
-                    len = a.block_len;
-                } else {
-                    i = a.b.tail_msg[g - a.b.n_full];
-                    b = a.b.msgs[i].nb - 1;
-                    len = (uint32_t)(a.b.msgs[i].n - b * a.block_len);
-                }
-            }
+            if (valid[m]) batch_chain(a, g, i, b, len);
             const MsgDesc &md = a.b.msgs[i];
             msg[m] = i;
             cnt[m] = valid[m] ? len : 0u;
@@ -828,6 +909,42 @@ __global__ __launch_bounds__(256) void batch_kernel(BatchArgs a) {
         else batch_body<M, I, 1>(a, lds);
     }
     count_waves(-waves);
+}
+
+// One round of the batch's segment plan.
+template <int I>
+__global__ __launch_bounds__(256) void batch_seg_kernel(BatchArgs a, SegPlan p, uint64_t first) {
+    extern __shared__ char lds[];
+    const int lane = threadIdx.x % WAVE;
+    count_waves(blockDim.x / WAVE);
+    uint32_t seg, wave;
+    if (seg_task(p, first, seg, wave)) {
+        const WaveLds w = wave_lds<WAVE>(lds + (size_t)(threadIdx.x / WAVE) * wave_lds_bytes(WAVE, a.tile), a.tile);
+        const uint64_t j = (uint64_t)wave * WAVE + lane, g = p.chain0 + j;
+        uint32_t i = 0, len = 0;
+        uint64_t b = 0;
+        const bool valid = g < a.b.n_full + a.b.n_tail;
+        if (valid) batch_chain(a, g, i, b, len);
+        const MsgDesc &md = a.b.msgs[i];
+        const uint32_t pos = seg * p.seg_len;
+        const uint32_t cnt = pos < len ? (len - pos < p.seg_len ? len - pos : p.seg_len) : 0u;
+        const uint64_t at = cnt ? b * a.block_len + pos : 0;
+        Chains<1> c;
+        const double r0[3] = {md.r0[0], md.r0[1], md.r0[2]}, ap[3] = {md.ap[0], md.ap[1], md.ap[2]};
+        const uint8_t mu[3] = {md.mu[0], md.mu[1], md.mu[2]}, om[3] = {md.om[0], md.om[1], md.om[2]},
+                      k[3] = {md.k[0], md.k[1], md.k[2]};
+        init_chain<1>(c, 0, r0, ap, mu, om, k, b, md.decrypt);
+        unsigned long long d[3] = {digest_word(c.x[0]), digest_word(c.y[0]), digest_word(c.z[0])};  // an empty message's
+        bool done = seg_run<I>(c, w, a.tile, md.in + at, md.out + at, pos, cnt, len, p.state[j], a.dt, a.n_it, lane, d);
+        done = done || (valid && len == 0 && seg == 0);
+        if (done) {
+            unsigned long long *t = &a.b.tag_acc[3 * (size_t)i];
+            atomicXor(t + 0, d[0]);
+            atomicXor(t + 1, d[1]);
+            atomicXor(t + 2, d[2]);
+        }
+    }
+    count_waves(-(int)(blockDim.x / WAVE));
 }
 
 // One workgroup per message: tag out (encrypt) or tag check, status and zeroing (decrypt).
@@ -1085,6 +1202,54 @@ int lanes_per_chain(uint64_t chains, int m, uint32_t integ, int simds) {
     return 1;
 }
 
+// A launch of W waves on S SIMDs takes ceil(W / S) waves' time, since a wave's chains cannot be cut among
+// SIMDs: 24 MB are 1.43 waves per SIMD and took the time of two.  Chains can be cut in time, though.  The
+// last P = S + W mod S waves are advanced in rounds of S waves, one wave on every SIMD, each by one
+// segment of its chains' bytes, round-robin: wave w's segments are P >= S tasks apart, so no round holds
+// two of them and a round finds the checkpoints of the one before.  The P waves then take P / S waves' time
+// and a launch per round.  The other waves, a multiple of S, run at once before them.
+//
+// `lens` gives the longest chain of each of the P waves (descending; NULL: all block_len).  Waves past
+// a short chain's end have no tasks, so off[] counts the waves that have a segment s.  The segment
+// count is the one of 4, 8, 16, 32 with the least predicted time, clocks per step as measured (4 per
+// instruction) and SEG_ROUND_US for a launch, its checkpoints and the gap before it; without 2% of
+// gain (short steps, or W just below a multiple of S) no plan is made.  Measured: 24 MB in 27.7 ms,
+// 39.0 without a plan; 512 files of 79 MB in 91.9 and 95.4.  A round of one wave per SIMD takes 1.20 ms
+// per 16 bytes, the rate of 64 MiB in one launch: the part's clock under a full load.
+SegPlan plan_segments(uint64_t chains, const uint32_t *lens, const lz_params &prm, int simds) {
+    constexpr double SEG_ROUND_US = 10.0, CLOCKS_PER_US = 2400.0;
+    SegPlan best{};
+    const uint64_t W = (chains + WAVE - 1) / WAVE, S = (uint64_t)simds;
+    if (S == 0 || W <= S || W % S == 0) return best;
+    const uint32_t P = (uint32_t)(S + W % S);
+    const double insts = prm.integrator == LZ_INTEGRATOR_RK4 ? 65 : (prm.integrator == LZ_INTEGRATOR_EULER_FMA ? 9 : 14);
+    const double byte_us = insts * 4.0 * prm.n_it / CLOCKS_PER_US;
+    const uint32_t B = prm.block_len;
+    // without a plan: S waves of full length, then the longest of the others beside them
+    double best_us = 0.98 * byte_us * ((double)B + (lens ? lens[S] : B));
+    for (uint32_t n = 4; n <= SEG_MAX; n *= 2) {
+        SegPlan p{};
+        p.seg_len = (B + n - 1) / n;
+        p.segs = (B + p.seg_len - 1) / p.seg_len;
+        bool apart = true;
+        for (uint32_t s = 0; s < p.segs; ++s) {
+            uint32_t k = P;
+            while (lens && k > 0 && s > 0 && lens[k - 1] <= s * p.seg_len) --k;
+            apart = apart && k >= S;
+            p.off[s + 1] = p.off[s] + k;
+        }
+        if (!apart) continue;
+        p.rounds = (uint32_t)((p.off[p.segs] + S - 1) / S);
+        const double us = p.rounds * (p.seg_len * byte_us + SEG_ROUND_US);
+        if (us >= best_us) continue;
+        best_us = us;
+        p.waves = P;
+        p.chain0 = (W - P) * WAVE;
+        best = p;
+    }
+    return best;
+}
+
 bool shape_valid(const KernelShape &sh, const DevInfo &dev) {
     if (sh.m != 1 && sh.m != 2 && sh.m != 4) return false;
     if (sh.wg != 64 && sh.wg != 128 && sh.wg != 256) return false;
@@ -1142,22 +1307,57 @@ hipError_t launch_claim(const KernelShape &sh, uint64_t grid, unsigned long long
     return hipGetLastError();
 }
 
+// The rounds of a segment plan: launch(grid, lds, first) starts one.
+template <typename F>
+hipError_t seg_rounds(const KernelShape &sh, const SegPlan &p, F launch) {
+    const uint64_t per_wg = (uint64_t)sh.wg / WAVE;
+    const unsigned grid = (unsigned)((sh.simds + per_wg - 1) / per_wg);
+    // a round's waves are one per SIMD: whole workgroups of it, so that round r starts at task r * waves
+    for (uint64_t first = 0; first < p.off[p.segs]; first += grid * per_wg) {
+        const hipError_t e = launch(grid, first);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
+// The tile that holds a segment, as far as there is one.
+int seg_tile(uint32_t seg_len, int most) {
+    int tile = 16;
+    while (tile < (int)seg_len && tile < most) tile *= 2;
+    return tile;
+}
+
 hipError_t launch_plain(const KernelShape &sh, const lz_key &key, const lz_params &prm, int decrypt,
-                        const uint8_t *in, uint8_t *out, uint64_t n, unsigned long long *tag_acc, hipStream_t s,
-                        uint64_t block_base) {
+                        const uint8_t *in, uint8_t *out, uint64_t n, unsigned long long *tag_acc, const SegPlan &plan,
+                        hipStream_t s) {
     const uint64_t nb = n == 0 ? 1 : (n + prm.block_len - 1) / prm.block_len;
-    const PlainArgs a = plain_args(sh, key, prm, decrypt, in, out, n, nb, tag_acc, block_base);
-    const uint64_t grid = grid_of(sh, nb);
-    const hipError_t e = sh.g > 1 ? launch_claim(sh, grid, tag_acc, TAG_WORDS, tag_acc + TAG_WIDE, s)
-                                  : launch_fill_u64(tag_acc, TAG_WORDS, s);
+    PlainArgs a = plain_args(sh, key, prm, decrypt, in, out, n, nb, tag_acc, 0);
+    if (plan.waves) a.nb = plan.chain0;
+    const uint64_t grid = grid_of(sh, a.nb);
+    hipError_t e = sh.g > 1 ? launch_claim(sh, grid, tag_acc, TAG_WORDS, tag_acc + TAG_WIDE, s)
+                            : launch_fill_u64(tag_acc, TAG_WORDS, s);
     if (e != hipSuccess) return e;
-    const size_t lds = lds_bytes(sh);
-    return dispatch(sh.m, sh.g, prm.integrator, [&](auto mc, auto ic, auto gc) {
-        constexpr int M = decltype(mc)::value;
-        constexpr int I = decltype(ic)::value;
-        constexpr int G = decltype(gc)::value;
-        hipLaunchKernelGGL((plain_kernel<M, I, false, G>), dim3((unsigned)grid), dim3(sh.wg), lds, s, a);
-        return hipGetLastError();
+    if (grid) {
+        e = dispatch(sh.m, sh.g, prm.integrator, [&](auto mc, auto ic, auto gc) {
+            constexpr int M = decltype(mc)::value;
+            constexpr int I = decltype(ic)::value;
+            constexpr int G = decltype(gc)::value;
+            hipLaunchKernelGGL((plain_kernel<M, I, false, G>), dim3((unsigned)grid), dim3(sh.wg), lds_bytes(sh), s, a);
+            return hipGetLastError();
+        });
+        if (e != hipSuccess) return e;
+    }
+    if (!plan.waves) return hipSuccess;
+    KernelShape ss = sh;
+    ss.tile = seg_tile(plan.seg_len, sh.tile);
+    a.nb = nb;
+    a.tile = (uint32_t)ss.tile;
+    return seg_rounds(ss, plan, [&](unsigned g, uint64_t first) {
+        return dispatch_i<1>(prm.integrator, [&](auto, auto ic, auto) {
+            constexpr int I = decltype(ic)::value;
+            hipLaunchKernelGGL((plain_seg_kernel<I>), dim3(g), dim3(ss.wg), lds_bytes(ss), s, a, plan, first);
+            return hipGetLastError();
+        });
     });
 }
 
@@ -1198,30 +1398,44 @@ hipError_t launch_plain_finalize(int decrypt, const unsigned long long *tag_acc,
 }
 
 hipError_t launch_batch(const KernelShape &sh, const DevInfo &dev, const lz_params &prm, const BatchDev &b,
-                        hipStream_t s) {
+                        const SegPlan &plan, hipStream_t s) {
     BatchArgs a;
     a.b = b;
     a.dt = prm.dt;
     a.n_it = prm.n_it;
     a.block_len = prm.block_len;
     a.tile = (uint32_t)sh.tile;
+    a.n_chains = plan.waves ? plan.chain0 : b.n_full + b.n_tail;
     // persistent grid: wps waves on each of the 4 SIMDs of every CU, but no more than the tasks
-    const uint64_t waves = (uint64_t)dev.cus * 4 * sh.wps;
+    const uint64_t waves = (uint64_t)dev.cus * CU_SIMDS * sh.wps;
     const uint64_t wpw = (uint64_t)sh.wg / WAVE;
     uint64_t grid = (waves + wpw - 1) / wpw;
-    const uint64_t need = grid_of(sh, b.n_full + b.n_tail);
-    if (need < grid) grid = need ? need : 1;
+    const uint64_t need = grid_of(sh, a.n_chains);
+    if (need < grid) grid = need;
     const size_t words = 3 * (size_t)b.n_msg + 1;  // tags and the work-queue counter
-    const hipError_t e = sh.g > 1 ? launch_claim(sh, grid, b.tag_acc, words, b.wide, s)
-                                  : launch_fill_u64(b.tag_acc, words, s);
+    hipError_t e = sh.g > 1 ? launch_claim(sh, grid, b.tag_acc, words, b.wide, s)
+                            : launch_fill_u64(b.tag_acc, words, s);
     if (e != hipSuccess) return e;
-    const size_t lds = lds_bytes(sh);
-    return dispatch(sh.m, sh.g, prm.integrator, [&](auto mc, auto ic, auto gc) {
-        constexpr int M = decltype(mc)::value;
-        constexpr int I = decltype(ic)::value;
-        constexpr int G = decltype(gc)::value;
-        hipLaunchKernelGGL((batch_kernel<M, I, G>), dim3((unsigned)grid), dim3(sh.wg), lds, s, a);
-        return hipGetLastError();
+    if (grid) {
+        e = dispatch(sh.m, sh.g, prm.integrator, [&](auto mc, auto ic, auto gc) {
+            constexpr int M = decltype(mc)::value;
+            constexpr int I = decltype(ic)::value;
+            constexpr int G = decltype(gc)::value;
+            hipLaunchKernelGGL((batch_kernel<M, I, G>), dim3((unsigned)grid), dim3(sh.wg), lds_bytes(sh), s, a);
+            return hipGetLastError();
+        });
+        if (e != hipSuccess) return e;
+    }
+    if (!plan.waves) return hipSuccess;
+    KernelShape ss = sh;
+    ss.tile = seg_tile(plan.seg_len, sh.tile);
+    a.tile = (uint32_t)ss.tile;
+    return seg_rounds(ss, plan, [&](unsigned g, uint64_t first) {
+        return dispatch_i<1>(prm.integrator, [&](auto, auto ic, auto) {
+            constexpr int I = decltype(ic)::value;
+            hipLaunchKernelGGL((batch_seg_kernel<I>), dim3(g), dim3(ss.wg), lds_bytes(ss), s, a, plan, first);
+            return hipGetLastError();
+        });
     });
 }
 

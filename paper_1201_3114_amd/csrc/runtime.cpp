@@ -91,6 +91,24 @@ KernelShape plain_shape(const lz_ctx *c, uint64_t nb) {
     return sh;
 }
 
+// Segment plan of a message of nb blocks, with the context's checkpoints: allocated for the first message
+// that has a plan, also when it is being captured (no node comes of it, and the capture mode is set
+// aside for the allocation).  Without them the message runs without a plan.
+SegPlan plain_plan(lz_ctx *c, const KernelShape &sh, uint64_t nb) {
+    if (sh.m != 1 || sh.g != 1) return SegPlan{};
+    SegPlan plan = plan_segments(nb, nullptr, c->prm, sh.simds);
+    if (plan.waves && !c->ws_seg) {
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+        (void)hipThreadExchangeStreamCaptureMode(&mode);
+        void *p = nullptr;
+        if (hipMalloc(&p, seg_state_bytes(sh.simds)) == hipSuccess) c->ws_seg = static_cast<ChainState *>(p);
+        else (void)hipGetLastError();
+        (void)hipThreadExchangeStreamCaptureMode(&mode);
+    }
+    plan.state = c->ws_seg;
+    return plan.state ? plan : SegPlan{};
+}
+
 // Orders a call on stream s after the previous call that used the same
 // workspace (possibly on another stream).
 int order_after(hipStream_t s, hipStream_t &last_stream, hipEvent_t ev, bool &has_last) {
@@ -208,6 +226,7 @@ extern "C" int lz_context_destroy(lz_ctx *c) {
     if (c->diag_merge) hipFree(c->diag_merge);
     if (c->diag_event) hipEventDestroy(c->diag_event);
     if (c->ws_tag) hipFree(c->ws_tag);
+    if (c->ws_seg) hipFree(c->ws_seg);
     if (c->ws_status) hipFree(c->ws_status);
     if (c->host_status) hipHostFree(c->host_status);
     if (c->last_event) hipEventDestroy(c->last_event);
@@ -245,7 +264,8 @@ extern "C" int lz_encrypt_key(lz_ctx *c, const lz_key *key, const uint8_t *d_P, 
     hipStream_t s = (hipStream_t)stream;
     LZ_HIP(hipSetDevice(c->device));
     if (int rc = order_after(s, c->last_stream, c->last_event, c->has_last)) return rc;
-    LZ_HIP(launch_plain(plain_shape(c, nb), *key, c->prm, 0, d_P, d_C, n, c->ws_tag, s));
+    const KernelShape sh = plain_shape(c, nb);
+    LZ_HIP(launch_plain(sh, *key, c->prm, 0, d_P, d_C, n, c->ws_tag, plain_plan(c, sh, nb), s));
     LZ_HIP(launch_plain_finalize(0, c->ws_tag, nullptr, d_C + n, nullptr, nullptr, n, s));
     return record(s, c->last_stream, c->last_event, c->has_last);
 }
@@ -262,7 +282,8 @@ extern "C" int lz_decrypt_key(lz_ctx *c, const lz_key *key, const uint8_t *d_C, 
     LZ_HIP(hipSetDevice(c->device));
     if (int rc = order_after(s, c->last_stream, c->last_event, c->has_last)) return rc;
     int32_t *st = d_status ? d_status : c->ws_status;
-    LZ_HIP(launch_plain(plain_shape(c, nb), *key, c->prm, 1, d_C, d_P, n, c->ws_tag, s));
+    const KernelShape sh = plain_shape(c, nb);
+    LZ_HIP(launch_plain(sh, *key, c->prm, 1, d_C, d_P, n, c->ws_tag, plain_plan(c, sh, nb), s));
     LZ_HIP(launch_plain_finalize(1, c->ws_tag, d_C + n, nullptr, st, d_P, n, s));
     if (d_status) return record(s, c->last_stream, c->last_event, c->has_last);
     LZ_HIP(hipMemcpyAsync(c->host_status, c->ws_status, sizeof(int32_t), hipMemcpyDeviceToHost, s));
@@ -370,6 +391,20 @@ int batch_create(lz_ctx *c, const lz_params &prm, int decrypt, size_t n_msg, con
     std::stable_sort(tails.begin(), tails.end(),
                      [&](uint32_t a, uint32_t b) { return lens[a] % B > lens[b] % B; });
 
+    // the batch's last waves may run by a segment plan: tails are the shortest chains, and come last
+    sh.simds = c->dev.cus * CU_SIMDS;
+    const uint64_t n_chains = prefix[n_msg] + tails.size();
+    sh.g = lanes_per_chain(n_chains, sh.m, prm.integrator, sh.simds);
+    SegPlan plan{};
+    const uint64_t waves = (n_chains + WAVE_LANES - 1) / WAVE_LANES, simds = (uint64_t)sh.simds;
+    if (sh.m == 1 && sh.g == 1 && waves > simds) {
+        std::vector<uint32_t> longest(simds + waves % simds);
+        for (size_t w = 0; w < longest.size(); ++w) {
+            const uint64_t g = (waves - longest.size() + w) * WAVE_LANES;
+            longest[w] = g < prefix[n_msg] ? B : (uint32_t)(lens[tails[g - prefix[n_msg]]] % B);
+        }
+        plan = plan_segments(n_chains, longest.data(), prm, sh.simds);
+    }
     lz_batch *b = new (std::nothrow) lz_batch();
     if (!b) return fail(LZ_E_NOMEM, "host allocation failed");
     b->ctx = c;
@@ -380,7 +415,8 @@ int batch_create(lz_ctx *c, const lz_params &prm, int decrypt, size_t n_msg, con
     const size_t o_tail = align_up(o_prefix + (n_msg + 1) * sizeof(uint64_t), 256);
     const size_t o_slot = align_up(o_tail + std::max<size_t>(tails.size(), 1) * sizeof(uint32_t), 256);
     const size_t o_tag = o_slot + 256;
-    const size_t total = o_tag + (3 * n_msg + 2) * sizeof(unsigned long long);  // tags, counter, wide
+    const size_t o_seg = align_up(o_tag + (3 * n_msg + 2) * sizeof(unsigned long long), 256);  // tags, counter, wide
+    const size_t total = o_seg + (size_t)plan.waves * WAVE_LANES * sizeof(ChainState);
     hipError_t e = hipMalloc(&b->dmem, total);
     if (e != hipSuccess) {
         batch_free(b);
@@ -406,8 +442,7 @@ int batch_create(lz_ctx *c, const lz_params &prm, int decrypt, size_t n_msg, con
     d.n_msg = (uint32_t)n_msg;
     d.n_tail = (uint32_t)tails.size();
     d.n_full = prefix[n_msg];
-    sh.simds = c->dev.cus * CU_SIMDS;
-    sh.g = lanes_per_chain(d.n_full + d.n_tail, sh.m, prm.integrator, sh.simds);
+    plan.state = reinterpret_cast<ChainState *>(base + o_seg);
     d.tag_acc = reinterpret_cast<unsigned long long *>(base + o_tag);
     d.counter = d.tag_acc + 3 * n_msg;
     d.wide = d.counter + 1;
@@ -422,7 +457,7 @@ int batch_create(lz_ctx *c, const lz_params &prm, int decrypt, size_t n_msg, con
     }
     e = hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal);
     if (e == hipSuccess) {
-        hipError_t e1 = launch_batch(sh, c->dev, prm, d, cap);
+        hipError_t e1 = launch_batch(sh, c->dev, prm, d, plan, cap);
         hipError_t e2 = e1 == hipSuccess ? launch_batch_finalize(d, b->decrypt, cap) : e1;
         e = hipStreamEndCapture(cap, &b->graph);
         if (e2 != hipSuccess) e = e2;
