@@ -104,3 +104,25 @@ def test_no_room_for_wide_launches(lz, integ):
     for k, o in enumerate(outs):
         assert np.array_equal(host(o), want), (integ, k)
     assert torch.equal(big_ctx.decrypt(C0, b"big"), big)
+
+
+@pytest.mark.parametrize("n", [1, 15, 16, 17, 16383, 16384 + 5, 131072 + 31, (1 << 20) + 3])
+def test_copies_of_unaligned_chunks(lz, n):
+    """Deferred chunks: staged and copied out in pieces whose source and destination agree modulo 16 or not, of
+    lengths around a move, a workgroup's turn and a piece; bytes beside them stay."""
+    import torch
+
+    rng = np.random.default_rng(n)
+    ctx = lz.Context(0, lz.params(n_it=1, block_len=64))
+    src = torch.from_numpy(rng.integers(0, 256, 3 * n + 64, dtype=np.uint8)).cuda()
+    dst = torch.full((3 * n + 96,), 7, dtype=torch.uint8, device="cuda")
+    at = [(5, 3), (5 + n, 3 + n + 8), (5 + 2 * n, 3 + 2 * n + 25)]  # (source, destination), gaps between the outputs
+    st = lz.Stream(ctx, False, b"copies")
+    for s, d in at:
+        st.update_deferred(src[s:s + n], out=dst[d:d + n])
+    tag = host(st.finish())
+    want = oracle.encrypt(b"copies", host(src)[5:5 + 3 * n], nthreads=ORACLE_THREADS, n_it=1, block_len=64)
+    got, keep = host(dst), np.full(3 * n + 96, 7, dtype=np.uint8)
+    for i, (s, d) in enumerate(at):
+        keep[d:d + n] = want[i * n:(i + 1) * n]
+    assert np.array_equal(got, keep) and np.array_equal(tag, want[3 * n:])
