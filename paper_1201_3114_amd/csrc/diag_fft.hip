@@ -1,7 +1,7 @@
 // The 2-D analyses of Section 4 for a byte matrix (a text or an image laid out row by row) as
 // GPU kernels: the Fourier power spectrum and the circular autocorrelation matrix, in binary64.
-// The 2-D transforms run as FFTs for sides with no prime factor above 5 and as binary64 matrix
-// products on the matrix cores otherwise.
+// The 2-D transforms run as FFTs for sides with no prime factor above 5, as FFT convolutions (Bluestein)
+// for other sides from 80 to 2048, and as binary64 matrix products on the matrix cores otherwise.
 #include "diag_common.h"
 
 #include <type_traits>
@@ -21,13 +21,11 @@ namespace {
 constexpr int DFT_T = 64;  // output tile edge (r and c)
 constexpr int DFT_KS32 = 32, DFT_KS64 = 16;  // terms per LDS stage for 32- and 64-row tiles
 
-// tw[j] = (cos 2 pi j / N, sin 2 pi j / N)
-__global__ void twiddle_kernel(double2 *tw, uint32_t N) {
-    const uint32_t j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= N) return;
+// (cos 2 pi j / N, sin 2 pi j / N)
+__device__ __forceinline__ double2 twiddle_of(uint32_t j, uint32_t N) {
     double s, c;
     sincospi(2.0 * (double)j / (double)N, &s, &c);
-    tw[j] = make_double2(c, s);
+    return make_double2(c, s);
 }
 
 __device__ __forceinline__ double2 dft_value(uint8_t v) { return make_double2((double)v, 0.0); }
@@ -59,6 +57,7 @@ typedef double v4d __attribute__((ext_vector_type(4)));
 // for at most 2^24 bytes); in the last pass one thread per workgroup adds up the copies (den,
 // NaN when n S2 = S1^2, that is when every byte is equal).
 constexpr uint32_t MOM_COPIES = 32, MOM_STRIDE = 16;  // 16 words: 128 bytes
+constexpr uint32_t MOM_WORDS = MOM_COPIES * MOM_STRIDE;
 enum : int { EPI_COMPLEX = 0, EPI_POWER = 1, EPI_POWER_NODC = 2, EPI_ACF = 3 };
 struct PassOut {
     double2 *z;
@@ -68,6 +67,7 @@ struct PassOut {
     unsigned long long *mom;  // first pass over bytes: add the moment sums here (or nullptr)
     uint64_t n;               // EPI_ACF: the matrix's n = h w, with mom holding its moment sums
     double den;               // EPI_ACF: set by the kernel from mom and n
+    double dc;                // EPI_POWER: added to the zero frequency (a first pass over x - 128 left it out)
 };
 
 // The workgroup's moment sums (per-thread s1, s2) into copy slot mod MOM_COPIES of o.mom; every
@@ -126,6 +126,7 @@ __device__ __forceinline__ void pass_store(const PassOut &o, uint32_t c, uint32_
             const double d = o.den;
             v = d != d ? d : re / d;
         } else {
+            if (E == EPI_POWER && c == 0 && r == 0) re += o.dc;
             v = (E == EPI_POWER_NODC && c == 0 && r == 0) ? 0.0 : re * re + im * im;
         }
         o.p[i] = v;
@@ -679,6 +680,339 @@ __global__ __launch_bounds__(DIAG_WG) void fft_mixed_pass_kernel(const In *src, 
     }
 }
 
+// ---- other lengths: Bluestein's chirp convolution ---------------------------------------
+//
+// With n k = (n^2 + k^2 - (k - n)^2) / 2, the transform X[k] = sum_n x[n] e^{-2 pi i n k / N} is
+//   X[k] = c[k] sum_n (x[n] c[n]) b[k - n],   c[n] = e^{-pi i n^2 / N},  b[m] = conj c[m],
+// a circular convolution of length M >= 2 N - 1, a power of two, done by two M-point FFTs in one kernel
+// (L. Bluestein, 1970).  n^2 mod 2N is exact in integers, so every chirp value is one correctly placed
+// sincospi.  The direct pass takes 8 N operations per value, this one about 20 log2 M + 30.
+//
+// What bounds it is latency: at a side of 1009 the columns are two waves a SIMD, so the FFTs keep their
+// values in registers, 16 per thread, and meet in LDS twice each.  M = 16 x 16 x R: with T = M / 16
+// threads a column, n = t + T j, t = a + R b and k = k1 + 16 c + 256 d (j, b, c, k1 < 16; a, d < R),
+//   forward:  16-point DFTs over j, W_M^{t k1}; over b, W_T^{a c}; R-point DFTs over a;
+//   inverse:  the same stages mirrored, so neither needs a reordering pass.
+// The forward result lies as X[p + 256 d] at thread p mod T: natural order, in which the transformed
+// chirp (the second table, 1/M included) is multiplied in.  The LDS row strides S1 and S2 put the 8 lanes
+// of a 128-byte LDS cycle on distinct banks in every exchange.  Two real columns make one complex column
+// (z = x1 + i x2; X1 and X2 are the even and odd parts of Z).  Bytes enter as x - 128, exactly, which
+// leaves the zero frequency out of the convolution's rounding errors; the second pass adds 128 h w there.
+// Against the transform in extended precision the error is below the direct pass's from 80 up: 1.15e-15 of the
+// correlation matrix at 1009 x 1009 (direct 3.3e-15), 7.2e-16 at 131 x 137 (1.6e-15), 1.1e-15 at 2039 x
+// 2011 (4.5e-15).  Measured, spectrum and correlation matrix: 1009 x 1009 in 41 and 80 us (direct 189
+// and 325), 131 x 137 in 28 and 55 (40 and 72), 2039 x 2011 in 105 and 204 (975 and 1606); a pass at 1009
+// takes 14 to 18 us, the tables 8.  83 x 89 in 27 and 48 (30 and 53); at 61 x 67 the direct
+// passes take 26 and 46, as long as the convolution at 83.
+constexpr uint32_t BLU_MIN = 80, BLU_MAX = 2048;
+
+// Per length N: the chirp c[n] (N entries), the transformed chirp over M (M entries, natural order), then
+// the FFTs' twiddles for that M in the order the threads take them: ta[k1 T + t] = W_M^{t k1} and
+// tb[16 a + c] = W_T^{a c}.
+struct BluTab {
+    double2 *c, *b, *ta, *tb;
+};
+__host__ __device__ constexpr int blu_r(uint32_t N) { return N <= 256 ? 2 : (N <= 512 ? 4 : (N <= 1024 ? 8 : 16)); }
+__host__ __device__ constexpr size_t blu_entries(uint32_t N) { return N + (size_t)blu_r(N) * (2 * 256 + 16); }
+__host__ __device__ inline BluTab blu_tab(double2 *p, uint32_t N) {
+    const size_t m = 256 * (size_t)blu_r(N);
+    return BluTab{p, p + N, p + N + m, p + N + 2 * m};
+}
+
+__device__ __forceinline__ double2 conj2(double2 a) { return make_double2(a.x, -a.y); }
+
+template <int R>
+struct BluFft {
+    static constexpr int M = 256 * R, T = 16 * R, COLS = DIAG_WG / T;
+    static constexpr int S1 = T + (R == 2 ? 2 : (R == 4 ? 4 : 0)), S2 = R == 2 ? 260 : (R == 4 ? 258 : 257);
+    static constexpr int COL = 16 * S1 > R * S2 ? 16 * S1 : R * S2;  // LDS entries per column
+    static constexpr size_t lds() { return (size_t)COLS * COL * sizeof(double2); }
+
+    static __device__ __forceinline__ void dft_r(double2 *v, double sign) {
+        if constexpr (R == 2) {
+            const double2 a = v[0];
+            v[0] = cadd(a, v[1]);
+            v[1] = csub(a, v[1]);
+        } else if constexpr (R == 4) {
+            dft4(v[0], v[1], v[2], v[3], sign);
+        } else if constexpr (R == 8) {
+            constexpr double R2 = 0.70710678118654752;  // cos(pi / 4)
+            double2 e0 = v[0], e1 = v[2], e2 = v[4], e3 = v[6], o0 = v[1], o1 = v[3], o2 = v[5], o3 = v[7];
+            dft4(e0, e1, e2, e3, sign);
+            dft4(o0, o1, o2, o3, sign);
+            o1 = cmul(o1, make_double2(R2, sign * R2));
+            o2 = rot_q(o2, 1, sign);
+            o3 = cmul(o3, make_double2(-R2, sign * R2));
+            v[0] = cadd(e0, o0); v[4] = csub(e0, o0);
+            v[1] = cadd(e1, o1); v[5] = csub(e1, o1);
+            v[2] = cadd(e2, o2); v[6] = csub(e2, o2);
+            v[3] = cadd(e3, o3); v[7] = csub(e3, o3);
+        } else {
+            double2 u[16];
+#pragma unroll
+            for (int k = 0; k < 16; ++k) u[k] = v[k];
+            dft16(u, sign);
+#pragma unroll
+            for (int k = 0; k < 16; ++k) v[k] = u[k];
+        }
+    }
+
+    // v[j] = x[t + T j] -> v[i R + d] = X[i T + t + 256 d].  Each stage's twiddles are loaded before its
+    // DFTs; TW gives them (BluTable from memory, or computed).
+    template <typename TW>
+    static __device__ __forceinline__ void forward(double2 (&v)[16], uint32_t t, double2 *L, const TW &tw) {
+        double2 w[16];
+#pragma unroll
+        for (int k1 = 1; k1 < 16; ++k1) w[k1] = tw.a(k1, t);
+        dft16(v, -1.0);
+#pragma unroll
+        for (int k1 = 0; k1 < 16; ++k1) L[k1 * S1 + t] = k1 ? cmul(v[k1], w[k1]) : v[0];
+        const uint32_t k1 = t / R, a = t % R;
+#pragma unroll
+        for (int c = 1; c < 16; ++c) w[c] = tw.b(a, c);
+        __syncthreads();
+#pragma unroll
+        for (int b = 0; b < 16; ++b) v[b] = L[k1 * S1 + a + R * b];
+        __syncthreads();
+        dft16(v, -1.0);
+#pragma unroll
+        for (int c = 0; c < 16; ++c) L[a * S2 + 16 * c + k1] = c ? cmul(v[c], w[c]) : v[0];
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < 16 / R; ++i) {
+#pragma unroll
+            for (int a2 = 0; a2 < R; ++a2) v[i * R + a2] = L[a2 * S2 + i * T + t];
+            dft_r(&v[i * R], -1.0);
+        }
+    }
+
+    // the way back (without the factor 1/M); starts with a barrier, so that L may still be read before it
+    template <typename TW>
+    static __device__ __forceinline__ void inverse(double2 (&v)[16], uint32_t t, double2 *L, const TW &tw) {
+        const uint32_t k1 = t / R, a = t % R;
+        double2 w[16];
+#pragma unroll
+        for (int c = 1; c < 16; ++c) w[c] = tw.b(a, c);
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < 16 / R; ++i) {
+            dft_r(&v[i * R], 1.0);
+#pragma unroll
+            for (int a2 = 0; a2 < R; ++a2) L[a2 * S2 + i * T + t] = v[i * R + a2];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int c = 0; c < 16; ++c) {
+            v[c] = L[a * S2 + 16 * c + k1];
+            if (c) v[c] = cmul(v[c], conj2(w[c]));
+        }
+#pragma unroll
+        for (int k = 1; k < 16; ++k) w[k] = tw.a(k, t);
+        __syncthreads();
+        dft16(v, 1.0);
+#pragma unroll
+        for (int b = 0; b < 16; ++b) L[k1 * S1 + a + R * b] = v[b];
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+            v[k] = L[k * S1 + t];
+            if (k) v[k] = cmul(v[k], conj2(w[k]));
+        }
+        dft16(v, 1.0);
+    }
+
+    // W_M^{k1 t} and W_T^{a c} (= W_M^{16 a c}), W_M = e^{-2 pi i / M}
+    static __device__ __forceinline__ double2 root(uint32_t j) {
+        double sn, cs;
+        sincospi(2.0 * (double)j / (double)M, &sn, &cs);
+        return make_double2(cs, -sn);
+    }
+    struct FromTable {
+        const double2 *ta, *tb;
+        __device__ __forceinline__ double2 a(int k1, uint32_t t) const { return ta[k1 * T + t]; }
+        __device__ __forceinline__ double2 b(uint32_t a, int c) const { return tb[16 * a + c]; }
+    };
+    struct Quarter {  // from e^{-2 pi i j / M}, j < M / 4, in LDS (the tables' own workgroup)
+        const double2 *q;
+        __device__ __forceinline__ double2 at(uint32_t j) const { return rot_q(q[j % (M / 4)], j / (M / 4), -1.0); }
+        __device__ __forceinline__ double2 a(int k1, uint32_t t) const { return at(k1 * t); }
+        __device__ __forceinline__ double2 b(uint32_t a, int c) const { return at(16 * a * c); }
+    };
+};
+
+// c[n] = e^{-pi i n^2 / N}
+__device__ __forceinline__ double2 chirp(uint32_t n, uint32_t N) {
+    const uint32_t e = n * n % (2 * N);  // n < N <= 2048
+    double sn, cs;
+    sincospi((double)e / (double)N, &sn, &cs);
+    return make_double2(cs, -sn);
+}
+
+// The tables of length N, by workgroups part = 0 .. parts - 1 (at least 2): the first the chirp and its
+// transform (its T first threads hold the column), the others the twiddles.
+template <int R>
+__device__ __forceinline__ void blu_tables(double2 *p, uint32_t N, uint32_t part, uint32_t parts, double2 *lds) {
+    using F = BluFft<R>;
+    const BluTab tab = blu_tab(p, N);
+    if (part > 0) {
+        for (uint32_t i = (part - 1) * DIAG_WG + threadIdx.x; i < F::M + 16 * R; i += (parts - 1) * DIAG_WG) {
+            if (i < F::M) tab.ta[i] = F::root((i / F::T) * (i % F::T));
+            else tab.tb[i - F::M] = F::root(16 * ((i - F::M) / 16) * (i % 16));
+        }
+        return;
+    }
+    double2 *q = lds + F::COL, *cl = q + F::M / 4;
+    for (uint32_t j = threadIdx.x; j < F::M / 4; j += DIAG_WG) q[j] = F::root(j);
+    for (uint32_t n = threadIdx.x; n < N; n += DIAG_WG) tab.c[n] = cl[n] = chirp(n, N);
+    __syncthreads();
+    const uint32_t t = threadIdx.x;
+    double2 v[16];
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+        const uint32_t n = t + F::T * j, m = n < N ? n : F::M - n;  // b is even
+        v[j] = t < F::T && m < N ? conj2(cl[m]) : make_double2(0.0, 0.0);
+    }
+    // the threads past the column have no place in L: they take part in the barriers alone
+    if (t < F::T) {
+        F::forward(v, t, lds, typename F::Quarter{q});
+#pragma unroll
+        for (int i = 0; i < 16 / R; ++i)
+#pragma unroll
+            for (int d = 0; d < R; ++d)
+                tab.b[i * F::T + t + 256 * d] =
+                    make_double2(v[i * R + d].x * (1.0 / F::M), v[i * R + d].y * (1.0 / F::M));
+    } else {
+        __syncthreads();
+        __syncthreads();
+        __syncthreads();
+    }
+}
+
+__host__ __device__ constexpr size_t blu_table_lds(uint32_t N) {
+    const size_t r = (size_t)blu_r(N), col = r == 2 ? 16 * 34 : (r == 4 ? 16 * 68 : (r == 8 ? 8 * 257 : 16 * 257));
+    return (col + 64 * r + N) * sizeof(double2);
+}
+static_assert(BluFft<2>::COL == 16 * 34 && BluFft<4>::COL == 16 * 68 && BluFft<8>::COL == 8 * 257 && BluFft<16>::COL == 16 * 257,
+              "columns of blu_table_lds");
+
+// blockIdx.y = 0: the tables of length Na, 1: those of Nb.  kind: 0 for the twiddles of the mixed-radix and direct
+// passes, 1 for the chirp convolution's tables.  mom (or NULL): the moment sums, cleared here for the passes.
+constexpr uint32_t TABLE_WGS = 9;
+__global__ __launch_bounds__(DIAG_WG) void tables_kernel(double2 *pa, uint32_t Na, int ka, double2 *pb, uint32_t Nb,
+                                                         int kb, unsigned long long *mom) {
+    extern __shared__ double2 fbuf[];
+    if (mom && blockIdx.x == gridDim.x - 1 && blockIdx.y == 0)
+        for (uint32_t j = threadIdx.x; j < MOM_WORDS; j += DIAG_WG) mom[j] = 0;
+    double2 *p = blockIdx.y ? pb : pa;
+    const uint32_t N = blockIdx.y ? Nb : Na;
+    if ((blockIdx.y ? kb : ka) == 0) {
+        for (uint32_t j = blockIdx.x * DIAG_WG + threadIdx.x; j < N; j += gridDim.x * DIAG_WG) p[j] = twiddle_of(j, N);
+        return;
+    }
+    switch (blu_r(N)) {
+        case 2: blu_tables<2>(p, N, blockIdx.x, gridDim.x, fbuf); break;
+        case 4: blu_tables<4>(p, N, blockIdx.x, gridDim.x, fbuf); break;
+        case 8: blu_tables<8>(p, N, blockIdx.x, gridDim.x, fbuf); break;
+        default: blu_tables<16>(p, N, blockIdx.x, gridDim.x, fbuf); break;
+    }
+}
+
+template <typename In, int E, int R>
+__global__ __launch_bounds__(DIAG_WG) void blu_pass_kernel(const In *src, uint32_t N, uint32_t M, const BluTab tab,
+                                                            double sign, PassOut dst) {
+    using F = BluFft<R>;
+    if constexpr (E == EPI_ACF) dst.den = acf_den(dst);
+    extern __shared__ double2 fbuf[];
+    constexpr bool REAL = !std::is_same_v<In, double2>;
+    constexpr uint32_t PER = REAL ? 2 : 1;  // columns of the matrix per transform
+    const uint32_t t = threadIdx.x % F::T, sub = threadIdx.x / F::T;
+    double2 *L = fbuf + (size_t)sub * F::COL;
+    const typename F::FromTable tw{tab.ta, tab.tb};
+    // consecutive column groups on the same XCD (the grid is a multiple of 8)
+    const uint32_t g = (blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8;
+    const uint32_t col = (g * F::COLS + sub) * PER;
+    const bool one = col < M, two = REAL && col + 1 < M;
+    // N <= M / 2: rows t + T j, j < 8.  All loads first: the column's (two adjacent bytes or doubles of a
+    // row in one go) and the chirp's.
+    In x0[8], x1[8];
+    double2 ch[8], v[16];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        const uint32_t n = t + F::T * j;
+        x0[j] = In{};
+        x1[j] = In{};
+        ch[j] = make_double2(0.0, 0.0);
+        if (one && n < N) {
+            const In *p = src + (size_t)n * M + col;
+            if constexpr (REAL) {
+                if (two) {
+                    struct Pair { In a, b; } pair;
+                    __builtin_memcpy(&pair, p, sizeof pair);
+                    x0[j] = pair.a;
+                    x1[j] = pair.b;
+                } else {
+                    x0[j] = *p;
+                }
+            } else {
+                x0[j] = *p;
+            }
+        }
+        if (n < N) ch[j] = tab.c[n];
+    }
+    unsigned long long m1 = 0, m2 = 0;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        double2 z;
+        if constexpr (std::is_same_v<In, uint8_t>) {
+            m1 += x0[j] + x1[j];  // zero past the last column
+            m2 += (uint32_t)x0[j] * x0[j] + (uint32_t)x1[j] * x1[j];
+            z = make_double2((double)x0[j] - 128.0, (double)x1[j] - 128.0);
+        } else if constexpr (REAL) {
+            z = make_double2(x0[j], x1[j]);
+        } else {
+            z = x0[j];
+        }
+        if (sign > 0) z.y = -z.y;  // the transform of the other sign: conjugated in and out
+        v[j] = cmul(z, ch[j]);     // zero past the last row, with its chirp
+        v[j + 8] = make_double2(0.0, 0.0);
+    }
+    if constexpr (std::is_same_v<In, uint8_t>)
+        if (dst.mom) add_moments(dst, m1, m2, blockIdx.x);
+    F::forward(v, t, L, tw);
+#pragma unroll
+    for (int i = 0; i < 16 / R; ++i)
+#pragma unroll
+        for (int d = 0; d < R; ++d) v[i * R + d] = cmul(v[i * R + d], tab.b[i * F::T + t + 256 * d]);
+    F::inverse(v, t, L, tw);
+    if constexpr (!REAL) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const uint32_t n = t + F::T * j;
+            if (one && n < N) {
+                const double2 z = cmul(v[j], tab.c[n]);
+                pass_store<E>(dst, col, n, N, M, z.x, sign > 0 ? -z.y : z.y);
+            }
+        }
+    } else {
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const uint32_t n = t + F::T * j;
+            if (n < N) {
+                const double2 z = cmul(v[j], tab.c[n]);
+                L[n] = make_double2(z.x, sign > 0 ? -z.y : z.y);
+            }
+        }
+        __syncthreads();
+        if (!one) return;
+        for (uint32_t k = t; k < dst.nout; k += F::T) {
+            const double2 a = L[k], b = L[k ? N - k : 0];
+            pass_store<E>(dst, col, k, N, M, 0.5 * (a.x + b.x), 0.5 * (a.y - b.y));
+            if (two) pass_store<E>(dst, col + 1, k, N, M, 0.5 * (a.y + b.y), 0.5 * (b.x - a.x));
+        }
+    }
+}
+
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 int check_matrix(const lz_ctx *c, const uint8_t *img, uint32_t h, uint32_t w, const void *out) {
@@ -693,14 +1027,17 @@ struct Dft2 {
     double2 *tw_h, *tw_w, *a, *b;
 };
 
-// Workspace: twiddles for h and w, then two h*w complex buffers; extra bytes go first.
+// Entries of length N's table: its twiddles, or the chirp and its transform.
+size_t table_entries(uint32_t N) { return N <= BLU_MAX ? blu_entries(N) : N; }
+
+// Workspace: tables for h and w, then two h*w complex buffers; extra bytes go first.
 Dft2 dft2_layout(char *ws, uint32_t h, uint32_t w, size_t extra) {
     Dft2 d;
     size_t off = align256(extra);
     d.tw_h = reinterpret_cast<double2 *>(ws + off);
-    off += align256((size_t)h * sizeof(double2));
+    off += align256(table_entries(h) * sizeof(double2));
     d.tw_w = reinterpret_cast<double2 *>(ws + off);
-    off += align256((size_t)w * sizeof(double2));
+    off += align256(table_entries(w) * sizeof(double2));
     d.a = reinterpret_cast<double2 *>(ws + off);
     off += align256((size_t)h * w * sizeof(double2));
     d.b = reinterpret_cast<double2 *>(ws + off);
@@ -708,18 +1045,8 @@ Dft2 dft2_layout(char *ws, uint32_t h, uint32_t w, size_t extra) {
 }
 
 size_t dft2_bytes(uint32_t h, uint32_t w, size_t extra) {
-    return align256(extra) + align256((size_t)h * sizeof(double2)) + align256((size_t)w * sizeof(double2)) +
+    return align256(extra) + align256(table_entries(h) * sizeof(double2)) + align256(table_entries(w) * sizeof(double2)) +
            2 * align256((size_t)h * w * sizeof(double2));
-}
-
-bool fft_ok(const lz_ctx *c, uint32_t N);
-
-// The twiddle tables of the lengths that are not powers of two (the power-of-two FFT makes its own).
-int launch_twiddles(const lz_ctx *c, const Dft2 &d, uint32_t h, uint32_t w, hipStream_t s) {
-    if (!fft_ok(c, h)) hipLaunchKernelGGL(twiddle_kernel, dim3((h + 255) / 256), dim3(256), 0, s, d.tw_h, h);
-    if (!fft_ok(c, w)) hipLaunchKernelGGL(twiddle_kernel, dim3((w + 255) / 256), dim3(256), 0, s, d.tw_w, w);
-    LZ_HIP(hipGetLastError());
-    return LZ_OK;
 }
 
 // The radices of N for the mixed-radix pass (5s, 3s, 4s, then a 2), or nst = 0 if N has
@@ -764,10 +1091,64 @@ bool fft_ok(const lz_ctx *c, uint32_t N) {
     return (N & (N - 1)) == 0 && N <= FFT_MAX && lds <= (size_t)c->dev.lds_per_wg_max;
 }
 
+size_t blu_lds(uint32_t N) {
+    switch (blu_r(N)) {
+        case 2: return BluFft<2>::lds();
+        case 4: return BluFft<4>::lds();
+        case 8: return BluFft<8>::lds();
+        default: return BluFft<16>::lds();
+    }
+}
+
+// Lengths for the chirp convolution: those with a prime factor above 5 from BLU_MIN on, where it takes over from
+// the direct pass in time and error, up to BLU_MAX, whose convolution of 4096 points a workgroup's LDS holds.
+bool blu_ok(const lz_ctx *c, uint32_t N) {
+    return N >= BLU_MIN && N <= BLU_MAX && !fft_ok(c, N) && !mixed_ok(c, N) &&
+           blu_lds(N) <= (size_t)c->dev.lds_per_wg_max && blu_table_lds(N) <= (size_t)c->dev.lds_per_wg_max;
+}
+
+// The tables of the lengths that are not powers of two (the power-of-two FFT makes its own); equal sides share
+// one.  Clears the moment sums mom (or NULL) on the way.
+int launch_tables(const lz_ctx *c, Dft2 &d, uint32_t h, uint32_t w, unsigned long long *mom, hipStream_t s) {
+    if (h == w) d.tw_w = d.tw_h;
+    const bool th = !fft_ok(c, h), tw = h != w && !fft_ok(c, w);
+    if (!th && !tw) {
+        if (mom) LZ_HIP(launch_fill_u64(mom, MOM_WORDS, s));
+        return LZ_OK;
+    }
+    const int kh = blu_ok(c, h), kw = blu_ok(c, w);
+    size_t lds = 0;
+    if (th && kh) lds = blu_table_lds(h);
+    if (tw && kw && blu_table_lds(w) > lds) lds = blu_table_lds(w);
+    if (lds > 65536)
+        LZ_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&tables_kernel),
+                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    uint32_t wgs = TABLE_WGS;  // more for the twiddles of a long side
+    while (wgs < 64 && wgs * DIAG_WG < (h > w ? h : w)) wgs *= 2;
+    hipLaunchKernelGGL(tables_kernel, dim3(wgs, th && tw ? 2 : 1), dim3(DIAG_WG), lds, s, th ? d.tw_h : d.tw_w,
+                       th ? h : w, th ? kh : kw, d.tw_w, w, kw, mom);
+    LZ_HIP(hipGetLastError());
+    return LZ_OK;
+}
+
+template <typename In, int E, int R>
+int launch_blu(const In *src, uint32_t N, uint32_t M, const double2 *table, double sign, PassOut out, hipStream_t s) {
+    using F = BluFft<R>;
+    const uint32_t cols = std::is_same_v<In, double2> ? M : (M + 1) / 2;
+    const uint32_t groups = ((cols + F::COLS - 1) / F::COLS + 7) / 8 * 8;  // a multiple of 8: the XCD-aware order
+    if (F::lds() > 65536)
+        LZ_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&blu_pass_kernel<In, E, R>),
+                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)F::lds()));
+    hipLaunchKernelGGL((blu_pass_kernel<In, E, R>), dim3(groups), dim3(DIAG_WG), F::lds(), s, src, N, M,
+                       blu_tab(const_cast<double2 *>(table), N), sign, out);
+    LZ_HIP(hipGetLastError());
+    return LZ_OK;
+}
+
 // Output (M x out.nout) = transpose of (DFT_N along the rows of src (N x M)), its first out.nout
 // rows, stored by epilogue E: by FFT when N is a power of two up to FFT_MAX, by mixed-radix FFT
-// when N <= FFT_MAX has no prime factor above 5, otherwise directly on the matrix cores (tw: the
-// N-entry table, needed by the last two).
+// when N <= FFT_MAX has no prime factor above 5, by chirp convolution where blu_ok, otherwise directly
+// on the matrix cores (tw: the length's table, needed by the last three).
 template <typename In, int E>
 int launch_dft_pass(const lz_ctx *c, const In *src, uint32_t N, uint32_t M, const double2 *tw, double sign,
                     PassOut out, hipStream_t s) {
@@ -802,6 +1183,13 @@ int launch_dft_pass(const lz_ctx *c, const In *src, uint32_t N, uint32_t M, cons
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
         hipLaunchKernelGGL((fft_mixed_pass_kernel<In, E>), dim3(groups), dim3(DIAG_WG), lds, s, src, N, M, C,
                            mixed_plan(N), tw, sign, out);
+    } else if (blu_ok(c, N)) {
+        switch (blu_r(N)) {
+            case 2: return launch_blu<In, E, 2>(src, N, M, tw, sign, out, s);
+            case 4: return launch_blu<In, E, 4>(src, N, M, tw, sign, out, s);
+            case 8: return launch_blu<In, E, 8>(src, N, M, tw, sign, out, s);
+            default: return launch_blu<In, E, 16>(src, N, M, tw, sign, out, s);
+        }
     } else {
         // 64 x 64 tiles, or 32 x 64 where those would leave compute units idle; DFT_KS32 and
         // DFT_KS64 terms per LDS stage (the smaller tiles do half the products per term)
@@ -823,10 +1211,10 @@ int launch_dft_pass(const lz_ctx *c, const In *src, uint32_t N, uint32_t M, cons
 // complex results, indices r < nout of each transform; real results, whole rows of n, with the
 // mirror rows of an h-row matrix (0: none)
 PassOut complex_out(double2 *z, uint32_t nout, unsigned long long *mom = nullptr) {
-    return PassOut{z, nullptr, nout, 0, mom, 0, 0.0};
+    return PassOut{z, nullptr, nout, 0, mom, 0, 0.0, 0.0};
 }
-PassOut real_out(double *p, uint32_t n, uint32_t h, unsigned long long *mom = nullptr, uint64_t count = 0) {
-    return PassOut{nullptr, p, n, h, mom, count, 0.0};
+PassOut real_out(double *p, uint32_t n, uint32_t h, unsigned long long *mom = nullptr, uint64_t count = 0, double dc = 0.0) {
+    return PassOut{nullptr, p, n, h, mom, count, 0.0, dc};
 }
 
 }  // namespace
@@ -841,14 +1229,15 @@ extern "C" int lz_power_spectrum_2d(lz_ctx *c, const uint8_t *d_img, uint32_t h,
     LZ_HIP(hipSetDevice(c->device));
     char *ws;
     if (int rc = diag_begin(c, s, dft2_bytes(h, w, 0), &ws)) return rc;
-    const Dft2 d = dft2_layout(ws, h, w, 0);
-    if (int rc = launch_twiddles(c, d, h, w, s)) return rc;
+    Dft2 d = dft2_layout(ws, h, w, 0);
+    if (int rc = launch_tables(c, d, h, w, nullptr, s)) return rc;
     // a: w x (h/2 + 1), the columns' transforms up to index h/2 (the rest is their mirror image);
     // then |Z|^2 of the second pass, rows 0..h/2 and their mirror rows, straight into the output
     const uint32_t hh = h / 2 + 1;
     if (int rc = launch_dft_pass<uint8_t, EPI_COMPLEX>(c, d_img, h, w, d.tw_h, -1.0, complex_out(d.a, hh), s))
         return rc;
-    if (int rc = launch_dft_pass<double2, EPI_POWER>(c, d.a, w, hh, d.tw_w, -1.0, real_out(d_power, w, h), s))
+    const double dc = blu_ok(c, h) ? 128.0 * h * w : 0.0;  // that pass transforms x - 128
+    if (int rc = launch_dft_pass<double2, EPI_POWER>(c, d.a, w, hh, d.tw_w, -1.0, real_out(d_power, w, h, nullptr, 0, dc), s))
         return rc;
     return diag_end(c, s);
 }
@@ -859,13 +1248,12 @@ extern "C" int lz_autocorrelation_2d(lz_ctx *c, const uint8_t *d_img, uint32_t h
     hipStream_t s = (hipStream_t)stream;
     LZ_HIP(hipSetDevice(c->device));
     char *ws;
-    const size_t extra = (size_t)MOM_STRIDE * MOM_COPIES * 8;  // the moment sums S1, S2 (a pair per copy)
+    const size_t extra = (size_t)MOM_WORDS * 8;  // the moment sums S1, S2 (a pair per copy)
     if (int rc = diag_begin(c, s, dft2_bytes(h, w, extra), &ws)) return rc;
     unsigned long long *mom = reinterpret_cast<unsigned long long *>(ws);
-    const Dft2 d = dft2_layout(ws, h, w, extra);
+    Dft2 d = dft2_layout(ws, h, w, extra);
     const uint64_t n = (uint64_t)h * w;
-    LZ_HIP(launch_fill_u64(mom, (size_t)MOM_STRIDE * MOM_COPIES, s));
-    if (int rc = launch_twiddles(c, d, h, w, s)) return rc;
+    if (int rc = launch_tables(c, d, h, w, mom, s)) return rc;
     // a: w x (h/2 + 1), adding the moment sums; b: |Z|^2 with the zero frequency removed (h x w,
     // real and even); a: w x (h/2 + 1) again; then Re G / den, den = n S2 - S1^2 from the moment
     // sums, rows 0..h/2 and their mirror rows (G is even too)
