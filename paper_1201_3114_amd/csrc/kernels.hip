@@ -115,13 +115,90 @@ __device__ __forceinline__ void step(double &x, double &y, double &z, double dt,
     else euler_step(x, y, z, dt);
 }
 
+// A counted loop of STEP: %[q] + 1 iterations of U steps (none if %[q] is -1), then %[r] single steps.  A
+// wave alone on its SIMD pays four clocks for each scalar instruction too: U = 120 (a divisor of the default
+// 3000; 8 to 13 KB of code) and two scalar instructions an iteration, instead of 60 and three, are 0.3% at four waves
+// per SIMD; 20 steps an iteration cost 2%.
+#define LZ_STEP_LOOP(U, STEP)                                                  \
+    "s_nop 4\n"                                                                \
+    "s_cmp_lt_i32 %[q], 0\n"                                                   \
+    "s_cbranch_scc1 2f\n"                                                      \
+    ".p2align 6\n"                                                             \
+    "1:\n"                                                                     \
+    ".rept " #U "\n" STEP ".endr\n"                                            \
+    "s_sub_u32 %[q], %[q], 1\n"                                                \
+    "s_cbranch_scc0 1b\n"                                                      \
+    "2:\n"                                                                     \
+    "s_cmp_eq_u32 %[r], 0\n"                                                   \
+    "s_cbranch_scc1 4f\n"                                                      \
+    ".p2align 6\n"                                                             \
+    "3:\n" STEP                                                                \
+    "s_sub_u32 %[r], %[r], 1\n"                                                \
+    "s_cmp_lg_u32 %[r], 0\n"                                                   \
+    "s_cbranch_scc1 3b\n"                                                      \
+    "4:\n"                                                                     \
+    "s_nop 1\n"
+constexpr uint32_t STEP_U = 120, RK4_U = 60;  // RK4: 22 KB, a step is 47 instructions
+
+// F^(n_it) of one chain per lane, for the two Euler maps: the instructions of euler_step and euler_fma_step in
+// an order of our own.  With all SIMDs busy the part's power decides the clock, and the order of a step's
+// instructions decides the power: like operations next to each other, the three products with dt in a row, draw
+// less than the compiler's interleaving.  Of 160 random valid orders of the 14 instructions (24 ms launches of
+// four waves per SIMD, three times each) the times ran from 36.97 to 38.08 ms per 384000 steps; the
+// compiler's order took 37.83, this one 37.00 (35.84 at 2.4 GHz).  For the fused map, 80 orders ran
+// from 37.85 (this one) to 39.69.  64 MiB in 74.0 ms, 76.2 in the order of the compiler (97% and 94% of the issue rate
+// at 2.4 GHz).
+template <int I>
+__device__ __forceinline__ void lane_steps(double &x, double &y, double &z, double dt, uint32_t n_it) {
+    double d, e, f, g;
+    uint32_t q = n_it / STEP_U - 1, r = n_it % STEP_U;
+    if constexpr (I == LZ_INTEGRATOR_EULER_FMA) {
+        asm volatile(LZ_STEP_LOOP(120,
+                         "v_add_f64 %[e], -%[z], %[rho]\n"
+                         "v_add_f64 %[d], %[y], -%[x]\n"
+                         "v_mul_f64 %[d], %[d], %[sigma]\n"
+                         "v_mul_f64 %[g], %[z], %[beta]\n"
+                         "v_fma_f64 %[e], %[x], %[e], -%[y]\n"
+                         "v_fma_f64 %[f], %[x], %[y], -%[g]\n"
+                         "v_fma_f64 %[x], %[dt], %[d], %[x]\n"
+                         "v_fma_f64 %[y], %[dt], %[e], %[y]\n"
+                         "v_fma_f64 %[z], %[dt], %[f], %[z]\n")
+                     : [x] "+v"(x), [y] "+v"(y), [z] "+v"(z), [d] "=&v"(d), [e] "=&v"(e), [f] "=&v"(f), [g] "=&v"(g),
+                       [q] "+s"(q), [r] "+s"(r)
+                     : [dt] "s"(dt), [sigma] "s"(SIGMA), [rho] "s"(RHO), [beta] "s"(BETA)
+                     : "scc");
+    } else {
+        static_assert(I == LZ_INTEGRATOR_EULER, "the two Euler maps");
+        asm volatile(LZ_STEP_LOOP(120,
+                         "v_add_f64 %[e], -%[z], %[rho]\n"
+                         "v_add_f64 %[d], %[y], -%[x]\n"
+                         "v_mul_f64 %[f], %[x], %[y]\n"
+                         "v_mul_f64 %[e], %[x], %[e]\n"
+                         "v_mul_f64 %[g], %[z], %[beta]\n"
+                         "v_mul_f64 %[d], %[d], %[sigma]\n"
+                         "v_add_f64 %[e], %[e], -%[y]\n"
+                         "v_add_f64 %[f], %[f], -%[g]\n"
+                         "v_mul_f64 %[d], %[dt], %[d]\n"
+                         "v_mul_f64 %[e], %[dt], %[e]\n"
+                         "v_mul_f64 %[f], %[dt], %[f]\n"
+                         "v_add_f64 %[x], %[x], %[d]\n"
+                         "v_add_f64 %[y], %[y], %[e]\n"
+                         "v_add_f64 %[z], %[z], %[f]\n")
+                     : [x] "+v"(x), [y] "+v"(y), [z] "+v"(z), [d] "=&v"(d), [e] "=&v"(e), [f] "=&v"(f), [g] "=&v"(g),
+                       [q] "+s"(q), [r] "+s"(r)
+                     : [dt] "s"(dt), [sigma] "s"(SIGMA), [rho] "s"(RHO), [beta] "s"(BETA)
+                     : "scc");
+    }
+}
+
 // Step 2's F^(n_it) for the M chains of a lane, interleaved step by step.
 template <int M, int I>
 __device__ __forceinline__ void lorenz_steps(double (&x)[M], double (&y)[M], double (&z)[M], double dt,
                                              uint32_t n_it) {
+    if constexpr (M == 1 && I != LZ_INTEGRATOR_RK4) return lane_steps<I>(x[0], y[0], z[0], dt, n_it);
     const double h2 = dt * 0.5, h6 = I == LZ_INTEGRATOR_RK4 ? dt / 6.0 : 0.0;
-    // Steps per loop iteration: 60 Euler steps for one chain (a divisor of the default 3000, about 6.7 KB
-    // of code), fewer per iteration with more chains; RK4's 68-operation step gains nothing from more.
+    // Steps per loop iteration: 60 / M Euler steps for M chains (a divisor of the default 3000, about 6.7 KB
+    // of code); RK4's 68-operation step gains nothing from more.
     constexpr int U = I == LZ_INTEGRATOR_RK4 ? 2 : 60 / M;
     const uint32_t q = n_it / U;
     for (uint32_t i = 0; i < q; ++i) {
@@ -198,28 +275,6 @@ __device__ __forceinline__ double dpp_f64(double v) {
     return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
 
-// A counted loop of STEP, 60 steps an iteration (a divisor of the default 3000), then the rest.
-#define LZ_STEP_LOOP(STEP)                                                     \
-    "s_nop 4\n"                                                                \
-    "s_cmp_eq_u32 %[q], 0\n"                                                   \
-    "s_cbranch_scc1 2f\n"                                                      \
-    ".p2align 6\n"                                                             \
-    "1:\n"                                                                     \
-    ".rept 60\n" STEP ".endr\n"                                                \
-    "s_sub_u32 %[q], %[q], 1\n"                                                \
-    "s_cmp_lg_u32 %[q], 0\n"                                                   \
-    "s_cbranch_scc1 1b\n"                                                      \
-    "2:\n"                                                                     \
-    "s_cmp_eq_u32 %[r], 0\n"                                                   \
-    "s_cbranch_scc1 4f\n"                                                      \
-    ".p2align 6\n"                                                             \
-    "3:\n" STEP                                                                \
-    "s_sub_u32 %[r], %[r], 1\n"                                                \
-    "s_cmp_lg_u32 %[r], 0\n"                                                   \
-    "s_cbranch_scc1 3b\n"                                                      \
-    "4:\n"                                                                     \
-    "s_nop 1\n"
-
 // The vector field of the value in v[LO:HI] into OUT (P1 in v[60:61], P2 in v[62:63]).
 #define LZ_QUAD_FIELD(LO, HI, OUT)                                                             \
     "v_fma_f64 %[q0], %[m], v[" LO ":" HI "], %[c]\n"                                          \
@@ -238,14 +293,15 @@ __device__ __forceinline__ void quad_steps(double &x, double &y, double &z, doub
                                            const LaneRole<4> &role, int lane) {
     const int lr = lane & 3;
     double v = lr == 0 ? x : (lr == 1 ? y : (lr == 2 ? z : SIGMA));
-    uint32_t q = n_it / 60, r = n_it % 60;
+    constexpr uint32_t U = I == LZ_INTEGRATOR_RK4 ? RK4_U : STEP_U;
+    uint32_t q = n_it / U - 1, r = n_it % U;
     double q0, u, t, p1, p2;
     if constexpr (I == LZ_INTEGRATOR_RK4) {
         // the field four times (9 instructions each) and the 11 operations of rk4_step between them:
         // 47 instructions a step against 65
         const double h2 = dt * 0.5, h6 = dt / 6.0;
         double a, b, d, w;
-        asm volatile(LZ_STEP_LOOP(
+        asm volatile(LZ_STEP_LOOP(60,
                          LZ_QUAD_FIELD("56", "57", "%[a]")
                          "v_mul_f64 v[58:59], %[a], %[h2]\n"
                          "v_add_f64 v[58:59], v[56:57], v[58:59]\n"
@@ -268,7 +324,7 @@ __device__ __forceinline__ void quad_steps(double &x, double &y, double &z, doub
                      : "scc");
     } else {
         static_assert(I == LZ_INTEGRATOR_EULER, "the quad form of this integrator is no shorter than the one-lane form");
-        asm volatile(LZ_STEP_LOOP(
+        asm volatile(LZ_STEP_LOOP(120,
                          LZ_QUAD_FIELD("56", "57", "%[t]")
                          "v_mul_f64 %[t], %[t], %[dt]\n"
                          "v_add_f64 v[56:57], v[56:57], %[t]\n")
@@ -312,10 +368,10 @@ __device__ __forceinline__ void row_steps(double &x, double &y, double &z, doubl
     double c = r == 0 ? SIGMA : (r == 3 ? 0.0 : x);
     double s2 = r == 0 ? -x : (r == 1 ? RHO : 0.0);
     double u = role.k * w, t;
-    uint32_t q = n_it / 60, rest = n_it % 60;
+    uint32_t q = n_it / STEP_U - 1, rest = n_it % STEP_U;
     if constexpr (I == LZ_INTEGRATOR_EULER_FMA) {
         const double dtv = dt, mdt = role.m * dt;
-        asm volatile(LZ_STEP_LOOP(
+        asm volatile(LZ_STEP_LOOP(120,
                          "v_fma_f64 %[t], %[s], %[s1], %[s2]\n"
                          "v_fma_f64 %[t], %[t], %[c], -%[u]\n"
                          "v_fma_f64 %[w], %[dt], %[t], %[w]\n"
@@ -330,7 +386,7 @@ __device__ __forceinline__ void row_steps(double &x, double &y, double &z, doubl
                      : "scc");
     } else {
         static_assert(I == LZ_INTEGRATOR_EULER, "this integrator has no row form");
-        asm volatile(LZ_STEP_LOOP(
+        asm volatile(LZ_STEP_LOOP(120,
                          "v_fma_f64 %[t], %[s], %[s1], %[s2]\n"
                          "v_mul_f64 %[t], %[t], %[c]\n"
                          "v_add_f64 %[t], %[t], -%[u]\n"
@@ -1213,8 +1269,8 @@ int lanes_per_chain(uint64_t chains, int m, uint32_t integ, int simds) {
 // a short chain's end have no tasks, so off[] counts the waves that have a segment s.  The segment
 // count is the one of 4, 8, 16, 32 with the least predicted time, clocks per step as measured (4 per
 // instruction) and SEG_ROUND_US for a launch, its checkpoints and the gap before it; without 2% of
-// gain (short steps, or W just below a multiple of S) no plan is made.  Measured: 24 MB in 27.7 ms,
-// 39.0 without a plan; 512 files of 79 MB in 91.9 and 95.4.  A round of one wave per SIMD takes 1.20 ms
+// gain (short steps, or W just below a multiple of S) no plan is made.  Measured: 24 MB in 27.1 ms,
+// 39.0 without a plan; 512 files of 79 MB in 89.1 and 93.0.  A round of one wave per SIMD takes 1.18 ms
 // per 16 bytes, the rate of 64 MiB in one launch: the part's clock under a full load.
 SegPlan plan_segments(uint64_t chains, const uint32_t *lens, const lz_params &prm, int simds) {
     constexpr double SEG_ROUND_US = 10.0, CLOCKS_PER_US = 2400.0;

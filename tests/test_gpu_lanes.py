@@ -1,6 +1,6 @@
 """Launches that spread a chain over several lanes (short messages, batches and stream updates), against the
 oracle bit for bit: around the chain counts where the layout changes and the edges of a wave, with
-step counts around the 60 steps of a loop iteration, and beside a launch that leaves no room for
+step counts around the 60 and 120 steps of a loop iteration, and beside a launch that leaves no room for
 the wide layout."""
 import numpy as np
 import pytest
@@ -34,7 +34,7 @@ def edges():
 
 
 @pytest.mark.parametrize("integ", ["euler", "euler_fma", "rk4"])
-@pytest.mark.parametrize("n_it", [1, 59, 60, 121])
+@pytest.mark.parametrize("n_it", [1, 59, 60, 119, 120, 241])
 def test_plain_at_layout_edges(lz, integ, n_it):
     rng = np.random.default_rng(n_it)
     ctx = lz.Context(0, lz.params(n_it=n_it, block_len=B, integrator=integ))
