@@ -688,7 +688,7 @@ __global__ __launch_bounds__(DIAG_WG) void fft_mixed_pass_kernel(const In *src, 
 // (L. Bluestein, 1970).  n^2 mod 2N is exact in integers, so every chirp value is one correctly placed
 // sincospi.  The direct pass takes 8 N operations per value, this one about 20 log2 M + 30.
 //
-// What bounds it is latency: at a side of 1009 the columns are two waves a SIMD, so the FFTs keep their
+// What bounds it is latency: at a side of 1009 the columns are one wave a SIMD, so the FFTs keep their
 // values in registers, 16 per thread, and meet in LDS twice each.  M = 16 x 16 x R: with T = M / 16
 // threads a column, n = t + T j, t = a + R b and k = k1 + 16 c + 256 d (j, b, c, k1 < 16; a, d < R),
 //   forward:  16-point DFTs over j, W_M^{t k1}; over b, W_T^{a c}; R-point DFTs over a;
@@ -700,8 +700,8 @@ __global__ __launch_bounds__(DIAG_WG) void fft_mixed_pass_kernel(const In *src, 
 // leaves the zero frequency out of the convolution's rounding errors; the second pass adds 128 h w there.
 // Against the transform in extended precision the error is below the direct pass's from 80 up: 1.15e-15 of the
 // correlation matrix at 1009 x 1009 (direct 3.3e-15), 7.2e-16 at 131 x 137 (1.6e-15), 1.1e-15 at 2039 x
-// 2011 (4.5e-15).  Measured, spectrum and correlation matrix: 1009 x 1009 in 41 and 80 us (direct 189
-// and 325), 131 x 137 in 28 and 55 (40 and 72), 2039 x 2011 in 105 and 204 (975 and 1606); a pass at 1009
+// 2011 (4.5e-15).  Measured, spectrum and correlation matrix: 1009 x 1009 in 40 and 77 us (direct 189
+// and 325), 131 x 137 in 28 and 51 (40 and 72), 2039 x 2011 in 105 and 204 (975 and 1606); a pass at 1009
 // takes 14 to 18 us, the tables 8.  83 x 89 in 27 and 48 (30 and 53); at 61 x 67 the direct
 // passes take 26 and 46, as long as the convolution at 83.
 constexpr uint32_t BLU_MIN = 80, BLU_MAX = 2048;
@@ -760,13 +760,14 @@ struct BluFft {
     // v[j] = x[t + T j] -> v[i R + d] = X[i T + t + 256 d].  Each stage's twiddles are loaded before its
     // DFTs; TW gives them (BluTable from memory, or computed).
     template <typename TW>
-    static __device__ __forceinline__ void forward(double2 (&v)[16], uint32_t t, double2 *L, const TW &tw) {
+    static __device__ __forceinline__ void forward(double2 (&v)[16], uint32_t t, double2 *L, const TW &tw,
+                                                   double2 (&wa)[16]) {
         double2 w[16];
 #pragma unroll
-        for (int k1 = 1; k1 < 16; ++k1) w[k1] = tw.a(k1, t);
+        for (int k1 = 1; k1 < 16; ++k1) wa[k1] = tw.a(k1, t);
         dft16(v, -1.0);
 #pragma unroll
-        for (int k1 = 0; k1 < 16; ++k1) L[k1 * S1 + t] = k1 ? cmul(v[k1], w[k1]) : v[0];
+        for (int k1 = 0; k1 < 16; ++k1) L[k1 * S1 + t] = k1 ? cmul(v[k1], wa[k1]) : v[0];
         const uint32_t k1 = t / R, a = t % R;
 #pragma unroll
         for (int c = 1; c < 16; ++c) w[c] = tw.b(a, c);
@@ -786,9 +787,11 @@ struct BluFft {
         }
     }
 
-    // the way back (without the factor 1/M); starts with a barrier, so that L may still be read before it
-    template <typename TW>
-    static __device__ __forceinline__ void inverse(double2 (&v)[16], uint32_t t, double2 *L, const TW &tw) {
+    // the way back (without the factor 1/M); starts with a barrier, so that L may still be read before it.  With
+    // KEEP, wa still holds the forward transform's first twiddles; otherwise they are loaded again.
+    template <bool KEEP, typename TW>
+    static __device__ __forceinline__ void inverse(double2 (&v)[16], uint32_t t, double2 *L, const TW &tw,
+                                                   double2 (&wa)[16]) {
         const uint32_t k1 = t / R, a = t % R;
         double2 w[16];
 #pragma unroll
@@ -806,8 +809,9 @@ struct BluFft {
             v[c] = L[a * S2 + 16 * c + k1];
             if (c) v[c] = cmul(v[c], conj2(w[c]));
         }
+        if constexpr (!KEEP)
 #pragma unroll
-        for (int k = 1; k < 16; ++k) w[k] = tw.a(k, t);
+            for (int k = 1; k < 16; ++k) wa[k] = tw.a(k, t);
         __syncthreads();
         dft16(v, 1.0);
 #pragma unroll
@@ -816,7 +820,7 @@ struct BluFft {
 #pragma unroll
         for (int k = 0; k < 16; ++k) {
             v[k] = L[k * S1 + t];
-            if (k) v[k] = cmul(v[k], conj2(w[k]));
+            if (k) v[k] = cmul(v[k], conj2(wa[k]));
         }
         dft16(v, 1.0);
     }
@@ -874,7 +878,8 @@ __device__ __forceinline__ void blu_tables(double2 *p, uint32_t N, uint32_t part
     }
     // the threads past the column have no place in L: they take part in the barriers alone
     if (t < F::T) {
-        F::forward(v, t, lds, typename F::Quarter{q});
+        double2 wa[16];
+        F::forward(v, t, lds, typename F::Quarter{q}, wa);
 #pragma unroll
         for (int i = 0; i < 16 / R; ++i)
 #pragma unroll
@@ -917,7 +922,9 @@ __global__ __launch_bounds__(DIAG_WG) void tables_kernel(double2 *pa, uint32_t N
     }
 }
 
-template <typename In, int E, int R>
+// KEEP: the first stage's twiddles stay in registers between the two FFTs, at more than 256 of them, so one
+// workgroup a CU.
+template <typename In, int E, int R, bool KEEP>
 __global__ __launch_bounds__(DIAG_WG) void blu_pass_kernel(const In *src, uint32_t N, uint32_t M, const BluTab tab,
                                                             double sign, PassOut dst) {
     using F = BluFft<R>;
@@ -978,18 +985,19 @@ __global__ __launch_bounds__(DIAG_WG) void blu_pass_kernel(const In *src, uint32
     }
     if constexpr (std::is_same_v<In, uint8_t>)
         if (dst.mom) add_moments(dst, m1, m2, blockIdx.x);
-    F::forward(v, t, L, tw);
+    double2 wa[16];
+    F::forward(v, t, L, tw, wa);
 #pragma unroll
     for (int i = 0; i < 16 / R; ++i)
 #pragma unroll
         for (int d = 0; d < R; ++d) v[i * R + d] = cmul(v[i * R + d], tab.b[i * F::T + t + 256 * d]);
-    F::inverse(v, t, L, tw);
+    F::template inverse<KEEP>(v, t, L, tw, wa);
     if constexpr (!REAL) {
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
             const uint32_t n = t + F::T * j;
             if (one && n < N) {
-                const double2 z = cmul(v[j], tab.c[n]);
+                const double2 z = cmul(v[j], ch[j]);
                 pass_store<E>(dst, col, n, N, M, z.x, sign > 0 ? -z.y : z.y);
             }
         }
@@ -999,7 +1007,7 @@ __global__ __launch_bounds__(DIAG_WG) void blu_pass_kernel(const In *src, uint32
         for (int j = 0; j < 8; ++j) {
             const uint32_t n = t + F::T * j;
             if (n < N) {
-                const double2 z = cmul(v[j], tab.c[n]);
+                const double2 z = cmul(v[j], ch[j]);
                 L[n] = make_double2(z.x, sign > 0 ? -z.y : z.y);
             }
         }
@@ -1131,16 +1139,26 @@ int launch_tables(const lz_ctx *c, Dft2 &d, uint32_t h, uint32_t w, unsigned lon
     return LZ_OK;
 }
 
+// The twiddles stay in registers (KEEP) where the grid leaves room for one workgroup a CU at most: 1009 x 1009 in 40
+// and 77 us instead of 42 and 81; at 2039 x 2011, four workgroups a CU, it would be 133 and 252 instead of
+// 106 and 203.
 template <typename In, int E, int R>
-int launch_blu(const In *src, uint32_t N, uint32_t M, const double2 *table, double sign, PassOut out, hipStream_t s) {
+int launch_blu(const lz_ctx *c, const In *src, uint32_t N, uint32_t M, const double2 *table, double sign, PassOut out,
+               hipStream_t s) {
     using F = BluFft<R>;
     const uint32_t cols = std::is_same_v<In, double2> ? M : (M + 1) / 2;
     const uint32_t groups = ((cols + F::COLS - 1) / F::COLS + 7) / 8 * 8;  // a multiple of 8: the XCD-aware order
-    if (F::lds() > 65536)
-        LZ_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&blu_pass_kernel<In, E, R>),
-                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)F::lds()));
-    hipLaunchKernelGGL((blu_pass_kernel<In, E, R>), dim3(groups), dim3(DIAG_WG), F::lds(), s, src, N, M,
-                       blu_tab(const_cast<double2 *>(table), N), sign, out);
+    const BluTab tab = blu_tab(const_cast<double2 *>(table), N);
+    auto run = [&](auto keep) -> int {
+        constexpr bool KEEP = decltype(keep)::value;
+        if (F::lds() > 65536)
+            LZ_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&blu_pass_kernel<In, E, R, KEEP>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)F::lds()));
+        hipLaunchKernelGGL((blu_pass_kernel<In, E, R, KEEP>), dim3(groups), dim3(DIAG_WG), F::lds(), s, src, N, M, tab,
+                           sign, out);
+        return LZ_OK;
+    };
+    if (int rc = groups <= (uint32_t)c->dev.cus ? run(std::true_type{}) : run(std::false_type{})) return rc;
     LZ_HIP(hipGetLastError());
     return LZ_OK;
 }
@@ -1185,10 +1203,10 @@ int launch_dft_pass(const lz_ctx *c, const In *src, uint32_t N, uint32_t M, cons
                            mixed_plan(N), tw, sign, out);
     } else if (blu_ok(c, N)) {
         switch (blu_r(N)) {
-            case 2: return launch_blu<In, E, 2>(src, N, M, tw, sign, out, s);
-            case 4: return launch_blu<In, E, 4>(src, N, M, tw, sign, out, s);
-            case 8: return launch_blu<In, E, 8>(src, N, M, tw, sign, out, s);
-            default: return launch_blu<In, E, 16>(src, N, M, tw, sign, out, s);
+            case 2: return launch_blu<In, E, 2>(c, src, N, M, tw, sign, out, s);
+            case 4: return launch_blu<In, E, 4>(c, src, N, M, tw, sign, out, s);
+            case 8: return launch_blu<In, E, 8>(c, src, N, M, tw, sign, out, s);
+            default: return launch_blu<In, E, 16>(c, src, N, M, tw, sign, out, s);
         }
     } else {
         // 64 x 64 tiles, or 32 x 64 where those would leave compute units idle; DFT_KS32 and
