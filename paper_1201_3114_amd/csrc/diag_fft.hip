@@ -28,9 +28,10 @@ __device__ __forceinline__ double2 twiddle_of(uint32_t j, uint32_t N) {
     return make_double2(c, s);
 }
 
-__device__ __forceinline__ double2 dft_value(uint8_t v) { return make_double2((double)v, 0.0); }
-__device__ __forceinline__ double2 dft_value(double v) { return make_double2(v, 0.0); }
-__device__ __forceinline__ double2 dft_value(double2 v) { return v; }
+// an input value as a complex number; bytes less their middle value
+__device__ __forceinline__ double2 dft_value(uint8_t v, double mid) { return make_double2((double)v - mid, 0.0); }
+__device__ __forceinline__ double2 dft_value(double v, double) { return make_double2(v, 0.0); }
+__device__ __forceinline__ double2 dft_value(double2 v, double) { return v; }
 
 // The pass runs on the matrix cores: binary64 MFMA 16x16x4 (v_mfma_f64_16x16x4f64), operand
 // layout: lane i holds A[i % 16][i / 16] and B[i / 16][i % 16] of the 16x4 and 4x16 operands,
@@ -50,67 +51,61 @@ typedef double v4d __attribute__((ext_vector_type(4)));
 // its real results (|Z|^2, or Re Z of an even real matrix's transform) are written twice:
 // row c, and, as row h - c with k2 -> w - k2, each row the pass does not compute itself
 // (mirror = h; 0 writes no mirror rows).
-// The autocorrelation matrix's denominator n S2 - S1^2 comes from the moment sums mom: a first
-// pass over bytes adds each workgroup's S1 = sum x and S2 = sum x^2 into copy (slot mod
-// MOM_COPIES), mom[MOM_STRIDE copy] and the word after it, a cache line per copy so that the
-// device atomics of different copies do not wait for each other (exact: S1 < 2^32 and S2 < 2^40
-// for at most 2^24 bytes); in the last pass one thread per workgroup adds up the copies (den,
-// NaN when n S2 = S1^2, that is when every byte is equal).
-constexpr uint32_t MOM_COPIES = 32, MOM_STRIDE = 16;  // 16 words: 128 bytes
-constexpr uint32_t MOM_WORDS = MOM_COPIES * MOM_STRIDE;
+// The sums S1 = sum x and S2 = sum x^2 over the bytes come from workgroups of their own in the launch that
+// makes the tables (tables_kernel), one pair of words per workgroup, exact (S1 < 2^32 and S2 < 2^40 for at
+// most 2^24 bytes).  They give the autocorrelation matrix's denominator n S2 - S1^2 in the last pass (NaN
+// when n S2 = S1^2, that is when every byte is equal), and the mean: a first pass transforms x - m, m the
+// mean to the nearest whole number, so the subtraction is exact, the mean, mostly the largest part of the
+// input, makes no rounding errors, and the spectrum's second pass adds m h w to the zero frequency.
+constexpr uint32_t SUM_WGS = 256;  // pairs, at most
 enum : int { EPI_COMPLEX = 0, EPI_POWER = 1, EPI_POWER_NODC = 2, EPI_ACF = 3 };
+struct Sums {
+    const unsigned long long *p;  // S1, S2 of workgroup 0, 1, ... (NULL: none, m = 0)
+    uint32_t wgs;
+    uint64_t n;                   // bytes of the matrix
+};
 struct PassOut {
     double2 *z;
     double *p;
     uint32_t nout;
     uint32_t mirror;
-    unsigned long long *mom;  // first pass over bytes: add the moment sums here (or nullptr)
-    uint64_t n;               // EPI_ACF: the matrix's n = h w, with mom holding its moment sums
-    double den;               // EPI_ACF: set by the kernel from mom and n
-    double dc;                // EPI_POWER: added to the zero frequency (a first pass over x - 128 left it out)
+    Sums sums;
+    double den;               // EPI_ACF: set by the kernel from the sums
+    double dc;                // EPI_POWER: m h w, set by the kernel from the sums
 };
 
-// The workgroup's moment sums (per-thread s1, s2) into copy slot mod MOM_COPIES of o.mom; every
-// thread of the workgroup (DIAG_WG threads) calls it: it holds a barrier.
-__device__ __forceinline__ void add_moments(const PassOut &o, unsigned long long s1, unsigned long long s2,
-                                            uint32_t slot) {
-    __shared__ unsigned long long mred[2][DIAG_WG / 64];
+// S1 and S2; every lane of a wave calls it and has the result.
+__device__ __forceinline__ void total_sums(const Sums &q, unsigned long long &s1, unsigned long long &s2) {
+    s1 = s2 = 0;
+    for (uint32_t i = threadIdx.x & 63; i < q.wgs; i += 64) {
+        s1 += q.p[2 * i];
+        s2 += q.p[2 * i + 1];
+    }
     for (int k = 32; k > 0; k >>= 1) {
         s1 += __shfl_xor(s1, k, 64);
         s2 += __shfl_xor(s2, k, 64);
     }
-    if ((threadIdx.x & 63) == 0) {
-        mred[0][threadIdx.x / 64] = s1;
-        mred[1][threadIdx.x / 64] = s2;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        unsigned long long t1 = 0, t2 = 0;
-        for (int w = 0; w < DIAG_WG / 64; ++w) {
-            t1 += mred[0][w];
-            t2 += mred[1][w];
-        }
-        unsigned long long *m = o.mom + MOM_STRIDE * (slot % MOM_COPIES);
-        if (t1) atomicAdd(&m[0], t1);
-        if (t2) atomicAdd(&m[1], t2);
-    }
 }
 
-// n S2 - S1^2 from the moment copies, exactly (n <= 2^24 keeps both products below 2^64): thread 0
-// adds up the copies and the workgroup (DIAG_WG threads, all of which call it) shares the result.
-__device__ __forceinline__ double acf_den(const PassOut &o) {
-    __shared__ double den_s;
-    if (threadIdx.x == 0) {
-        unsigned long long s1 = 0, s2 = 0;
-        for (uint32_t c = 0; c < MOM_COPIES; ++c) {
-            s1 += o.mom[MOM_STRIDE * c];
-            s2 += o.mom[MOM_STRIDE * c + 1];
-        }
-        const unsigned long long d = o.n * s2 - s1 * s1;
-        den_s = d == 0 ? __builtin_nan("") : (double)d;
+// m: the mean byte to the nearest whole number.
+__device__ __forceinline__ double byte_mid(const Sums &q) {
+    if (!q.p) return 0.0;
+    unsigned long long s1, s2;
+    total_sums(q, s1, s2);
+    return rint((double)s1 / (double)q.n);
+}
+
+// What a pass's store needs of the sums.
+template <int E>
+__device__ __forceinline__ void pass_sums(PassOut &o) {
+    if constexpr (E == EPI_ACF) {
+        unsigned long long s1, s2;
+        total_sums(o.sums, s1, s2);
+        const unsigned long long d = o.sums.n * s2 - s1 * s1;  // n <= 2^24 keeps both products below 2^64
+        o.den = d == 0 ? __builtin_nan("") : (double)d;
+    } else if constexpr (E == EPI_POWER) {
+        o.dc = byte_mid(o.sums) * (double)o.sums.n;
     }
-    __syncthreads();
-    return den_s;
 }
 
 template <int E>
@@ -138,15 +133,13 @@ __device__ __forceinline__ void pass_store(const PassOut &o, uint32_t c, uint32_
 template <typename In, int E, int TR, int KS>
 __global__ __launch_bounds__(DIAG_WG) void dft_pass_kernel(const In *src, uint32_t N, uint32_t M, const double2 *tw,
                                                             double sign, PassOut dst) {
-    if constexpr (E == EPI_ACF) dst.den = acf_den(dst);
+    pass_sums<E>(dst);
     // Workgroups are dealt to the 8 XCDs in turn: when the tiles divide evenly, those sharing an
     // input column tile go to one XCD, whose L2 then reads those columns from HBM once.
     const uint32_t nt = gridDim.x * gridDim.y, lin = blockIdx.x + gridDim.x * blockIdx.y;
     const uint32_t tix = nt % 8 == 0 ? (lin % 8) * (nt / 8) + lin / 8 : lin;
     const uint32_t rt = tix % gridDim.x, ct = tix / gridDim.x;  // row tile, column tile
-    // the workgroups of the first row tile see every input once: they add the moment sums
-    const bool moments = std::is_same_v<In, uint8_t> && dst.mom && rt == 0;
-    unsigned long long m1 = 0, m2 = 0;
+    const double mid = std::is_same_v<In, uint8_t> ? byte_mid(dst.sums) : 0.0;
     // TR x 64 outputs per workgroup: with TR = 64 each wave takes a 32 x 32 block as 2 x 2 tiles of
     // 16 x 16, with TR = 32 (grids that would not fill the chip) a 32 x 16 block as 2 x 1 tiles.
     // A real input (bytes or doubles) has no imaginary part: two of the four products are skipped.
@@ -197,12 +190,7 @@ __global__ __launch_bounds__(DIAG_WG) void dft_pass_kernel(const In *src, uint32
         for (int q = 0; q < QX; ++q) {
             const uint32_t k = k0 + kq + 4 * q;
             const bool in = k < N && c0 + cc < M;
-            s_src[kq + 4 * q][cc] = in ? dft_value(nx[q]) : make_double2(0.0, 0.0);
-            if constexpr (std::is_same_v<In, uint8_t>) {
-                const unsigned long long xv = in ? nx[q] : 0;
-                m1 += xv;
-                m2 += xv * xv;
-            }
+            s_src[kq + 4 * q][cc] = in ? dft_value(nx[q], mid) : make_double2(0.0, 0.0);
         }
         for (int q = 0; q < TWQ; ++q) {
             const uint32_t kk = kt + (KS / TWQ) * q, k = k0 + kk;
@@ -228,7 +216,6 @@ __global__ __launch_bounds__(DIAG_WG) void dft_pass_kernel(const In *src, uint32
         }
         __syncthreads();
     }
-    if (moments) add_moments(dst, m1, m2, ct);
     for (int a = 0; a < 2; ++a)
         for (int b = 0; b < TB; ++b)
             for (int j = 0; j < 4; ++j) {
@@ -279,7 +266,7 @@ __device__ __forceinline__ double2 fft_twiddle(const double2 *q, uint32_t j, uin
 template <typename In, int E>
 __global__ __launch_bounds__(DIAG_WG) void fft_pass_kernel(const In *src, uint32_t N, uint32_t M, uint32_t logN,
                                                             uint32_t C, double sign, PassOut dst) {
-    if constexpr (E == EPI_ACF) dst.den = acf_den(dst);
+    pass_sums<E>(dst);
     // C columns of N values (twice when N <= FFT_PP_MAX: each stage reads one copy and writes the
     // other, so it needs one barrier instead of two), then the twiddles
     extern __shared__ double2 fbuf[];
@@ -311,20 +298,15 @@ __global__ __launch_bounds__(DIAG_WG) void fft_pass_kernel(const In *src, uint32
             sincospi(2.0 * (double)j / (double)N, &sn, &cs);
             ftw[j] = make_double2(cs, sign * sn);
         }
-        unsigned long long m1 = 0, m2 = 0;
+        const double mid = std::is_same_v<In, uint8_t> ? byte_mid(dst.sums) : 0.0;
 #pragma unroll
         for (int i = 0; i < FFT_EPT; ++i) {
             const uint32_t e = threadIdx.x + i * DIAG_WG;
             if (e < total) {
                 const uint32_t k = e / cols, cl = e - k * cols;
-                cur[cl * N + k] = dft_value(v[i]);
-                if constexpr (std::is_same_v<In, uint8_t>) {
-                    m1 += v[i];
-                    m2 += (unsigned long long)v[i] * v[i];
-                }
+                cur[cl * N + k] = dft_value(v[i], mid);
             }
         }
-        if (std::is_same_v<In, uint8_t> && dst.mom) add_moments(dst, m1, m2, blockIdx.x);
     }
     __syncthreads();
     uint32_t st = 0;  // log2 of the stride s
@@ -491,7 +473,7 @@ __device__ __forceinline__ void dft16(double2 (&v)[16], double sign) {
 
 template <typename In, int E>
 __global__ __launch_bounds__(DIAG_WG) void fft1k_pass_kernel(const In *src, uint32_t M, double sign, PassOut dst) {
-    if constexpr (E == EPI_ACF) dst.den = acf_den(dst);
+    pass_sums<E>(dst);
     extern __shared__ double2 fbuf[];
     const uint32_t lane = threadIdx.x % 64, wave = threadIdx.x / 64;
     double2 *L = fbuf + (size_t)wave * FFT1K_WAVE;
@@ -510,23 +492,12 @@ __global__ __launch_bounds__(DIAG_WG) void fft1k_pass_kernel(const In *src, uint
         sincospi(2.0 * (double)threadIdx.x / (double)FFT1K, &sn, &cs);
         q[threadIdx.x] = make_double2(cs, sign * sn);
     }
+    const double mid = std::is_same_v<In, uint8_t> ? byte_mid(dst.sums) : 0.0;
     __syncthreads();
-    if constexpr (std::is_same_v<In, uint8_t>) {
-        if (dst.mom) {  // every thread: the waves past the last column add nothing
-            unsigned long long m1 = 0, m2 = 0;
-            if (live)
-#pragma unroll
-                for (int j = 0; j < 16; ++j) {
-                    m1 += x[j];
-                    m2 += (unsigned long long)x[j] * x[j];
-                }
-            add_moments(dst, m1, m2, blockIdx.x);
-        }
-    }
     if (!live) return;  // the whole wave
     double2 v[16];
 #pragma unroll
-    for (int j = 0; j < 16; ++j) v[j] = dft_value(x[j]);
+    for (int j = 0; j < 16; ++j) v[j] = dft_value(x[j], mid);
     // stage 1: 16-point DFT over j, twiddles W^{t k1}
     dft16(v, sign);
 #pragma unroll
@@ -553,6 +524,53 @@ __global__ __launch_bounds__(DIAG_WG) void fft1k_pass_kernel(const In *src, uint
         pass_store<E>(dst, col, p + 512, FFT1K, M, a2.x, a2.y);
         pass_store<E>(dst, col, p + 768, FFT1K, M, a3.x, a3.y);
     }
+}
+
+// ---- two real columns as one complex column ---------------------------------------------
+//
+// The mixed-radix and the chirp pass over real columns (bytes, or the inverse passes' real spectrum) transform
+// z = x1 + i x2 for columns 2p and 2p + 1; X1 and X2 are the even and odd parts of Z, of which only the indices
+// up to N/2 are kept.  That halves the transforms: 1000 x 1000 takes 43 and 79 us (spectrum and correlation
+// matrix), 52 and 104 with a transform per column.  The two columns share their rounding errors; without the mean
+// (see Sums) these are no larger than they were with it in a transform per column.
+template <typename In>
+constexpr uint32_t per_transform() { return std::is_same_v<In, double2> ? 1 : 2; }
+
+template <typename In>
+struct PackIn { In a, b; };
+template <>
+struct PackIn<double2> { double2 a; };
+
+// The input of transform p at row k of the N x M matrix src.
+template <typename In>
+__device__ __forceinline__ PackIn<In> pack_load(const In *src, uint32_t k, uint32_t p, uint32_t M) {
+    if constexpr (std::is_same_v<In, double2>) {
+        return PackIn<In>{src[(size_t)k * M + p]};
+    } else {
+        const In *q = src + (size_t)k * M + 2 * p;
+        PackIn<In> v;
+        if (2 * p + 1 < M) {
+            __builtin_memcpy(&v, q, sizeof v);  // one load of both
+        } else {
+            v.a = *q;
+            v.b = In{};
+        }
+        return v;
+    }
+}
+
+template <typename In>
+__device__ __forceinline__ double2 pack_value(const PackIn<In> &v, double mid) {
+    if constexpr (std::is_same_v<In, double2>) return v.a;
+    else return make_double2((double)v.a - mid, (double)v.b - mid);  // mid = 0 but for bytes
+}
+
+// Indices k and N - k of a transform of columns c and c + 1 -> index k of both.
+template <int E>
+__device__ __forceinline__ void pair_store(const PassOut &o, uint32_t c, uint32_t k, uint32_t N, uint32_t M, double2 a,
+                                           double2 b) {
+    pass_store<E>(o, c, k, N, M, 0.5 * (a.x + b.x), 0.5 * (a.y - b.y));
+    if (c + 1 < M) pass_store<E>(o, c + 1, k, N, M, 0.5 * (a.y + b.y), 0.5 * (b.x - a.x));
 }
 
 // Lengths N <= FFT_MAX whose only prime factors are 2, 3 and 5 (and that are not
@@ -625,43 +643,38 @@ template <typename In, int E>
 __global__ __launch_bounds__(DIAG_WG) void fft_mixed_pass_kernel(const In *src, uint32_t N, uint32_t M, uint32_t C,
                                                                   FftPlan plan, const double2 *tw, double sign,
                                                                   PassOut dst) {
-    if constexpr (E == EPI_ACF) dst.den = acf_den(dst);
-    extern __shared__ double2 fbuf[];  // C columns of N values, then the N twiddles
+    pass_sums<E>(dst);
+    extern __shared__ double2 fbuf[];  // C transforms of N values, then the N twiddles
     double2 *ftw = fbuf + (size_t)C * N;
     uint32_t g = blockIdx.x;
     if (gridDim.x % 8 == 0) g = (blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8;
-    const uint32_t c0 = g * C;
-    if (c0 >= M) return;  // a workgroup of the padding (the grid is a multiple of 8)
-    const uint32_t cols = M - c0 < C ? M - c0 : C;
+    const uint32_t c0 = g * C, MT = (M + per_transform<In>() - 1) / per_transform<In>();
+    if (c0 >= MT) return;  // a workgroup of the padding (the grid is a multiple of 8)
+    const uint32_t cols = MT - c0 < C ? MT - c0 : C;  // transforms
     const uint32_t total = cols * N;
     {
-        In v[FFT_EPT];
+        PackIn<In> v[FFT_EPT];
 #pragma unroll
         for (int i = 0; i < FFT_EPT; ++i) {
             const uint32_t e = threadIdx.x + i * DIAG_WG;
             if (e < total) {
                 const uint32_t k = e / cols, cl = e - k * cols;
-                v[i] = src[(size_t)k * M + c0 + cl];
+                v[i] = pack_load(src, k, c0 + cl, M);
             }
         }
         for (uint32_t j = threadIdx.x; j < N; j += DIAG_WG) {
             const double2 w = tw[j];
             ftw[j] = make_double2(w.x, sign * w.y);
         }
-        unsigned long long m1 = 0, m2 = 0;
+        const double mid = std::is_same_v<In, uint8_t> ? byte_mid(dst.sums) : 0.0;
 #pragma unroll
         for (int i = 0; i < FFT_EPT; ++i) {
             const uint32_t e = threadIdx.x + i * DIAG_WG;
             if (e < total) {
                 const uint32_t k = e / cols, cl = e - k * cols;
-                fbuf[cl * N + k] = dft_value(v[i]);
-                if constexpr (std::is_same_v<In, uint8_t>) {
-                    m1 += v[i];
-                    m2 += (unsigned long long)v[i] * v[i];
-                }
+                fbuf[cl * N + k] = pack_value<In>(v[i], mid);
             }
         }
-        if (std::is_same_v<In, uint8_t> && dst.mom) add_moments(dst, m1, m2, blockIdx.x);
     }
     __syncthreads();
     uint32_t s = 1;
@@ -673,10 +686,19 @@ __global__ __launch_bounds__(DIAG_WG) void fft_mixed_pass_kernel(const In *src, 
         else mixed_stage<2>(fbuf, ftw, N, cols, s, sign);
         s *= R;
     }
-    for (uint32_t e = threadIdx.x; e < total; e += DIAG_WG) {
-        const double2 v = fbuf[e];
-        const uint32_t cl = e / N;
-        pass_store<E>(dst, c0 + cl, e - cl * N, N, M, v.x, v.y);
+    if constexpr (per_transform<In>() == 1) {
+        for (uint32_t e = threadIdx.x; e < total; e += DIAG_WG) {
+            const double2 v = fbuf[e];
+            const uint32_t cl = e / N;
+            pass_store<E>(dst, c0 + cl, e - cl * N, N, M, v.x, v.y);
+        }
+    } else {
+        const uint32_t half = dst.nout;  // N / 2 + 1
+        for (uint32_t e = threadIdx.x; e < cols * half; e += DIAG_WG) {
+            const uint32_t cl = e / half, k = e - cl * half;
+            const double2 *z = fbuf + (size_t)cl * N;
+            pair_store<E>(dst, 2 * (c0 + cl), k, N, M, z[k], z[k ? N - k : 0]);
+        }
     }
 }
 
@@ -695,15 +717,13 @@ __global__ __launch_bounds__(DIAG_WG) void fft_mixed_pass_kernel(const In *src, 
 //   inverse:  the same stages mirrored, so neither needs a reordering pass.
 // The forward result lies as X[p + 256 d] at thread p mod T: natural order, in which the transformed
 // chirp (the second table, 1/M included) is multiplied in.  The LDS row strides S1 and S2 put the 8 lanes
-// of a 128-byte LDS cycle on distinct banks in every exchange.  Two real columns make one complex column
-// (z = x1 + i x2; X1 and X2 are the even and odd parts of Z).  Bytes enter as x - 128, exactly, which
-// leaves the zero frequency out of the convolution's rounding errors; the second pass adds 128 h w there.
+// of a 128-byte LDS cycle on distinct banks in every exchange.  Real columns go in pairs.
 // Against the transform in extended precision the error is below the direct pass's from 80 up: 1.15e-15 of the
 // correlation matrix at 1009 x 1009 (direct 3.3e-15), 7.2e-16 at 131 x 137 (1.6e-15), 1.1e-15 at 2039 x
-// 2011 (4.5e-15).  Measured, spectrum and correlation matrix: 1009 x 1009 in 40 and 77 us (direct 189
-// and 325), 131 x 137 in 28 and 51 (40 and 72), 2039 x 2011 in 105 and 204 (975 and 1606); a pass at 1009
-// takes 14 to 18 us, the tables 8.  83 x 89 in 27 and 48 (30 and 53); at 61 x 67 the direct
-// passes take 26 and 46, as long as the convolution at 83.
+// 2011 (4.5e-15).  Measured, spectrum and correlation matrix: 1009 x 1009 in 41 and 76 us (direct 189
+// and 325), 131 x 137 in 28 and 45 (40 and 72), 2039 x 2011 in 107 and 190 (975 and 1606); a pass at 1009
+// takes 14 to 18 us, the tables 8.  83 x 89 in 26 and 42 (30 and 53); at 61 x 67 the direct
+// passes take 26 and 42, as long as the convolution at 83.
 constexpr uint32_t BLU_MIN = 80, BLU_MAX = 2048;
 
 // Per length N: the chirp c[n] (N entries), the transformed chirp over M (M entries, natural order), then
@@ -900,26 +920,80 @@ __host__ __device__ constexpr size_t blu_table_lds(uint32_t N) {
 static_assert(BluFft<2>::COL == 16 * 34 && BluFft<4>::COL == 16 * 68 && BluFft<8>::COL == 8 * 257 && BluFft<16>::COL == 16 * 257,
               "columns of blu_table_lds");
 
-// blockIdx.y = 0: the tables of length Na, 1: those of Nb.  kind: 0 for the twiddles of the mixed-radix and direct
-// passes, 1 for the chirp convolution's tables.  mom (or NULL): the moment sums, cleared here for the passes.
+// Workgroups of one launch: a.wgs for the tables of length a.N, b.wgs for those of b.N, and the rest, one
+// pair of sums each (Sums).  kind: 0 for the twiddles of the mixed-radix and direct passes, 1 for the chirp
+// convolution's tables.
+struct TableJob {
+    double2 *p;
+    uint32_t N, wgs;
+    int kind;
+};
 constexpr uint32_t TABLE_WGS = 9;
-__global__ __launch_bounds__(DIAG_WG) void tables_kernel(double2 *pa, uint32_t Na, int ka, double2 *pb, uint32_t Nb,
-                                                         int kb, unsigned long long *mom) {
-    extern __shared__ double2 fbuf[];
-    if (mom && blockIdx.x == gridDim.x - 1 && blockIdx.y == 0)
-        for (uint32_t j = threadIdx.x; j < MOM_WORDS; j += DIAG_WG) mom[j] = 0;
-    double2 *p = blockIdx.y ? pb : pa;
-    const uint32_t N = blockIdx.y ? Nb : Na;
-    if ((blockIdx.y ? kb : ka) == 0) {
-        for (uint32_t j = blockIdx.x * DIAG_WG + threadIdx.x; j < N; j += gridDim.x * DIAG_WG) p[j] = twiddle_of(j, N);
+
+__device__ __forceinline__ void make_table(const TableJob &job, uint32_t part, double2 *lds) {
+    if (job.kind == 0) {
+        for (uint32_t j = part * DIAG_WG + threadIdx.x; j < job.N; j += job.wgs * DIAG_WG) job.p[j] = twiddle_of(j, job.N);
         return;
     }
-    switch (blu_r(N)) {
-        case 2: blu_tables<2>(p, N, blockIdx.x, gridDim.x, fbuf); break;
-        case 4: blu_tables<4>(p, N, blockIdx.x, gridDim.x, fbuf); break;
-        case 8: blu_tables<8>(p, N, blockIdx.x, gridDim.x, fbuf); break;
-        default: blu_tables<16>(p, N, blockIdx.x, gridDim.x, fbuf); break;
+    switch (blu_r(job.N)) {
+        case 2: blu_tables<2>(job.p, job.N, part, job.wgs, lds); break;
+        case 4: blu_tables<4>(job.p, job.N, part, job.wgs, lds); break;
+        case 8: blu_tables<8>(job.p, job.N, part, job.wgs, lds); break;
+        default: blu_tables<16>(job.p, job.N, part, job.wgs, lds); break;
     }
+}
+
+// Workgroup `part` of `wgs` of the sums: 16 bytes a load at any alignment, the tail by bytes.
+__device__ __forceinline__ void make_sums(const uint8_t *x, uint64_t n, unsigned long long *sums, uint32_t part,
+                                          uint32_t wgs) {
+    __shared__ unsigned long long red[2][DIAG_WG / 64];
+    unsigned long long s1 = 0, s2 = 0;
+    auto word = [&](uint32_t w) {
+        for (int q = 0; q < 4; ++q) {
+            const uint32_t v = (w >> (8 * q)) & 0xFF;
+            s1 += v;
+            s2 += v * v;
+        }
+    };
+    const uint64_t nv = n / 16;
+    for (uint64_t i = (uint64_t)part * DIAG_WG + threadIdx.x; i < nv; i += (uint64_t)wgs * DIAG_WG) {
+        uint4 v;
+        __builtin_memcpy(&v, x + 16 * i, 16);
+        word(v.x);
+        word(v.y);
+        word(v.z);
+        word(v.w);
+    }
+    if (part == 0 && nv * 16 + threadIdx.x < n) {
+        const uint32_t v = x[nv * 16 + threadIdx.x];
+        s1 += v;
+        s2 += v * v;
+    }
+    for (int k = 32; k > 0; k >>= 1) {
+        s1 += __shfl_xor(s1, k, 64);
+        s2 += __shfl_xor(s2, k, 64);
+    }
+    if ((threadIdx.x & 63) == 0) {
+        red[0][threadIdx.x / 64] = s1;
+        red[1][threadIdx.x / 64] = s2;
+    }
+    __syncthreads();
+    if (threadIdx.x < 2) {
+        unsigned long long t = 0;
+        for (int w = 0; w < DIAG_WG / 64; ++w) t += red[threadIdx.x][w];
+        sums[2 * part + threadIdx.x] = t;
+    }
+}
+
+__global__ __launch_bounds__(DIAG_WG) void tables_kernel(TableJob a, TableJob b, const uint8_t *img, uint64_t n,
+                                                         unsigned long long *sums) {
+    extern __shared__ double2 fbuf[];
+    uint32_t part = blockIdx.x;
+    if (part < a.wgs) return make_table(a, part, fbuf);
+    part -= a.wgs;
+    if (part < b.wgs) return make_table(b, part, fbuf);
+    part -= b.wgs;
+    make_sums(img, n, sums, part, gridDim.x - a.wgs - b.wgs);
 }
 
 // KEEP: the first stage's twiddles stay in registers between the two FFTs, at more than 256 of them, so one
@@ -928,63 +1002,35 @@ template <typename In, int E, int R, bool KEEP>
 __global__ __launch_bounds__(DIAG_WG) void blu_pass_kernel(const In *src, uint32_t N, uint32_t M, const BluTab tab,
                                                             double sign, PassOut dst) {
     using F = BluFft<R>;
-    if constexpr (E == EPI_ACF) dst.den = acf_den(dst);
+    pass_sums<E>(dst);
     extern __shared__ double2 fbuf[];
     constexpr bool REAL = !std::is_same_v<In, double2>;
-    constexpr uint32_t PER = REAL ? 2 : 1;  // columns of the matrix per transform
     const uint32_t t = threadIdx.x % F::T, sub = threadIdx.x / F::T;
     double2 *L = fbuf + (size_t)sub * F::COL;
     const typename F::FromTable tw{tab.ta, tab.tb};
     // consecutive column groups on the same XCD (the grid is a multiple of 8)
     const uint32_t g = (blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8;
-    const uint32_t col = (g * F::COLS + sub) * PER;
-    const bool one = col < M, two = REAL && col + 1 < M;
-    // N <= M / 2: rows t + T j, j < 8.  All loads first: the column's (two adjacent bytes or doubles of a
-    // row in one go) and the chirp's.
-    In x0[8], x1[8];
+    const uint32_t tr = g * F::COLS + sub, col = tr * per_transform<In>();
+    const bool one = col < M;
+    // N <= M / 2: rows t + T j, j < 8.  All loads first: the column's and the chirp's.
+    PackIn<In> x[8];
     double2 ch[8], v[16];
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
         const uint32_t n = t + F::T * j;
-        x0[j] = In{};
-        x1[j] = In{};
+        x[j] = PackIn<In>{};
         ch[j] = make_double2(0.0, 0.0);
-        if (one && n < N) {
-            const In *p = src + (size_t)n * M + col;
-            if constexpr (REAL) {
-                if (two) {
-                    struct Pair { In a, b; } pair;
-                    __builtin_memcpy(&pair, p, sizeof pair);
-                    x0[j] = pair.a;
-                    x1[j] = pair.b;
-                } else {
-                    x0[j] = *p;
-                }
-            } else {
-                x0[j] = *p;
-            }
-        }
+        if (one && n < N) x[j] = pack_load(src, n, tr, M);
         if (n < N) ch[j] = tab.c[n];
     }
-    unsigned long long m1 = 0, m2 = 0;
+    const double mid = std::is_same_v<In, uint8_t> ? byte_mid(dst.sums) : 0.0;
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
-        double2 z;
-        if constexpr (std::is_same_v<In, uint8_t>) {
-            m1 += x0[j] + x1[j];  // zero past the last column
-            m2 += (uint32_t)x0[j] * x0[j] + (uint32_t)x1[j] * x1[j];
-            z = make_double2((double)x0[j] - 128.0, (double)x1[j] - 128.0);
-        } else if constexpr (REAL) {
-            z = make_double2(x0[j], x1[j]);
-        } else {
-            z = x0[j];
-        }
+        double2 z = pack_value<In>(x[j], mid);
         if (sign > 0) z.y = -z.y;  // the transform of the other sign: conjugated in and out
         v[j] = cmul(z, ch[j]);     // zero past the last row, with its chirp
         v[j + 8] = make_double2(0.0, 0.0);
     }
-    if constexpr (std::is_same_v<In, uint8_t>)
-        if (dst.mom) add_moments(dst, m1, m2, blockIdx.x);
     double2 wa[16];
     F::forward(v, t, L, tw, wa);
 #pragma unroll
@@ -1014,9 +1060,7 @@ __global__ __launch_bounds__(DIAG_WG) void blu_pass_kernel(const In *src, uint32
         __syncthreads();
         if (!one) return;
         for (uint32_t k = t; k < dst.nout; k += F::T) {
-            const double2 a = L[k], b = L[k ? N - k : 0];
-            pass_store<E>(dst, col, k, N, M, 0.5 * (a.x + b.x), 0.5 * (a.y - b.y));
-            if (two) pass_store<E>(dst, col + 1, k, N, M, 0.5 * (a.y + b.y), 0.5 * (b.x - a.x));
+            pair_store<E>(dst, col, k, N, M, L[k], L[k ? N - k : 0]);
         }
     }
 }
@@ -1032,16 +1076,20 @@ int check_matrix(const lz_ctx *c, const uint8_t *img, uint32_t h, uint32_t w, co
 }
 
 struct Dft2 {
+    unsigned long long *sums;
     double2 *tw_h, *tw_w, *a, *b;
 };
 
 // Entries of length N's table: its twiddles, or the chirp and its transform.
 size_t table_entries(uint32_t N) { return N <= BLU_MAX ? blu_entries(N) : N; }
 
-// Workspace: tables for h and w, then two h*w complex buffers; extra bytes go first.
-Dft2 dft2_layout(char *ws, uint32_t h, uint32_t w, size_t extra) {
+constexpr size_t SUMS_BYTES = (size_t)SUM_WGS * 2 * sizeof(unsigned long long);
+
+// Workspace: the sums, tables for h and w, then two h*w complex buffers.
+Dft2 dft2_layout(char *ws, uint32_t h, uint32_t w) {
     Dft2 d;
-    size_t off = align256(extra);
+    size_t off = align256(SUMS_BYTES);
+    d.sums = reinterpret_cast<unsigned long long *>(ws);
     d.tw_h = reinterpret_cast<double2 *>(ws + off);
     off += align256(table_entries(h) * sizeof(double2));
     d.tw_w = reinterpret_cast<double2 *>(ws + off);
@@ -1052,9 +1100,9 @@ Dft2 dft2_layout(char *ws, uint32_t h, uint32_t w, size_t extra) {
     return d;
 }
 
-size_t dft2_bytes(uint32_t h, uint32_t w, size_t extra) {
-    return align256(extra) + align256(table_entries(h) * sizeof(double2)) + align256(table_entries(w) * sizeof(double2)) +
-           2 * align256((size_t)h * w * sizeof(double2));
+size_t dft2_bytes(uint32_t h, uint32_t w) {
+    return align256(SUMS_BYTES) + align256(table_entries(h) * sizeof(double2)) +
+           align256(table_entries(w) * sizeof(double2)) + 2 * align256((size_t)h * w * sizeof(double2));
 }
 
 // The radices of N for the mixed-radix pass (5s, 3s, 4s, then a 2), or nst = 0 if N has
@@ -1115,26 +1163,32 @@ bool blu_ok(const lz_ctx *c, uint32_t N) {
            blu_lds(N) <= (size_t)c->dev.lds_per_wg_max && blu_table_lds(N) <= (size_t)c->dev.lds_per_wg_max;
 }
 
-// The tables of the lengths that are not powers of two (the power-of-two FFT makes its own); equal sides share
-// one.  Clears the moment sums mom (or NULL) on the way.
-int launch_tables(const lz_ctx *c, Dft2 &d, uint32_t h, uint32_t w, unsigned long long *mom, hipStream_t s) {
+// One launch for the tables of the lengths that are not powers of two (the power-of-two FFT makes its own;
+// equal sides share one) and the sums over the bytes, if anything needs them: the correlation matrix does,
+// and a spectrum with a table to make takes the mean out as well.
+int launch_tables(const lz_ctx *c, Dft2 &d, const uint8_t *img, uint32_t h, uint32_t w, bool need_sums, Sums *sums,
+                  hipStream_t s) {
     if (h == w) d.tw_w = d.tw_h;
-    const bool th = !fft_ok(c, h), tw = h != w && !fft_ok(c, w);
-    if (!th && !tw) {
-        if (mom) LZ_HIP(launch_fill_u64(mom, MOM_WORDS, s));
-        return LZ_OK;
-    }
-    const int kh = blu_ok(c, h), kw = blu_ok(c, w);
+    TableJob a{}, b{};
     size_t lds = 0;
-    if (th && kh) lds = blu_table_lds(h);
-    if (tw && kw && blu_table_lds(w) > lds) lds = blu_table_lds(w);
+    auto job = [&](double2 *p, uint32_t N) {
+        TableJob t{p, N, 0, blu_ok(c, N) ? 1 : 0};
+        if (fft_ok(c, N)) return t;
+        t.wgs = t.kind ? TABLE_WGS : (N + DIAG_WG - 1) / DIAG_WG;
+        if (t.kind && blu_table_lds(N) > lds) lds = blu_table_lds(N);
+        return t;
+    };
+    a = job(d.tw_h, h);
+    if (h != w) b = job(d.tw_w, w);
+    *sums = Sums{nullptr, 0, (uint64_t)h * w};
+    if (!need_sums && !a.wgs && !b.wgs) return LZ_OK;
+    const uint64_t want = (sums->n + 16383) / 16384;  // 16 KiB a workgroup at least
+    sums->wgs = want < SUM_WGS ? (uint32_t)want : SUM_WGS;
+    sums->p = d.sums;
     if (lds > 65536)
         LZ_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&tables_kernel),
                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    uint32_t wgs = TABLE_WGS;  // more for the twiddles of a long side
-    while (wgs < 64 && wgs * DIAG_WG < (h > w ? h : w)) wgs *= 2;
-    hipLaunchKernelGGL(tables_kernel, dim3(wgs, th && tw ? 2 : 1), dim3(DIAG_WG), lds, s, th ? d.tw_h : d.tw_w,
-                       th ? h : w, th ? kh : kw, d.tw_w, w, kw, mom);
+    hipLaunchKernelGGL(tables_kernel, dim3(a.wgs + b.wgs + sums->wgs), dim3(DIAG_WG), lds, s, a, b, img, sums->n, d.sums);
     LZ_HIP(hipGetLastError());
     return LZ_OK;
 }
@@ -1194,7 +1248,8 @@ int launch_dft_pass(const lz_ctx *c, const In *src, uint32_t N, uint32_t M, cons
     } else if (mixed_ok(c, N)) {
         const uint32_t per_wg = N > FFT_WG_ELEMS ? N : FFT_WG_ELEMS;
         const uint32_t C = per_wg / N;
-        const uint32_t groups = ((M + C - 1) / C + 7) / 8 * 8;  // a multiple of 8: the XCD-aware order
+        const uint32_t MT = (M + per_transform<In>() - 1) / per_transform<In>();
+        const uint32_t groups = ((MT + C - 1) / C + 7) / 8 * 8;  // a multiple of 8: the XCD-aware order
         const size_t lds = mixed_lds(N);
         if (lds > 65536)
             LZ_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&fft_mixed_pass_kernel<In, E>),
@@ -1227,12 +1282,12 @@ int launch_dft_pass(const lz_ctx *c, const In *src, uint32_t N, uint32_t M, cons
 }
 
 // complex results, indices r < nout of each transform; real results, whole rows of n, with the
-// mirror rows of an h-row matrix (0: none)
-PassOut complex_out(double2 *z, uint32_t nout, unsigned long long *mom = nullptr) {
-    return PassOut{z, nullptr, nout, 0, mom, 0, 0.0, 0.0};
+// mirror rows of an h-row matrix (0: none).  sums: for a pass over bytes and for the last pass.
+PassOut complex_out(double2 *z, uint32_t nout, const Sums &sums = Sums{}) {
+    return PassOut{z, nullptr, nout, 0, sums, 0.0, 0.0};
 }
-PassOut real_out(double *p, uint32_t n, uint32_t h, unsigned long long *mom = nullptr, uint64_t count = 0, double dc = 0.0) {
-    return PassOut{nullptr, p, n, h, mom, count, 0.0, dc};
+PassOut real_out(double *p, uint32_t n, uint32_t h, const Sums &sums = Sums{}) {
+    return PassOut{nullptr, p, n, h, sums, 0.0, 0.0};
 }
 
 }  // namespace
@@ -1246,16 +1301,16 @@ extern "C" int lz_power_spectrum_2d(lz_ctx *c, const uint8_t *d_img, uint32_t h,
     hipStream_t s = (hipStream_t)stream;
     LZ_HIP(hipSetDevice(c->device));
     char *ws;
-    if (int rc = diag_begin(c, s, dft2_bytes(h, w, 0), &ws)) return rc;
-    Dft2 d = dft2_layout(ws, h, w, 0);
-    if (int rc = launch_tables(c, d, h, w, nullptr, s)) return rc;
+    if (int rc = diag_begin(c, s, dft2_bytes(h, w), &ws)) return rc;
+    Dft2 d = dft2_layout(ws, h, w);
+    Sums sums;
+    if (int rc = launch_tables(c, d, d_img, h, w, false, &sums, s)) return rc;
     // a: w x (h/2 + 1), the columns' transforms up to index h/2 (the rest is their mirror image);
     // then |Z|^2 of the second pass, rows 0..h/2 and their mirror rows, straight into the output
     const uint32_t hh = h / 2 + 1;
-    if (int rc = launch_dft_pass<uint8_t, EPI_COMPLEX>(c, d_img, h, w, d.tw_h, -1.0, complex_out(d.a, hh), s))
+    if (int rc = launch_dft_pass<uint8_t, EPI_COMPLEX>(c, d_img, h, w, d.tw_h, -1.0, complex_out(d.a, hh, sums), s))
         return rc;
-    const double dc = blu_ok(c, h) ? 128.0 * h * w : 0.0;  // that pass transforms x - 128
-    if (int rc = launch_dft_pass<double2, EPI_POWER>(c, d.a, w, hh, d.tw_w, -1.0, real_out(d_power, w, h, nullptr, 0, dc), s))
+    if (int rc = launch_dft_pass<double2, EPI_POWER>(c, d.a, w, hh, d.tw_w, -1.0, real_out(d_power, w, h, sums), s))
         return rc;
     return diag_end(c, s);
 }
@@ -1266,24 +1321,22 @@ extern "C" int lz_autocorrelation_2d(lz_ctx *c, const uint8_t *d_img, uint32_t h
     hipStream_t s = (hipStream_t)stream;
     LZ_HIP(hipSetDevice(c->device));
     char *ws;
-    const size_t extra = (size_t)MOM_WORDS * 8;  // the moment sums S1, S2 (a pair per copy)
-    if (int rc = diag_begin(c, s, dft2_bytes(h, w, extra), &ws)) return rc;
-    unsigned long long *mom = reinterpret_cast<unsigned long long *>(ws);
-    Dft2 d = dft2_layout(ws, h, w, extra);
-    const uint64_t n = (uint64_t)h * w;
-    if (int rc = launch_tables(c, d, h, w, mom, s)) return rc;
-    // a: w x (h/2 + 1), adding the moment sums; b: |Z|^2 with the zero frequency removed (h x w,
-    // real and even); a: w x (h/2 + 1) again; then Re G / den, den = n S2 - S1^2 from the moment
-    // sums, rows 0..h/2 and their mirror rows (G is even too)
+    if (int rc = diag_begin(c, s, dft2_bytes(h, w), &ws)) return rc;
+    Dft2 d = dft2_layout(ws, h, w);
+    Sums sums;
+    if (int rc = launch_tables(c, d, d_img, h, w, true, &sums, s)) return rc;
+    // a: w x (h/2 + 1); b: |Z|^2 with the zero frequency removed (h x w, real and even); a: w x (h/2 + 1)
+    // again; then Re G / den, den = n S2 - S1^2 from the sums, rows 0..h/2 and their mirror rows (G is
+    // even too)
     const uint32_t hh = h / 2 + 1;
     double *pm = reinterpret_cast<double *>(d.b);
-    if (int rc = launch_dft_pass<uint8_t, EPI_COMPLEX>(c, d_img, h, w, d.tw_h, -1.0, complex_out(d.a, hh, mom), s))
+    if (int rc = launch_dft_pass<uint8_t, EPI_COMPLEX>(c, d_img, h, w, d.tw_h, -1.0, complex_out(d.a, hh, sums), s))
         return rc;
     if (int rc = launch_dft_pass<double2, EPI_POWER_NODC>(c, d.a, w, hh, d.tw_w, -1.0, real_out(pm, w, h), s))
         return rc;
     if (int rc = launch_dft_pass<double, EPI_COMPLEX>(c, pm, h, w, d.tw_h, 1.0, complex_out(d.a, hh), s))
         return rc;
-    if (int rc = launch_dft_pass<double2, EPI_ACF>(c, d.a, w, hh, d.tw_w, 1.0, real_out(d_acf, w, h, mom, n), s))
+    if (int rc = launch_dft_pass<double2, EPI_ACF>(c, d.a, w, hh, d.tw_w, 1.0, real_out(d_acf, w, h, sums), s))
         return rc;
     return diag_end(c, s);
 }
