@@ -73,7 +73,17 @@ struct SegPlan {
     uint32_t off[SEG_MAX + 1];   // tasks before segment s
     ChainState *state;           // a checkpoint per chain of the plan
 };
+// A message between the chain counts of two layouts, run in rounds of both (plan_mix).
+struct MixPlan {
+    uint32_t rounds;             // 0: no plan
+    int ga, gb;                  // lanes per chain of the two layouts
+    uint32_t unit, units;        // chains of a unit, units
+    uint32_t a;                  // units in ga lanes each round
+    uint32_t la, lb;             // bytes a round in ga and in gb lanes
+    ChainState *state;           // a checkpoint per chain
+};
 // Checkpoints of any plan on this many SIMDs: fewer than two waves per SIMD.
+ChainState *alloc_checkpoints(int simds);
 constexpr size_t seg_state_bytes(int simds) { return (size_t)simds * 2 * 64 * sizeof(ChainState); }
 
 // The two partial-block chains of a stream update, carried by a plain launch as the
@@ -126,19 +136,20 @@ constexpr int CU_SIMDS = 4;     // SIMDs of a compute unit
 constexpr size_t TAG_WORDS = 3, TAG_WIDE = 3;
 int lanes_per_chain(uint64_t chains, int m, uint32_t integ, int simds);
 SegPlan plan_segments(uint64_t chains, const uint32_t *lens, const lz_params &prm, int simds);
+MixPlan plan_mix(uint64_t chains, const lz_params &prm, int simds);
 
 // ---- kernel launchers (kernels.hip) --------------------------------------------------
 hipError_t launch_fill_u64(unsigned long long *p, size_t n, hipStream_t s);
 // Clears the tag accumulator (TAG_WORDS and the word after them) and runs the message, its last waves
-// by the segment plan if there is one.
+// by the segment plan or all of it by the mix plan if there is one.
 hipError_t launch_plain(const KernelShape &sh, const lz_key &key, const lz_params &prm, int decrypt,
                         const uint8_t *in, uint8_t *out, uint64_t n, unsigned long long *tag_acc, const SegPlan &plan,
-                        hipStream_t s);
+                        const MixPlan &mix, hipStream_t s);
 // One stream update: its full whole blocks from in / out at global block index
 // block_base, plus x's head and tail chains, in one launch of one chain per lane.
 hipError_t launch_stream_step(const KernelShape &shape, const lz_key &key, const lz_params &prm, int decrypt,
                               const uint8_t *in, uint8_t *out, uint64_t full, uint64_t block_base,
-                              const StreamExtra &x, unsigned long long *tag_acc, hipStream_t s);
+                              const StreamExtra &x, unsigned long long *tag_acc, const MixPlan &mix, hipStream_t s);
 hipError_t launch_plain_finalize(int decrypt, const unsigned long long *tag_acc, const uint8_t *stored_tag,
                                  uint8_t *tag_out, int32_t *status, uint8_t *body, uint64_t n,
                                  hipStream_t s);
@@ -228,7 +239,7 @@ struct lz_ctx {
     char arch[64];               // gcnArchName of the device
     double tuned_ms;             // last autotune: time of the winning shape's launch
     unsigned long long *ws_tag;  // plain path tag accumulator (TAG_WORDS + 1)
-    lz::ChainState *ws_seg;      // plain path segment checkpoints (seg_state_bytes, on first use)
+    lz::ChainState *ws_seg;      // plain path checkpoints between rounds (seg_state_bytes, on first use)
     int32_t *ws_status;          // plain path status (synchronous decrypt)
     int32_t *host_status;        // pinned
     hipStream_t last_stream;

@@ -770,16 +770,25 @@ __device__ __forceinline__ bool seg_task(const SegPlan &p, uint64_t first, uint3
 // Runs cnt bytes of the lane's chain from byte pos of its block of len bytes: from its start (pos = 0, c
 // initialised by the caller) or from `st`, to its end (then d holds the digest and the result is
 // true) or back to `st`.  A lane with cnt = 0 has nothing left to do.
+__device__ __forceinline__ void load_state(Chains<1> &c, const ChainState &s) {
+    c.x[0] = s.r[0]; c.y[0] = s.r[1]; c.z[0] = s.r[2];
+    c.a0[0] = s.al[0]; c.a1[0] = s.al[1]; c.a2[0] = s.al[2];
+    c.mu0[0] = s.mu[0]; c.mu1[0] = s.mu[1]; c.mu2[0] = s.mu[2];
+    c.om0[0] = s.om[0]; c.om1[0] = s.om[1]; c.om2[0] = s.om[2];
+}
+
+__device__ __forceinline__ void save_state(ChainState &s, const Chains<1> &c) {
+    s.r[0] = c.x[0]; s.r[1] = c.y[0]; s.r[2] = c.z[0];
+    s.al[0] = c.a0[0]; s.al[1] = c.a1[0]; s.al[2] = c.a2[0];
+    s.mu[0] = (uint8_t)c.mu0[0]; s.mu[1] = (uint8_t)c.mu1[0]; s.mu[2] = (uint8_t)c.mu2[0];
+    s.om[0] = (uint8_t)c.om0[0]; s.om[1] = (uint8_t)c.om1[0]; s.om[2] = (uint8_t)c.om2[0];
+}
+
 template <int I>
 __device__ __forceinline__ bool seg_run(Chains<1> &c, const WaveLds &w, uint32_t tile, const uint8_t *in, uint8_t *out,
                                         uint32_t pos, uint32_t cnt, uint32_t len, ChainState &st, double dt,
                                         uint32_t n_it, int lane, unsigned long long (&d)[3]) {
-    if (pos > 0 && cnt > 0) {
-        c.x[0] = st.r[0]; c.y[0] = st.r[1]; c.z[0] = st.r[2];
-        c.a0[0] = st.al[0]; c.a1[0] = st.al[1]; c.a2[0] = st.al[2];
-        c.mu0[0] = st.mu[0]; c.mu1[0] = st.mu[1]; c.mu2[0] = st.mu[2];
-        c.om0[0] = st.om[0]; c.om1[0] = st.om[1]; c.om2[0] = st.om[2];
-    }
+    if (pos > 0 && cnt > 0) load_state(c, st);
     const uint8_t *ins[1] = {in};
     uint8_t *outs[1] = {out};
     const uint32_t cnts[1] = {cnt};
@@ -790,10 +799,7 @@ __device__ __forceinline__ bool seg_run(Chains<1> &c, const WaveLds &w, uint32_t
             d[1] = digest_word(c.y[0]);
             d[2] = digest_word(c.z[0]);
         } else {
-            st.r[0] = c.x[0]; st.r[1] = c.y[0]; st.r[2] = c.z[0];
-            st.al[0] = c.a0[0]; st.al[1] = c.a1[0]; st.al[2] = c.a2[0];
-            st.mu[0] = (uint8_t)c.mu0[0]; st.mu[1] = (uint8_t)c.mu1[0]; st.mu[2] = (uint8_t)c.mu2[0];
-            st.om[0] = (uint8_t)c.om0[0]; st.om[1] = (uint8_t)c.om1[0]; st.om[2] = (uint8_t)c.om2[0];
+            save_state(st, c);
         }
     });
     return cnt > 0 && pos + cnt == len;
@@ -830,6 +836,104 @@ __global__ __launch_bounds__(256) void plain_seg_kernel(PlainArgs a, SegPlan p, 
         }
     }
     count_waves(-(int)(blockDim.x / WAVE));
+}
+
+// One round of a mix plan (see plan_mix): the chains of one unit, in GA lanes each (`first` = 0) or a quarter or
+// sixteenth of them in GB, advance by la or lb bytes.  Unit u has run n times in GA lanes before round r, n the
+// multiples u, u + U, ... below r A, so its position follows from r alone.
+template <int I, bool X, int G>
+__device__ __forceinline__ void mix_body(const PlainArgs &a, const MixPlan &p, uint32_t round, uint32_t unit,
+                                         uint32_t first, uint32_t step, char *lds) {
+    constexpr int ROWS = WAVE / G;
+    const int lane = threadIdx.x % WAVE;
+    const WaveLds w = wave_lds<ROWS>(lds + (size_t)(threadIdx.x / WAVE) * wave_lds_bytes(WAVE, a.tile), a.tile);
+    const uint32_t ra = round * p.a, n = ra > unit ? (ra - 1 - unit) / p.units + 1 : 0;
+    const uint32_t pos = n * p.la + (round - n) * p.lb;
+    const uint64_t g = (uint64_t)unit * p.unit + first + lane / G, off = g * a.block_len;
+    const uint32_t n_head = X && a.x.head_slot ? 1u : 0u;
+    const uint32_t role = !X || g < a.nb ? 0u : (g == a.nb && n_head ? 1u : (g == a.nb + n_head && a.x.tail_slot ? 2u : 0u));
+    uint32_t len = g < a.nb ? (uint32_t)(a.n - off < a.block_len ? a.n - off : a.block_len) : 0u;
+    const uint8_t *in = a.in + (g < a.nb ? off : 0);
+    uint8_t *out = a.out + (g < a.nb ? off : 0);
+    const double r0[3] = {a.r0[0], a.r0[1], a.r0[2]}, ap[3] = {a.ap[0], a.ap[1], a.ap[2]};
+    const uint8_t mu[3] = {a.mu[0], a.mu[1], a.mu[2]}, om[3] = {a.om[0], a.om[1], a.om[2]},
+                  k[3] = {a.k[0], a.k[1], a.k[2]};
+    uint64_t block = a.block_base + (g < a.nb ? g : 0);
+    if constexpr (X) {
+        if (role == 1) {
+            len = a.x.head_cnt;
+            in = a.x.head_in;
+            out = a.x.head_out;
+        } else if (role == 2) {
+            len = a.x.tail_cnt;
+            in = a.x.tail_in;
+            out = a.x.tail_out;
+            block = a.x.tail_block;
+        }
+    }
+    const uint32_t cnt = pos < len ? (len - pos < step ? len - pos : step) : 0u;
+    Chains<1> c;
+    init_chain<1>(c, 0, r0, ap, mu, om, k, block, a.decrypt);
+    if (cnt) {
+        in += pos;
+        out += pos;
+        if (pos > 0) load_state(c, p.state[g]);
+        else if (X && role == 1) load_slot(c, *a.x.head_slot, ap, k, a.decrypt);
+    }
+    bool done = false;
+    unsigned long long d0 = 0, d1 = 0, d2 = 0;
+    const uint8_t *ins[1] = {in};
+    uint8_t *outs[1] = {out};
+    const uint32_t cnts[1] = {cnt};
+    wave_run<1, I, G>(c, w, (int)a.tile, ins, outs, cnts, a.dt, a.n_it, lane, [&](int) __attribute__((always_inline)) {
+        if (cnt == 0) return;
+        if (pos + cnt != len) {
+            save_state(p.state[g], c);
+            return;
+        }
+        if constexpr (X) {
+            if (role == 2 || (role == 1 && !a.x.head_complete)) {
+                save_slot(role == 2 ? *a.x.tail_slot : *a.x.head_slot, c);
+                return;
+            }
+        }
+        done = lane % G == 0;
+        d0 = digest_word(c.x[0]);
+        d1 = digest_word(c.y[0]);
+        d2 = digest_word(c.z[0]);
+    });
+    if (__any(done)) {
+        const unsigned long long t0 = wave_xor_u64(done ? d0 : 0ull), t1 = wave_xor_u64(done ? d1 : 0ull),
+                                 t2 = wave_xor_u64(done ? d2 : 0ull);
+        if (lane == 0) {
+            atomicXor(&a.tag_acc[0], t0);
+            atomicXor(&a.tag_acc[1], t1);
+            atomicXor(&a.tag_acc[2], t2);
+        }
+    }
+}
+
+// Waves 0 .. p.a - 1 take the round's units in GA lanes, the others the rest of the units in GB, GB / GA waves a
+// unit.  Without room on the device (claim_kernel) the first round runs everything, one chain per lane.
+template <int I, bool X, int GA, int GB>
+__global__ __launch_bounds__(256) void mix_kernel(PlainArgs a, MixPlan p, uint32_t round) {
+    extern __shared__ char lds[];
+    const int waves = blockDim.x / WAVE;
+    if (*a.wide) {
+        if (round > 0) count_waves(waves);  // the first round's are claimed
+        constexpr uint32_t K = GB / GA;
+        const uint32_t v = __builtin_amdgcn_readfirstlane(blockIdx.x * waves + threadIdx.x / WAVE);
+        const uint32_t start = (round * p.a) % p.units;
+        if (v < p.a) {
+            mix_body<I, X, GA>(a, p, round, (start + v) % p.units, 0, p.la, lds);
+        } else if ((v - p.a) / K < p.units - p.a) {
+            mix_body<I, X, GB>(a, p, round, (start + p.a + (v - p.a) / K) % p.units, (v - p.a) % K * (WAVE / GB), p.lb, lds);
+        }
+        count_waves(-waves);
+    } else if (round == 0) {
+        plain_body<1, I, X, 1>(a, lds);
+        count_waves(-waves);
+    }
 }
 
 // Encrypt: tag bytes to out_tag.  Decrypt: compare with stored tag, status,
@@ -1306,6 +1410,58 @@ SegPlan plan_segments(uint64_t chains, const uint32_t *lens, const lz_params &pr
     return best;
 }
 
+// Clocks of a step with one wave per SIMD, g lanes per chain.
+static double step_clocks(uint32_t integ, int g) {
+    if (integ == LZ_INTEGRATOR_RK4) return g == 4 ? 190 : 262;
+    if (integ == LZ_INTEGRATOR_EULER_FMA) return g == 16 ? 32.6 : 36.6;
+    return g == 16 ? 40.6 : (g == 4 ? 44.6 : 56.6);
+}
+
+// Between the chain counts of two layouts (lanes_per_chain) the wider one does not fit and the narrower one leaves SIMDs
+// idle: 8 MB are half a wave per SIMD with a lane per chain.  A mix plan runs in rounds in which every SIMD has a wave:
+// of U units (a wave of chains in ga lanes each) A run in ga lanes and the rest in gb, gb / ga waves a unit, A
+// the least that makes them at most one wave per SIMD; the units take turns, so all advance alike.  A
+// round is la bytes in ga lanes and lb in gb, chosen to take the same time.  The plan with the least predicted time is
+// taken (a step's clocks as measured, MIX_ROUND_US for a round's launch, checkpoints and gap), if it beats one
+// launch in ga lanes by 3%.  Measured (with and without a plan): 4.1 MiB in
+// 15.1 and 18.5 ms, 6 MiB 16.5 and 18.5, 8 MiB 17.6 and 18.7, 1.3 MiB 13.8 and 14.6; RK4 at 5 MiB 70.3 and
+// 88.9; the fused map at 1.3 MiB 11.3 and 12.0.  From 10 MiB on the gain would be under 3%.
+MixPlan plan_mix(uint64_t chains, const lz_params &prm, int simds) {
+    constexpr double MIX_ROUND_US = 12.0, CLOCKS_PER_US = 2400.0;
+    MixPlan best{};
+    const int ga = lanes_per_chain(chains, 1, prm.integrator, simds);
+    const int gb = prm.integrator == LZ_INTEGRATOR_EULER ? 4 * ga : (prm.integrator == LZ_INTEGRATOR_RK4 ? 4 : 16);
+    if (ga >= gb || gb > 16 || chains * ga > (uint64_t)simds * WAVE) return best;
+    MixPlan p{};
+    p.ga = ga;
+    p.gb = gb;
+    p.unit = WAVE / ga;
+    p.units = (uint32_t)((chains + p.unit - 1) / p.unit);
+    const uint32_t K = gb / ga;
+    if (p.units * K <= (uint32_t)simds) return best;  // fits gb lanes (only with a partial unit)
+    p.a = (p.units * K - simds + K - 2) / (K - 1);
+    if (p.a >= p.units) return best;
+    const double ca = step_clocks(prm.integrator, ga), cb = step_clocks(prm.integrator, gb);
+    const double step_us = prm.n_it / CLOCKS_PER_US;
+    double best_us = 0.97 * prm.block_len * ca * step_us;
+    for (p.la = 6; p.la <= 32; ++p.la) {
+        p.lb = (uint32_t)(p.la * ca / cb * 1.004);
+        // the units with the most turns in ga lanes are the last to end
+        uint32_t r = prm.block_len / p.lb;
+        auto reached = [&](uint32_t rr) {
+            const uint32_t turns = (rr * p.a + p.units - 1) / p.units;
+            return turns * p.la + (rr - turns) * p.lb >= prm.block_len;
+        };
+        while (!reached(r)) ++r;
+        const double us = r * ((p.la * ca > p.lb * cb ? p.la * ca : p.lb * cb) * step_us + MIX_ROUND_US);
+        if (us >= best_us) continue;
+        best_us = us;
+        best = p;
+        best.rounds = r;
+    }
+    return best;
+}
+
 bool shape_valid(const KernelShape &sh, const DevInfo &dev) {
     if (sh.m != 1 && sh.m != 2 && sh.m != 4) return false;
     if (sh.wg != 64 && sh.wg != 128 && sh.wg != 256) return false;
@@ -1383,11 +1539,37 @@ int seg_tile(uint32_t seg_len, int most) {
     return tile;
 }
 
+// The rounds of a mix plan over a's chains; p, n: words to clear first (the tags of a whole message).
+template <bool X>
+hipError_t launch_mix(const KernelShape &shape, const PlainArgs &args, uint32_t integ, const MixPlan &plan,
+                      unsigned long long *p, size_t n, hipStream_t s) {
+    KernelShape sh = shape;
+    PlainArgs a = args;
+    sh.tile = seg_tile(plan.lb, sh.tile);
+    a.tile = (uint32_t)sh.tile;
+    const uint32_t waves = plan.a + (plan.units - plan.a) * (plan.gb / plan.ga), wpw = sh.wg / WAVE;
+    const unsigned grid = (waves + wpw - 1) / wpw;
+    hipError_t e = launch_claim(sh, grid, p, n, a.tag_acc + TAG_WIDE, s);
+    for (uint32_t r = 0; r < plan.rounds && e == hipSuccess; ++r) {
+        auto run = [&](auto ic, auto ac, auto bc) {
+            constexpr int I = decltype(ic)::value, GA = decltype(ac)::value, GB = decltype(bc)::value;
+            hipLaunchKernelGGL((mix_kernel<I, X, GA, GB>), dim3(grid), dim3(sh.wg), lds_bytes(sh), s, a, plan, r);
+            return hipGetLastError();
+        };
+        if (integ == LZ_INTEGRATOR_EULER && plan.ga == 1) e = run(Int<0>{}, Int<1>{}, Int<4>{});
+        else if (integ == LZ_INTEGRATOR_EULER) e = run(Int<0>{}, Int<4>{}, Int<16>{});
+        else if (integ == LZ_INTEGRATOR_EULER_FMA) e = run(Int<1>{}, Int<1>{}, Int<16>{});
+        else e = run(Int<2>{}, Int<1>{}, Int<4>{});
+    }
+    return e;
+}
+
 hipError_t launch_plain(const KernelShape &sh, const lz_key &key, const lz_params &prm, int decrypt,
                         const uint8_t *in, uint8_t *out, uint64_t n, unsigned long long *tag_acc, const SegPlan &plan,
-                        hipStream_t s) {
+                        const MixPlan &mix, hipStream_t s) {
     const uint64_t nb = n == 0 ? 1 : (n + prm.block_len - 1) / prm.block_len;
     PlainArgs a = plain_args(sh, key, prm, decrypt, in, out, n, nb, tag_acc, 0);
+    if (mix.rounds) return launch_mix<false>(sh, a, prm.integrator, mix, tag_acc, TAG_WORDS, s);
     if (plan.waves) a.nb = plan.chain0;
     const uint64_t grid = grid_of(sh, a.nb);
     hipError_t e = sh.g > 1 ? launch_claim(sh, grid, tag_acc, TAG_WORDS, tag_acc + TAG_WIDE, s)
@@ -1419,7 +1601,7 @@ hipError_t launch_plain(const KernelShape &sh, const lz_key &key, const lz_param
 
 hipError_t launch_stream_step(const KernelShape &shape, const lz_key &key, const lz_params &prm, int decrypt,
                               const uint8_t *in, uint8_t *out, uint64_t full, uint64_t block_base,
-                              const StreamExtra &x, unsigned long long *tag_acc, hipStream_t s) {
+                              const StreamExtra &x, unsigned long long *tag_acc, const MixPlan &mix, hipStream_t s) {
     const uint64_t lanes = full + (x.head_slot ? 1 : 0) + (x.tail_slot ? 1 : 0);
     if (lanes == 0) return hipSuccess;
     KernelShape sh{1, shape.wg, shape.tile, shape.wps};
@@ -1427,6 +1609,7 @@ hipError_t launch_stream_step(const KernelShape &shape, const lz_key &key, const
     sh.g = lanes_per_chain(lanes, 1, prm.integrator, sh.simds);
     PlainArgs a = plain_args(sh, key, prm, decrypt, in, out, full * prm.block_len, full, tag_acc, block_base);
     a.x = x;
+    if (mix.rounds) return launch_mix<true>(sh, a, prm.integrator, mix, nullptr, 0, s);
     const uint64_t grid = grid_of(sh, lanes);
     if (sh.g > 1) {
         const hipError_t e = launch_claim(sh, grid, nullptr, 0, tag_acc + TAG_WIDE, s);

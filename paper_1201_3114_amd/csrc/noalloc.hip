@@ -85,7 +85,7 @@ extern "C" int lz_decrypt_noalloc(const lz_params *prm, const uint8_t *pw, size_
 
     hipStream_t s = static_cast<hipStream_t>(stream);
     // the accumulator keeps the previous call's value: launch_plain clears it with a kernel (no memset node under capture)
-    LZ_HIP(launch_plain(sh, key, p, 1, d_C, d_P, n, d.ptr, SegPlan{}, s));
+    LZ_HIP(launch_plain(sh, key, p, 1, d_C, d_P, n, d.ptr, SegPlan{}, MixPlan{}, s));
     LZ_HIP(launch_plain_finalize(1, d.ptr, d_C + n, nullptr, d_status, d_P, n, s));
     return LZ_OK;
 }

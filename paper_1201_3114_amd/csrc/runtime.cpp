@@ -91,22 +91,20 @@ KernelShape plain_shape(const lz_ctx *c, uint64_t nb) {
     return sh;
 }
 
-// Segment plan of a message of nb blocks, with the context's checkpoints: allocated for the first message
-// that has a plan, also when it is being captured (no node comes of it, and the capture mode is set
-// aside for the allocation).  Without them the message runs without a plan.
-SegPlan plain_plan(lz_ctx *c, const KernelShape &sh, uint64_t nb) {
-    if (sh.m != 1 || sh.g != 1) return SegPlan{};
-    SegPlan plan = plan_segments(nb, nullptr, c->prm, sh.simds);
-    if (plan.waves && !c->ws_seg) {
-        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-        (void)hipThreadExchangeStreamCaptureMode(&mode);
-        void *p = nullptr;
-        if (hipMalloc(&p, seg_state_bytes(sh.simds)) == hipSuccess) c->ws_seg = static_cast<ChainState *>(p);
-        else (void)hipGetLastError();
-        (void)hipThreadExchangeStreamCaptureMode(&mode);
+// Segment or mix plan of a message of nb blocks, with the context's checkpoints, allocated for the first
+// message that has a plan.  Without them the message runs without one.
+void plain_plan(lz_ctx *c, const KernelShape &sh, uint64_t nb, SegPlan &seg, MixPlan &mix) {
+    seg = SegPlan{};
+    mix = MixPlan{};
+    if (sh.m != 1) return;
+    if (sh.g == 1) seg = plan_segments(nb, nullptr, c->prm, sh.simds);
+    mix = plan_mix(nb, c->prm, sh.simds);
+    if ((seg.waves || mix.rounds) && !c->ws_seg) c->ws_seg = alloc_checkpoints(sh.simds);
+    seg.state = mix.state = c->ws_seg;
+    if (!c->ws_seg) {
+        seg = SegPlan{};
+        mix = MixPlan{};
     }
-    plan.state = c->ws_seg;
-    return plan.state ? plan : SegPlan{};
 }
 
 // Orders a call on stream s after the previous call that used the same
@@ -124,6 +122,21 @@ int record(hipStream_t s, hipStream_t &last_stream, hipEvent_t ev, bool &has_las
 }
 
 }  // namespace
+
+// Checkpoints of any plan (seg_state_bytes), or NULL.  Also for a call that is being captured: no node comes of
+// the allocation, and the capture mode is set aside for it.
+ChainState *alloc_checkpoints(int simds) {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    void *p = nullptr;
+    if (hipMalloc(&p, seg_state_bytes(simds)) != hipSuccess) {
+        (void)hipGetLastError();
+        p = nullptr;
+    }
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    return static_cast<ChainState *>(p);
+}
+
 }  // namespace lz
 
 using namespace lz;
@@ -265,7 +278,10 @@ extern "C" int lz_encrypt_key(lz_ctx *c, const lz_key *key, const uint8_t *d_P, 
     LZ_HIP(hipSetDevice(c->device));
     if (int rc = order_after(s, c->last_stream, c->last_event, c->has_last)) return rc;
     const KernelShape sh = plain_shape(c, nb);
-    LZ_HIP(launch_plain(sh, *key, c->prm, 0, d_P, d_C, n, c->ws_tag, plain_plan(c, sh, nb), s));
+    SegPlan seg;
+    MixPlan mix;
+    plain_plan(c, sh, nb, seg, mix);
+    LZ_HIP(launch_plain(sh, *key, c->prm, 0, d_P, d_C, n, c->ws_tag, seg, mix, s));
     LZ_HIP(launch_plain_finalize(0, c->ws_tag, nullptr, d_C + n, nullptr, nullptr, n, s));
     return record(s, c->last_stream, c->last_event, c->has_last);
 }
@@ -283,7 +299,10 @@ extern "C" int lz_decrypt_key(lz_ctx *c, const lz_key *key, const uint8_t *d_C, 
     if (int rc = order_after(s, c->last_stream, c->last_event, c->has_last)) return rc;
     int32_t *st = d_status ? d_status : c->ws_status;
     const KernelShape sh = plain_shape(c, nb);
-    LZ_HIP(launch_plain(sh, *key, c->prm, 1, d_C, d_P, n, c->ws_tag, plain_plan(c, sh, nb), s));
+    SegPlan seg;
+    MixPlan mix;
+    plain_plan(c, sh, nb, seg, mix);
+    LZ_HIP(launch_plain(sh, *key, c->prm, 1, d_C, d_P, n, c->ws_tag, seg, mix, s));
     LZ_HIP(launch_plain_finalize(1, c->ws_tag, d_C + n, nullptr, st, d_P, n, s));
     if (d_status) return record(s, c->last_stream, c->last_event, c->has_last);
     LZ_HIP(hipMemcpyAsync(c->host_status, c->ws_status, sizeof(int32_t), hipMemcpyDeviceToHost, s));

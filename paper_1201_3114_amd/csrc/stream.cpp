@@ -48,6 +48,7 @@ struct lz_stream {
     };
     uint8_t *stage;      // input, then output
     uint64_t fill;       // staged bytes
+    ChainState *state;   // checkpoints of a mix plan (on first use)
     std::vector<Deferred> segs;
     std::vector<CopyPiece> pieces;  // the staged chunks' output copies, built at a flush
 };
@@ -60,6 +61,7 @@ void stream_free(lz_stream *st) {
     if (st->has_last) hipEventSynchronize(st->ev);
     if (st->dmem) hipFree(st->dmem);
     if (st->stage) hipFree(st->stage);
+    if (st->state) hipFree(st->state);
     if (st->h_status) hipHostFree(st->h_status);
     if (st->ev) hipEventDestroy(st->ev);
     delete st;
@@ -141,8 +143,13 @@ int stream_step(lz_stream *st, const uint8_t *d_in, size_t n, uint8_t *d_out, hi
     }
     KernelShape sh = c->shape;
     sh.simds = c->dev.cus * CU_SIMDS;
+    // an update between the chain counts of two layouts runs by a mix plan, from checkpoints of the stream's own
+    MixPlan mix = plan_mix(full + (h > 0) + (rem > 0), c->prm, sh.simds);
+    if (mix.rounds && !st->state) st->state = alloc_checkpoints(sh.simds);
+    mix.state = st->state;
+    if (!mix.state) mix = MixPlan{};
     LZ_HIP(launch_stream_step(sh, st->key, c->prm, st->decrypt, d_in + h, d_out + h, full, (pos0 + h) / B, x,
-                              st->tag, s));
+                              st->tag, mix, s));
     if (rem > 0) st->cur ^= 1;
     st->pos = pos0 + n;
     return LZ_OK;
