@@ -465,6 +465,11 @@ int lz_lag_sums(lz_ctx *ctx, const uint8_t *d_data, size_t n, uint32_t max_lag, 
  * entropy formula; S_max = 8).  Asynchronous on stream. */
 int lz_entropy(lz_ctx *ctx, const uint64_t *d_hist, double *d_S, void *stream);
 
+/* lz_entropy_value: the same into *S in host memory, waiting for it.  The
+ * kernel writes into a pinned word of the context, so no copy is launched;
+ * calls through one context from several threads take turns. */
+int lz_entropy_value(lz_ctx *ctx, const uint64_t *d_hist, double *S, void *stream);
+
 /* lz_autocorrelation: d_r (device, max_lag + 1 doubles, overwritten) receives
  * the autocorrelation coefficients of the mean-removed byte sequence d_data
  * (device, n bytes): r_k = sum_{i<n-k} (x_i - m)(x_{i+k} - m) / sum_i (x_i - m)^2,

@@ -101,6 +101,7 @@ SIGNATURES = {
     "lz_histogram": (ctypes.c_int, [vp, vp, ctypes.c_size_t, vp, vp]),
     "lz_lag_sums": (ctypes.c_int, [vp, vp, ctypes.c_size_t, ctypes.c_uint32, vp, vp]),
     "lz_entropy": (ctypes.c_int, [vp, vp, vp, vp]),
+    "lz_entropy_value": (ctypes.c_int, [vp, vp, ctypes.POINTER(ctypes.c_double), vp]),
     "lz_autocorrelation": (ctypes.c_int, [vp, vp, ctypes.c_size_t, ctypes.c_uint32, vp, vp]),
     "lz_power_spectrum_2d": (ctypes.c_int, [vp, vp, ctypes.c_uint32, ctypes.c_uint32, vp, vp]),
     "lz_autocorrelation_2d": (ctypes.c_int, [vp, vp, ctypes.c_uint32, ctypes.c_uint32, vp, vp]),

@@ -5,6 +5,7 @@
 
 #include <cstddef>
 #include <cstdint>
+#include <mutex>
 #include <string>
 
 #include "../../include/lorenz_cipher.h"
@@ -242,6 +243,8 @@ struct lz_ctx {
     lz::ChainState *ws_seg;      // plain path checkpoints between rounds (seg_state_bytes, on first use)
     int32_t *ws_status;          // plain path status (synchronous decrypt)
     int32_t *host_status;        // pinned
+    double *host_entropy;        // pinned, beside host_status (lz_entropy_value)
+    std::mutex entropy_mu;       // its users take turns
     hipStream_t last_stream;
     hipEvent_t last_event;
     bool has_last;
