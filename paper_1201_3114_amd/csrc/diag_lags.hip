@@ -53,6 +53,7 @@ constexpr uint32_t LS_MAX_NT = 9;               // lags up to 256
 // merge copies: workgroup b adds into copy b mod LS_COPIES (hundreds of workgroups add to each lag)
 constexpr uint32_t LS_COPIES = 32;
 static_assert((size_t)LS_COPIES * (32 * (LS_MAX_NT - 1) + 2) <= DIAG_MERGE_WORDS, "merge buffer too small");
+static_assert(32 * (LS_MAX_NT - 1) <= DIAG_WG && LS_COPIES <= 64, "a thread per lag, and a lane per copy");
 static_assert(LS_ROWS % 128 == 0 && LS_ROWS >= 128, "whole 32-row blocks for each of the four waves");
 static_assert((uint64_t)LS_FLUSH * LS_ROWS * 16384 < (1ull << 31), "32-bit accumulators");
 
@@ -86,9 +87,99 @@ __device__ inline uint4 ls_load16(const uint8_t *data, uint64_t n, uint64_t i0, 
     return make_uint4(w[0], w[1], w[2], w[3]);
 }
 
+// The coefficient r_k, k = 0..L, of a byte sequence x_0..x_{n-1} (n > 0) with mean m, from S_k, S_0 and the byte total T:
+//   r_k = sum_{i<n-k} (x_i - m)(x_{i+k} - m) / sum_i (x_i - m)^2
+//       = (S_k - m (A_k + B_k) + (n-k) m^2) / (S_0 - n m^2),
+// A_k = sum_{i<n-k} x_i = T - (sum of the last k bytes), B_k = sum_{i>=k} x_i = T - (sum of the first k bytes),
+// so A_k + B_k = 2T - pq with pq = P_k + Q_k = sum_{j<k} (x_j + x_{n-1-j}), an exact integer below 2^53.
+// NaN for one repeated byte (n S_0 = T^2 exactly then, and only then, compared in 128-bit integers), 0 for k >= n.
+__device__ inline double autocorr_r(uint64_t n, uint64_t k, unsigned long long sk, unsigned long long S0,
+                                    unsigned long long T, unsigned long long pq) {
+    if ((unsigned __int128)n * S0 == (unsigned __int128)T * T) return __builtin_nan("");
+    if (k == 0) return 1.0;
+    if (k >= n) return 0.0;
+    const double mean = (double)T / (double)n;
+    const double den = (double)S0 - (double)n * mean * mean;
+    return ((double)sk - mean * (double)(2 * T - pq) + (double)(n - k) * mean * mean) / den;
+}
+
+// r_k of an empty sequence
+__global__ __launch_bounds__(DIAG_WG) void autocorr_empty_kernel(double *r, uint32_t L) {
+    const uint32_t k = blockIdx.x * DIAG_WG + threadIdx.x;
+    if (k <= L) r[k] = __builtin_nan("");
+}
+
+// The correction for L <= 256: S_k and r_k, each where asked for, in one workgroup of DIAG_WG threads: thread t takes lag t + 1 (raw, the sum of the
+// workgroups' counts for it, and x = x_t + x_{n-1-t}, 0 past L or n), thread 0 also lag 0 and the byte total T.
+// P_k + Q_k comes from one scan of x (a wave scan by shuffles, then the wave totals through LDS).
+__device__ inline void lagsum_finish(uint64_t n, uint32_t L, unsigned long long raw, unsigned long long raw0,
+                                     unsigned long long T, uint32_t x, unsigned long long *sums, double *r) {
+    __shared__ uint32_t wsum[DIAG_WG / 64];
+    __shared__ unsigned long long s0t[2];
+    const uint32_t t = threadIdx.x, k = t + 1, lane = t % 64, wave = t / 64;
+    uint32_t inc = x;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t y = __shfl_up(inc, o, 64);
+        if ((int)lane >= o) inc += y;
+    }
+    if (lane == 63) wsum[wave] = inc;
+    if (t == 0) {
+        s0t[0] = raw0 - 16384ull * n;
+        s0t[1] = T;
+    }
+    __syncthreads();
+    unsigned long long pq = inc;  // P_k + Q_k: the bytes j < k of both ends
+#pragma unroll
+    for (uint32_t w = 0; w < DIAG_WG / 64; ++w) pq += w < wave ? wsum[w] : 0u;
+    const unsigned long long S0 = s0t[0];
+    T = s0t[1];
+    if (t == 0) {
+        if (sums) sums[0] = S0;
+        if (r) r[0] = autocorr_r(n, 0, S0, S0, T, 0);
+    }
+    if (k > L) return;
+    const unsigned long long sk = raw - 128ull * pq - 16384ull * (k < n ? n - k : 0);
+    if (sums) sums[k] = sk;
+    if (r) r[k] = autocorr_r(n, k, sk, S0, T, pq);
+}
+
+// x_t + x_{n-1-t}
+__device__ inline uint32_t both_ends(const uint8_t *data, uint64_t n, uint32_t L) {
+    const uint32_t t = threadIdx.x;
+    return t < L && t < n ? (uint32_t)data[t] + data[n - 1 - t] : 0u;
+}
+
+// The same from the merge copies (all loads issued before the first is used), which it clears.
+__global__ __launch_bounds__(DIAG_WG) void lagsum_merge_kernel(const uint8_t *data, uint64_t n, uint32_t L,
+                                                               unsigned long long *merge, unsigned long long *sums,
+                                                               double *r) {
+    const uint32_t t = threadIdx.x, k = t + 1, x = both_ends(data, n, L);
+    const size_t cs = (size_t)L + 2;  // copy stride: lags 0..L, then the byte total
+    unsigned long long part[LS_COPIES], raw = 0;
+#pragma unroll
+    for (uint32_t c = 0; c < LS_COPIES; ++c) part[c] = k <= L ? merge[c * cs + k] : 0ull;
+    unsigned long long raw0 = t < LS_COPIES ? merge[t * cs] : 0ull;
+    unsigned long long T = t < LS_COPIES ? merge[t * cs + L + 1] : 0ull;
+#pragma unroll
+    for (uint32_t c = 0; c < LS_COPIES; ++c) raw += part[c];
+    if (k <= L)
+#pragma unroll
+        for (uint32_t c = 0; c < LS_COPIES; ++c) merge[c * cs + k] = 0;
+    if (t < LS_COPIES) merge[t * cs] = merge[t * cs + L + 1] = 0;
+    for (int o = LS_COPIES / 2; o > 0; o >>= 1) {
+        raw0 += __shfl_down(raw0, o, 64);
+        T += __shfl_down(T, o, 64);
+    }
+    lagsum_finish(n, L, raw, raw0, T, x, sums, r);
+}
+
+// A launch of one workgroup (16 KiB) has its counters alone and applies the correction at once: 20.6 us a call and wait of
+// lz_autocorrelation at 256 lags, 24.6 with the second kernel.
 template <int NT>
 __global__ __launch_bounds__(DIAG_WG) __attribute__((amdgpu_waves_per_eu(2))) void lagsum_small_kernel(const uint8_t *data, uint64_t n, uint32_t L,
-                                                                unsigned long long *merge) {
+                                                                unsigned long long *merge, unsigned long long *sums,
+                                                                double *r) {
     static_assert(NT >= 1 && NT <= (int)LS_MAX_NT, "tiles");
     constexpr int F = NT / 4, S = NT % 4;  // tiles per wave over all rows; tiles shared out by rows
     __shared__ __align__(16) uint8_t lt[32 * LS_STRIDE];
@@ -280,6 +371,10 @@ __global__ __launch_bounds__(DIAG_WG) __attribute__((amdgpu_waves_per_eu(2))) vo
     __syncthreads();  // also: every wave's flush is done
     const unsigned long long tot =
         (unsigned long long)(wred[0] + wred[1] + wred[2] + wred[3]) + 128ull * nb;
+    if (gridDim.x == 1) {
+        lagsum_finish(n, L, t < L ? acc[t + 1] + 256ull * tot : 0ull, acc[0] + 256ull * tot, tot, both_ends(data, n, L), sums, r);
+        return;
+    }
     unsigned long long *copy = merge + (size_t)(blockIdx.x % LS_COPIES) * (L + 2);
     for (uint32_t k = t; k <= L; k += DIAG_WG) {
         const unsigned long long v = acc[k] + 256ull * tot;
@@ -463,86 +558,31 @@ __global__ __launch_bounds__(LW_WG) void lagsum_wide_kernel(const uint8_t *data,
     if (k_lo == 0 && t == 0 && tot) atomicAdd(&copy[L_all + 1], tot);
 }
 
-// The correction for L <= 256 (one window, one workgroup of LS_FIX_WG threads): thread k takes
-// lag k, sums its LS_COPIES merge copies (all loads issued before the first is used) and clears
-// them; the first and last L bytes are loaded at the same time, and P_k + Q_k comes from one scan
-// of x_j + x_{n-1-j} (a wave scan by shuffles, then the wave totals through LDS).  With r
-// non-null (n > 0) it also writes the normalised coefficients r_k, as autocorr_norm_kernel does
-// and in the same binary64 operations: A_k + B_k = 2T - (P_k + Q_k) is an exact integer below
-// 2^53, as is each of A_k and B_k there.
-constexpr int LS_FIX_WG = 512;
-static_assert(LS_FIX_WG > 32 * (LS_MAX_NT - 1) && LS_FIX_WG >= (int)LS_COPIES, "a thread per lag and per copy");
-__global__ __launch_bounds__(LS_FIX_WG) void lagsum_fix_small_kernel(const uint8_t *data, uint64_t n, uint32_t L,
-                                                                     unsigned long long *merge,
-                                                                     unsigned long long *sums,
-                                                                     unsigned long long *total, double *r) {
-    __shared__ uint32_t wsum[LS_FIX_WG / 64];
-    __shared__ unsigned long long tsum[LS_FIX_WG / 64];
-    __shared__ unsigned long long s0;
-    const uint32_t k = threadIdx.x, lane = k % 64, wave = k / 64;
-    const size_t cs = (size_t)L + 2;  // copy stride: lags 0..L, then the byte total
-    unsigned long long part[LS_COPIES];
-#pragma unroll
-    for (uint32_t c = 0; c < LS_COPIES; ++c) part[c] = k <= L ? merge[c * cs + k] : 0ull;
-    unsigned long long tc = k < LS_COPIES ? merge[k * cs + L + 1] : 0ull;
-    const uint32_t x = k < L && k < n ? (uint32_t)data[k] + data[n - 1 - k] : 0u;  // j = k < L <= 256
-    // inclusive scan of x over the block
-    uint32_t inc = x;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t y = __shfl_up(inc, o, 64);
-        if ((int)lane >= o) inc += y;
-    }
-    for (int o = 32; o > 0; o >>= 1) tc += __shfl_down(tc, o, 64);
-    if (lane == 63) wsum[wave] = inc;
-    if (lane == 0) tsum[wave] = tc;
-    __syncthreads();
-    uint32_t before = 0;
-#pragma unroll
-    for (uint32_t w = 0; w < LS_FIX_WG / 64; ++w) before += w < wave ? wsum[w] : 0u;
-    // P_k + Q_k: the bytes j < k of both ends
-    const unsigned long long pq = before + inc - x;
-    unsigned long long sk = 0;
-    if (k <= L) {
-        unsigned long long raw = 0;
-#pragma unroll
-        for (uint32_t c = 0; c < LS_COPIES; ++c) {
-            raw += part[c];
-            merge[c * cs + k] = 0;
-        }
-        const unsigned long long m = k < n ? n - k : 0;
-        sk = raw - 128ull * pq - 16384ull * m;
-        sums[k] = sk;
-        if (k == 0) s0 = sk;
-    }
-    if (k < LS_COPIES) merge[k * cs + L + 1] = 0;
-    unsigned long long T = 0;
-    for (uint32_t w = 0; w < LS_FIX_WG / 64; ++w) T += tsum[w];
-    if (k == 0 && total) *total = T;
-    if (!r) return;
-    __syncthreads();  // S_0
-    if (k > L) return;
-    const unsigned long long S0 = s0;
-    const double mean = (double)T / (double)n;
-    const double den = (double)S0 - (double)n * mean * mean;
-    // no coefficient when every byte is equal: n S_0 = T^2 exactly then, and only then
-    const bool constant = (unsigned __int128)n * S0 == (unsigned __int128)T * T;
-    double v;
-    if (constant) v = __builtin_nan("");
-    else if (k == 0) v = 1.0;
-    else if (k >= n) v = 0.0;
-    else v = ((double)sk - mean * (double)(2 * T - pq) + (double)(n - k) * mean * mean) / den;
-    r[k] = v;
-}
-
 // S_k = raw_k - 128 (P_k + Q_k) - 16384 max(n - k, 0) for k <= L, raw_k the sum of the merge
 // copies (cleared here for the next call), P_k and Q_k the sums of the first and the last min(k, n)
 // bytes.  Workgroup b takes lags kb = FIX_LAGS b .. kb + FIX_LAGS - 1, a lag per thread: it adds
 // up the first and the last min(kb, n) bytes (16-byte loads where aligned), then scans
 // x_j + x_{n-1-j} over its own lags (a wave scan by shuffles, the wave totals through LDS); every
-// load of a thread is issued before the first is used.  The first workgroup also writes the
-// byte total when asked for.
+// load of a thread is issued before the first is used.  Every workgroup also adds up lag 0 and the
+// byte total, which r_k needs and the last one clears.  It writes the sums and the normalised coefficients where asked for
+// (a kernel of its own for these, scanning the bytes again, took 3 us more a call).
 constexpr int FIX_LAGS = DIAG_WG;
+
+// True in the launch's last workgroup to come here; the word it is counted in, the merge buffer's last, is 0 again for
+// the next launch.  The others end: nothing waits.
+__device__ inline bool last_workgroup(unsigned long long *merge) {
+    __shared__ bool last;
+    unsigned long long *word = merge + DIAG_MERGE_WORDS;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        last = __hip_atomic_fetch_add(word, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1;
+        if (last) __hip_atomic_store(word, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __syncthreads();
+    return last;
+}
+
 
 // sum of data[lo, hi) over the block: each thread adds its 16-byte chunks and the unaligned ends
 __device__ inline unsigned long long fix_range_part(const uint8_t *data, uint64_t lo, uint64_t hi) {
@@ -574,16 +614,20 @@ __device__ inline unsigned long long fix_range_part(const uint8_t *data, uint64_
 
 __global__ __launch_bounds__(DIAG_WG) void lagsum_fix_kernel(const uint8_t *data, uint64_t n, uint32_t L,
                                                              unsigned long long *merge, unsigned long long *sums,
-                                                             unsigned long long *total) {
+                                                             double *r) {
     __shared__ unsigned long long wtot[DIAG_WG / 64];
     __shared__ uint32_t wscan[DIAG_WG / 64];
+    __shared__ unsigned long long s0t[2];
     const uint32_t t = threadIdx.x, lane = t % 64, wave = t / 64;
     const uint32_t kb = blockIdx.x * FIX_LAGS, k = kb + t;
     const size_t cs = (size_t)L + 2;  // copy stride: lags 0..L, then the byte total
-    unsigned long long part[DIAG_MERGE], tc = 0;
+    unsigned long long part[DIAG_MERGE], raw0 = 0, tc = 0;
 #pragma unroll
     for (int c = 0; c < DIAG_MERGE; ++c) part[c] = k <= L ? merge[c * cs + k] : 0ull;
-    if (blockIdx.x == 0 && t < DIAG_MERGE) tc = merge[t * cs + L + 1];
+    if (t < DIAG_MERGE) {
+        raw0 = merge[t * cs];
+        tc = merge[t * cs + L + 1];
+    }
     const uint32_t x = k < L && k < n ? (uint32_t)data[k] + data[n - 1 - k] : 0u;  // j = k, for the lags above k
     const uint64_t m = kb < n ? kb : n;
     unsigned long long base = fix_range_part(data, 0, m) + fix_range_part(data, n - m, n);
@@ -595,9 +639,16 @@ __global__ __launch_bounds__(DIAG_WG) void lagsum_fix_kernel(const uint8_t *data
         if ((int)lane >= o) inc += y;
     }
     for (int o = 32; o > 0; o >>= 1) base += __shfl_down(base, o, 64);
-    for (int o = 32; o > 0; o >>= 1) tc += __shfl_down(tc, o, 64);
+    for (int o = DIAG_MERGE / 2; o > 0; o >>= 1) {
+        raw0 += __shfl_down(raw0, o, 64);
+        tc += __shfl_down(tc, o, 64);
+    }
     if (lane == 63) wscan[wave] = inc;
     if (lane == 0) wtot[wave] = base;
+    if (t == 0) {
+        s0t[0] = raw0 - 16384ull * n;
+        s0t[1] = tc;
+    }
     __syncthreads();
     unsigned long long pq = 0;  // P_k + Q_k: the bytes j < k of both ends
 #pragma unroll
@@ -608,84 +659,23 @@ __global__ __launch_bounds__(DIAG_WG) void lagsum_fix_kernel(const uint8_t *data
 #pragma unroll
         for (int c = 0; c < DIAG_MERGE; ++c) {
             raw += part[c];
-            merge[c * cs + k] = 0;
+            if (k > 0) merge[c * cs + k] = 0;
         }
-        const unsigned long long mk = k < n ? n - k : 0;
-        sums[k] = raw - 128ull * pq - 16384ull * mk;
+        const unsigned long long mk = k < n ? n - k : 0, sk = raw - 128ull * pq - 16384ull * mk;
+        if (sums) sums[k] = sk;
+        if (r) r[k] = autocorr_r(n, k, sk, s0t[0], s0t[1], pq);
     }
-    if (blockIdx.x == 0) {
-        if (t < DIAG_MERGE) merge[t * cs + L + 1] = 0;
-        if (t == 0 && total) *total = tc;
-    }
+    // the words that every workgroup reads are cleared when all have read them
+    if (last_workgroup(merge) && t < DIAG_MERGE) merge[t * cs] = merge[t * cs + L + 1] = 0;
 }
 
-// ---- the normalised 1-D autocorrelation ---------------------------------------------------
-
-// r_k for k = 0..L of a byte sequence x_0..x_{n-1} with mean m:
-//   r_k = sum_{i<n-k} (x_i - m)(x_{i+k} - m) / sum_i (x_i - m)^2
-//       = (S_k - m (A_k + B_k) + (n-k) m^2) / (S_0 - n m^2),
-// A_k = sum_{i<n-k} x_i = T - (sum of the last k bytes), B_k = sum_{i>=k} x_i = T - (sum of the first k bytes),
-// so A_k + B_k = 2T - (P_k + Q_k) with P_k + Q_k = sum_{j<k} (x_j + x_{n-1-j}), an exact integer below 2^53.
-// One workgroup per 256 lags: workgroup b takes k = 256 b + 1 .. 256 b + 256 (and workgroup 0 also r_0):
-// the sum of x_j + x_{n-1-j} over j < 256 b (16-byte loads where aligned, a workgroup sum), then a
-// wave scan over its own 256 values of j.  NaN for no bytes or one repeated byte (n S_0 = T^2 exactly,
-// compared in 128-bit integers), 0 for k >= n.
-__global__ __launch_bounds__(DIAG_WG) void autocorr_norm_kernel(const uint8_t *data, uint64_t n, uint32_t L,
-                                                                 const unsigned long long *sums,
-                                                                 const unsigned long long *total, double *r) {
-    __shared__ unsigned long long red[DIAG_WG];
-    __shared__ uint32_t wsum[DIAG_WG / 64];
-    const uint32_t t = threadIdx.x, lane = t % 64, wave = t / 64;
-    const uint64_t kb = (uint64_t)blockIdx.x * DIAG_WG;
-    const unsigned long long T = *total;
-    const bool constant = n == 0 || (unsigned __int128)n * sums[0] == (unsigned __int128)T * T;
-    const uint64_t mb = kb < n ? kb : n;
-    const unsigned long long base =
-        block_sum<unsigned long long>(fix_range_part(data, 0, mb) + fix_range_part(data, n - mb, n), red);
-    const uint64_t j = kb + t;  // lag k = j + 1 includes byte j of both ends
-    const uint32_t x = j < n ? (uint32_t)data[j] + data[n - 1 - j] : 0u;
-    uint32_t inc = x;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t y = __shfl_up(inc, o, 64);
-        if ((int)lane >= o) inc += y;
-    }
-    if (lane == 63) wsum[wave] = inc;
-    __syncthreads();
-    uint32_t before = 0;
-    for (uint32_t w = 0; w < wave; ++w) before += wsum[w];
-    if (blockIdx.x == 0 && t == 0) r[0] = constant ? __builtin_nan("") : 1.0;
-    const uint64_t k = j + 1;
-    if (k > L) return;
-    double v;
-    if (constant) {
-        v = __builtin_nan("");
-    } else if (k >= n) {
-        v = 0.0;
-    } else {
-        const unsigned long long pq = base + before + inc;  // P_k + Q_k
-        const double mean = (double)T / (double)n;
-        const double den = (double)sums[0] - (double)n * mean * mean;
-        v = ((double)sums[k] - mean * (double)(2 * T - pq) + (double)(n - k) * mean * mean) / den;
-    }
-    r[k] = v;
-}
-
-// The lag sums into sums[0..max_lag]; with total non-null, also the byte total into *total.
-// ordered: the caller has already ordered this stream after the context's other diagnostics
-// (diag_begin) and records the event afterwards itself.
-// r: when the lags fit one launch (and n > 0), the normalised coefficients are written too and
-// *normalised is set.
-int lag_sums(lz_ctx *c, const uint8_t *d_data, size_t n, uint32_t max_lag, unsigned long long *sums,
-             unsigned long long *total, hipStream_t s, bool ordered = false, double *r = nullptr,
-             bool *normalised = nullptr) {
-    if (normalised) *normalised = false;
+// The lag sums into sums[0..max_lag] and the normalised coefficients into r[0..max_lag], each unless NULL.
+int lag_sums(lz_ctx *c, const uint8_t *d_data, size_t n, uint32_t max_lag, unsigned long long *sums, double *r,
+             hipStream_t s) {
     if (n > 0) {
-        // the workgroups' sums meet in the context's merge copies, which the correction kernel adds
-        // up, writes to d_sums and clears: calls on different streams are ordered
+        // the workgroups' sums meet in the context's merge copies: calls on different streams are ordered
         char *ws;
-        if (!ordered)
-            if (int rc = diag_begin(c, s, 0, &ws)) return rc;
+        if (int rc = diag_begin(c, s, 0, &ws)) return rc;
         // resident workgroups only, as many tasks each (rounds = tasks / slots, rounded up)
         auto grid = [&](const void *kern, int wg, uint64_t tasks, unsigned *blocks) -> int {
             int per_cu = 0;
@@ -699,18 +689,19 @@ int lag_sums(lz_ctx *c, const uint8_t *d_data, size_t n, uint32_t max_lag, unsig
         unsigned blocks = 0;
         if (max_lag <= 32 * (LS_MAX_NT - 1)) {  // up to 256 lags: one launch
             const uint32_t nt = (max_lag + 31) / 32 + 1;
-            void (*kern)(const uint8_t *, uint64_t, uint32_t, unsigned long long *) =
+            void (*kern)(const uint8_t *, uint64_t, uint32_t, unsigned long long *, unsigned long long *, double *) =
                 nt == 1 ? lagsum_small_kernel<1> : nt == 2 ? lagsum_small_kernel<2> : nt == 3 ? lagsum_small_kernel<3>
                 : nt == 4 ? lagsum_small_kernel<4> : nt == 5 ? lagsum_small_kernel<5> : nt == 6 ? lagsum_small_kernel<6>
                 : nt == 7 ? lagsum_small_kernel<7> : nt == 8 ? lagsum_small_kernel<8> : lagsum_small_kernel<9>;
             if (int rc = grid(reinterpret_cast<const void *>(kern), DIAG_WG, ((n + 31) / 32 + LS_ROWS - 1) / LS_ROWS, &blocks))
                 return rc;
-            hipLaunchKernelGGL(kern, dim3(blocks), dim3(DIAG_WG), 0, s, d_data, (uint64_t)n, max_lag, c->diag_merge);
-            hipLaunchKernelGGL(lagsum_fix_small_kernel, dim3(1), dim3(LS_FIX_WG), 0, s, d_data, (uint64_t)n, max_lag,
-                               c->diag_merge, sums, total, r);
+            hipLaunchKernelGGL(kern, dim3(blocks), dim3(DIAG_WG), 0, s, d_data, (uint64_t)n, max_lag, c->diag_merge,
+                               sums, r);
+            if (blocks > 1)
+                hipLaunchKernelGGL(lagsum_merge_kernel, dim3(1), dim3(DIAG_WG), 0, s, d_data, (uint64_t)n, max_lag,
+                                   c->diag_merge, sums, r);
             LZ_HIP(hipGetLastError());
-            if (normalised) *normalised = r != nullptr;
-            return ordered ? LZ_OK : diag_end(c, s);
+            return diag_end(c, s);
         }
         // windows of at most LW_WINDOW lags, as even as 32-lag steps allow, one launch each
         const uint64_t lags = (uint64_t)max_lag + 1, nwin = (lags + LW_WINDOW - 1) / LW_WINDOW;
@@ -724,12 +715,12 @@ int lag_sums(lz_ctx *c, const uint8_t *d_data, size_t n, uint32_t max_lag, unsig
                                max_lag, c->diag_merge);
         }
         hipLaunchKernelGGL(lagsum_fix_kernel, dim3(max_lag / FIX_LAGS + 1), dim3(DIAG_WG), 0, s, d_data,
-                           (uint64_t)n, max_lag, c->diag_merge, sums, total);
+                           (uint64_t)n, max_lag, c->diag_merge, sums, r);
         LZ_HIP(hipGetLastError());
-        return ordered ? LZ_OK : diag_end(c, s);
+        return diag_end(c, s);
     }
-    LZ_HIP(launch_fill_u64(sums, (size_t)max_lag + 1, s));  // n == 0: every sum is 0
-    if (total) LZ_HIP(launch_fill_u64(total, 1, s));
+    if (sums) LZ_HIP(launch_fill_u64(sums, (size_t)max_lag + 1, s));  // n == 0: every sum is 0
+    if (r) hipLaunchKernelGGL(autocorr_empty_kernel, dim3(max_lag / DIAG_WG + 1), dim3(DIAG_WG), 0, s, r, max_lag);
     LZ_HIP(hipGetLastError());
     return LZ_OK;
 }
@@ -744,25 +735,13 @@ extern "C" int lz_lag_sums(lz_ctx *c, const uint8_t *d_data, size_t n, uint32_t 
     if (!c || !d_sums || (!d_data && n)) return fail(LZ_E_INVAL, "NULL argument");
     if (max_lag > 16384) return fail(LZ_E_INVAL, "max_lag must be <= 16384");
     LZ_HIP(hipSetDevice(c->device));
-    return lag_sums(c, d_data, n, max_lag, reinterpret_cast<unsigned long long *>(d_sums), nullptr,
-                    (hipStream_t)stream);
+    return lag_sums(c, d_data, n, max_lag, reinterpret_cast<unsigned long long *>(d_sums), nullptr, (hipStream_t)stream);
 }
 
 extern "C" int lz_autocorrelation(lz_ctx *c, const uint8_t *d_data, size_t n, uint32_t max_lag, double *d_r,
                                   void *stream) {
     if (!c || !d_r || (!d_data && n)) return fail(LZ_E_INVAL, "NULL argument");
     if (max_lag > 16384) return fail(LZ_E_INVAL, "max_lag must be <= 16384");
-    hipStream_t s = (hipStream_t)stream;
     LZ_HIP(hipSetDevice(c->device));
-    char *ws;
-    if (int rc = diag_begin(c, s, 8 + ((size_t)max_lag + 1) * 8, &ws)) return rc;
-    unsigned long long *total = reinterpret_cast<unsigned long long *>(ws);
-    unsigned long long *sums = total + 1;
-    bool normalised = false;
-    if (int rc = lag_sums(c, d_data, n, max_lag, sums, total, s, true, d_r, &normalised)) return rc;
-    if (!normalised)
-        hipLaunchKernelGGL(autocorr_norm_kernel, dim3(max_lag > 0 ? (max_lag + DIAG_WG - 1) / DIAG_WG : 1),
-                           dim3(DIAG_WG), 0, s, d_data, (uint64_t)n, max_lag, sums, total, d_r);
-    LZ_HIP(hipGetLastError());
-    return diag_end(c, s);
+    return lag_sums(c, d_data, n, max_lag, nullptr, d_r, (hipStream_t)stream);
 }

@@ -207,7 +207,7 @@ inline void add_copy_pieces(CopyPiece *arr, uint32_t &n, const void *src, void *
     }
 }
 // diagnostics merge buffer: workgroup b of the histogram and of the lag sums adds its partial
-// results into copy b mod DIAG_MERGE; the one-workgroup kernel that follows sums and clears them
+// results into copy b mod DIAG_MERGE; the kernel that follows sums and clears them
 constexpr int DIAG_MERGE = 8;
 constexpr size_t DIAG_MERGE_WORDS = (size_t)DIAG_MERGE * 16386;  // 64-bit: 256 bins, or up to 16385 lags + the byte total, a copy
 hipError_t launch_copy_many(const CopyPiece *pieces, uint32_t n, hipStream_t s);
@@ -248,7 +248,7 @@ struct lz_ctx {
     hipStream_t last_stream;
     hipEvent_t last_event;
     bool has_last;
-    // diagnostics merge buffer (DIAG_MERGE_WORDS), zero between calls: each call's last kernel clears it
+    // diagnostics merge buffer (DIAG_MERGE_WORDS and the word of last_workgroup), zero between calls: each call clears it
     unsigned long long *diag_merge;
     // diagnostics workspace (grown on demand) and the event that orders its users
     void *diag_ws;

@@ -218,8 +218,8 @@ extern "C" int lz_context_create(int device, const lz_params *prm, lz_ctx **out)
     if (e == hipSuccess) c->host_entropy = reinterpret_cast<double *>(c->host_status) + 1;
     if (e == hipSuccess) e = hipEventCreateWithFlags(&c->last_event, hipEventDisableTiming);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&c->diag_event, hipEventDisableTiming);
-    if (e == hipSuccess) e = hipMalloc(&c->diag_merge, DIAG_MERGE_WORDS * 8);
-    if (e == hipSuccess) e = hipMemset(c->diag_merge, 0, DIAG_MERGE_WORDS * 8);
+    if (e == hipSuccess) e = hipMalloc(&c->diag_merge, (DIAG_MERGE_WORDS + 1) * 8);
+    if (e == hipSuccess) e = hipMemset(c->diag_merge, 0, (DIAG_MERGE_WORDS + 1) * 8);
     if (e != hipSuccess) {
         int rc = hip_fail(e, "context allocation");
         lz_context_destroy(c);
