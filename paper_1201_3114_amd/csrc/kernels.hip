@@ -1444,7 +1444,9 @@ MixPlan plan_mix(uint64_t chains, const lz_params &prm, int simds) {
     const double ca = step_clocks(prm.integrator, ga), cb = step_clocks(prm.integrator, gb);
     const double step_us = prm.n_it / CLOCKS_PER_US;
     double best_us = 0.97 * prm.block_len * ca * step_us;
-    for (p.la = 6; p.la <= 32; ++p.la) {
+    // 6 to 32 bytes of the default block of 256, and as many rounds of a longer one
+    const uint32_t unit_bytes = prm.block_len > 256 ? prm.block_len / 256 : 1;
+    for (p.la = 6 * unit_bytes; p.la <= 32 * unit_bytes; p.la += unit_bytes) {
         p.lb = (uint32_t)(p.la * ca / cb * 1.004);
         // the units with the most turns in ga lanes are the last to end
         uint32_t r = prm.block_len / p.lb;

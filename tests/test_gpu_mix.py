@@ -104,3 +104,16 @@ def test_no_room_and_capture(lz, integ, per):
         g.replay()
         assert np.array_equal(host(C), want), k
         assert np.array_equal(host(ctx.encrypt(dP, b"mix")), want), k
+
+
+@pytest.mark.parametrize("per,block", [(5, 4096), (20, 1000), (4, 300)])
+def test_long_blocks(lz, per, block):
+    """Rounds of more bytes, as many as of a default block."""
+    rng = np.random.default_rng(block)
+    n = (per * simds() + 3) * block - 77
+    prm = dict(n_it=40, block_len=block)
+    ctx = lz.Context(0, lz.params(**prm))
+    P = rng.integers(0, 256, n, dtype=np.uint8)
+    C = ctx.encrypt(to_dev(P), b"mix")
+    assert np.array_equal(host(C), oracle.encrypt(b"mix", P, nthreads=ORACLE_THREADS, **prm))
+    assert np.array_equal(host(ctx.decrypt(C, b"mix")), P)
