@@ -74,7 +74,7 @@ struct SegPlan {
     uint32_t off[SEG_MAX + 1];   // tasks before segment s
     ChainState *state;           // a checkpoint per chain of the plan
 };
-// A message between the chain counts of two layouts, run in rounds of both (plan_mix).
+// A message or batch between the chain counts of two layouts, run in rounds of both (plan_mix).
 struct MixPlan {
     uint32_t rounds;             // 0: no plan
     int ga, gb;                  // lanes per chain of the two layouts
@@ -170,7 +170,7 @@ struct BatchDev {
 };
 // Clears the tags and the counter and runs the batch.
 hipError_t launch_batch(const KernelShape &sh, const DevInfo &dev, const lz_params &prm, const BatchDev &b,
-                        const SegPlan &plan, hipStream_t s);
+                        const SegPlan &plan, const MixPlan &mix, hipStream_t s);
 hipError_t launch_batch_finalize(const BatchDev &b, int decrypt, hipStream_t s);
 // One-thread kernel: *slot = status (ordered on s before a batch replay that reads the slot).
 hipError_t launch_set_status_ref(int32_t **slot, int32_t *status, hipStream_t s);

@@ -767,9 +767,9 @@ __device__ __forceinline__ bool seg_task(const SegPlan &p, uint64_t first, uint3
     return true;
 }
 
-// Runs cnt bytes of the lane's chain from byte pos of its block of len bytes: from its start (pos = 0, c
-// initialised by the caller) or from `st`, to its end (then d holds the digest and the result is
-// true) or back to `st`.  A lane with cnt = 0 has nothing left to do.
+// Runs cnt bytes of the lanes' chain from byte pos of its block of len bytes: from its start (pos = 0, c
+// initialised by the caller) or from `st`, to its end (then d holds the digest and the result is true in
+// the chain's first lane) or back to `st`.  A lane with cnt = 0 has nothing left to do.
 __device__ __forceinline__ void load_state(Chains<1> &c, const ChainState &s) {
     c.x[0] = s.r[0]; c.y[0] = s.r[1]; c.z[0] = s.r[2];
     c.a0[0] = s.al[0]; c.a1[0] = s.al[1]; c.a2[0] = s.al[2];
@@ -784,7 +784,7 @@ __device__ __forceinline__ void save_state(ChainState &s, const Chains<1> &c) {
     s.om[0] = (uint8_t)c.om0[0]; s.om[1] = (uint8_t)c.om1[0]; s.om[2] = (uint8_t)c.om2[0];
 }
 
-template <int I>
+template <int I, int G = 1>
 __device__ __forceinline__ bool seg_run(Chains<1> &c, const WaveLds &w, uint32_t tile, const uint8_t *in, uint8_t *out,
                                         uint32_t pos, uint32_t cnt, uint32_t len, ChainState &st, double dt,
                                         uint32_t n_it, int lane, unsigned long long (&d)[3]) {
@@ -792,7 +792,7 @@ __device__ __forceinline__ bool seg_run(Chains<1> &c, const WaveLds &w, uint32_t
     const uint8_t *ins[1] = {in};
     uint8_t *outs[1] = {out};
     const uint32_t cnts[1] = {cnt};
-    wave_run<1, I, 1>(c, w, (int)tile, ins, outs, cnts, dt, n_it, lane, [&](int) __attribute__((always_inline)) {
+    wave_run<1, I, G>(c, w, (int)tile, ins, outs, cnts, dt, n_it, lane, [&](int) __attribute__((always_inline)) {
         if (cnt == 0) return;
         if (pos + cnt == len) {
             d[0] = digest_word(c.x[0]);
@@ -802,7 +802,7 @@ __device__ __forceinline__ bool seg_run(Chains<1> &c, const WaveLds &w, uint32_t
             save_state(st, c);
         }
     });
-    return cnt > 0 && pos + cnt == len;
+    return cnt > 0 && pos + cnt == len && lane % G == 0;
 }
 
 template <int I>
@@ -838,17 +838,22 @@ __global__ __launch_bounds__(256) void plain_seg_kernel(PlainArgs a, SegPlan p, 
     count_waves(-(int)(blockDim.x / WAVE));
 }
 
-// One round of a mix plan (see plan_mix): the chains of one unit, in GA lanes each (`first` = 0) or a quarter or
-// sixteenth of them in GB, advance by la or lb bytes.  Unit u has run n times in GA lanes before round r, n the
+// The byte that a unit of a mix plan starts a round at: it has run n times in GA lanes before round r, n the
 // multiples u, u + U, ... below r A, so its position follows from r alone.
+__device__ __forceinline__ uint32_t mix_pos(const MixPlan &p, uint32_t round, uint32_t unit) {
+    const uint32_t ra = round * p.a, n = ra > unit ? (ra - 1 - unit) / p.units + 1 : 0;
+    return n * p.la + (round - n) * p.lb;
+}
+
+// One round of a mix plan (see plan_mix): the chains of one unit, in GA lanes each (`first` = 0) or a quarter or
+// sixteenth of them in GB, advance by la or lb bytes.
 template <int I, bool X, int G>
 __device__ __forceinline__ void mix_body(const PlainArgs &a, const MixPlan &p, uint32_t round, uint32_t unit,
                                          uint32_t first, uint32_t step, char *lds) {
     constexpr int ROWS = WAVE / G;
     const int lane = threadIdx.x % WAVE;
     const WaveLds w = wave_lds<ROWS>(lds + (size_t)(threadIdx.x / WAVE) * wave_lds_bytes(WAVE, a.tile), a.tile);
-    const uint32_t ra = round * p.a, n = ra > unit ? (ra - 1 - unit) / p.units + 1 : 0;
-    const uint32_t pos = n * p.la + (round - n) * p.lb;
+    const uint32_t pos = mix_pos(p, round, unit);
     const uint64_t g = (uint64_t)unit * p.unit + first + lane / G, off = g * a.block_len;
     const uint32_t n_head = X && a.x.head_slot ? 1u : 0u;
     const uint32_t role = !X || g < a.nb ? 0u : (g == a.nb && n_head ? 1u : (g == a.nb + n_head && a.x.tail_slot ? 2u : 0u));
@@ -914,26 +919,37 @@ __device__ __forceinline__ void mix_body(const PlainArgs &a, const MixPlan &p, u
 }
 
 // Waves 0 .. p.a - 1 take the round's units in GA lanes, the others the rest of the units in GB, GB / GA waves a
-// unit.  Without room on the device (claim_kernel) the first round runs everything, one chain per lane.
-template <int I, bool X, int GA, int GB>
-__global__ __launch_bounds__(256) void mix_kernel(PlainArgs a, MixPlan p, uint32_t round) {
-    extern __shared__ char lds[];
+// unit: body(lanes, unit, first chain of the unit, bytes).  Without room on the device (claim_kernel) the first round
+// runs everything, one chain per lane: all().
+template <int GA, int GB, class Body, class All>
+__device__ __forceinline__ void mix_round(const MixPlan &p, uint32_t round, uint32_t wide, Body &&body, All &&all) {
     const int waves = blockDim.x / WAVE;
-    if (*a.wide) {
+    if (wide) {
         if (round > 0) count_waves(waves);  // the first round's are claimed
         constexpr uint32_t K = GB / GA;
         const uint32_t v = __builtin_amdgcn_readfirstlane(blockIdx.x * waves + threadIdx.x / WAVE);
         const uint32_t start = (round * p.a) % p.units;
         if (v < p.a) {
-            mix_body<I, X, GA>(a, p, round, (start + v) % p.units, 0, p.la, lds);
+            body(std::integral_constant<int, GA>{}, (start + v) % p.units, 0u, p.la);
         } else if ((v - p.a) / K < p.units - p.a) {
-            mix_body<I, X, GB>(a, p, round, (start + p.a + (v - p.a) / K) % p.units, (v - p.a) % K * (WAVE / GB), p.lb, lds);
+            body(std::integral_constant<int, GB>{}, (start + p.a + (v - p.a) / K) % p.units, (v - p.a) % K * (WAVE / GB), p.lb);
         }
         count_waves(-waves);
     } else if (round == 0) {
-        plain_body<1, I, X, 1>(a, lds);
+        all();
         count_waves(-waves);
     }
+}
+
+template <int I, bool X, int GA, int GB>
+__global__ __launch_bounds__(256) void mix_kernel(PlainArgs a, MixPlan p, uint32_t round) {
+    extern __shared__ char lds[];
+    mix_round<GA, GB>(
+        p, round, *a.wide,
+        [&](auto g, uint32_t unit, uint32_t first, uint32_t step) __attribute__((always_inline)) {
+            mix_body<I, X, decltype(g)::value>(a, p, round, unit, first, step, lds);
+        },
+        [&]() __attribute__((always_inline)) { plain_body<1, I, X, 1>(a, lds); });
 }
 
 // Encrypt: tag bytes to out_tag.  Decrypt: compare with stored tag, status,
@@ -1105,6 +1121,49 @@ __global__ __launch_bounds__(256) void batch_seg_kernel(BatchArgs a, SegPlan p, 
         }
     }
     count_waves(-(int)(blockDim.x / WAVE));
+}
+
+// One round of the batch's mix plan: mix_body over its chains.
+template <int I, int G>
+__device__ __forceinline__ void batch_mix_body(const BatchArgs &a, const MixPlan &p, uint32_t round, uint32_t unit,
+                                               uint32_t first, uint32_t step, char *lds) {
+    constexpr int ROWS = WAVE / G;
+    const int lane = threadIdx.x % WAVE;
+    const WaveLds w = wave_lds<ROWS>(lds + (size_t)(threadIdx.x / WAVE) * wave_lds_bytes(WAVE, a.tile), a.tile);
+    const uint32_t pos = mix_pos(p, round, unit);
+    const uint64_t g = (uint64_t)unit * p.unit + first + lane / G;
+    uint32_t i = 0, len = 0;
+    uint64_t b = 0;
+    const bool valid = g < a.n_chains;
+    if (valid) batch_chain(a, g, i, b, len);
+    const MsgDesc &md = a.b.msgs[i];
+    const uint32_t cnt = pos < len ? (len - pos < step ? len - pos : step) : 0u;
+    const uint64_t at = cnt ? b * a.block_len + pos : 0;
+    Chains<1> c;
+    const double r0[3] = {md.r0[0], md.r0[1], md.r0[2]}, ap[3] = {md.ap[0], md.ap[1], md.ap[2]};
+    const uint8_t mu[3] = {md.mu[0], md.mu[1], md.mu[2]}, om[3] = {md.om[0], md.om[1], md.om[2]},
+                  k[3] = {md.k[0], md.k[1], md.k[2]};
+    init_chain<1>(c, 0, r0, ap, mu, om, k, b, md.decrypt);
+    unsigned long long d[3] = {digest_word(c.x[0]), digest_word(c.y[0]), digest_word(c.z[0])};  // an empty message's
+    bool done = seg_run<I, G>(c, w, a.tile, md.in + at, md.out + at, pos, cnt, len, p.state[g], a.dt, a.n_it, lane, d);
+    done = done || (valid && len == 0 && round == 0 && lane % G == 0);
+    if (done) {
+        unsigned long long *t = &a.b.tag_acc[3 * (size_t)i];
+        atomicXor(t + 0, d[0]);
+        atomicXor(t + 1, d[1]);
+        atomicXor(t + 2, d[2]);
+    }
+}
+
+template <int I, int GA, int GB>
+__global__ __launch_bounds__(256) void batch_mix_kernel(BatchArgs a, MixPlan p, uint32_t round) {
+    extern __shared__ char lds[];
+    mix_round<GA, GB>(
+        p, round, *a.b.wide,
+        [&](auto g, uint32_t unit, uint32_t first, uint32_t step) __attribute__((always_inline)) {
+            batch_mix_body<I, decltype(g)::value>(a, p, round, unit, first, step, lds);
+        },
+        [&]() __attribute__((always_inline)) { batch_body<1, I, 1>(a, lds); });
 }
 
 // One workgroup per message: tag out (encrypt) or tag check, status and zeroing (decrypt).
@@ -1425,7 +1484,8 @@ static double step_clocks(uint32_t integ, int g) {
 // taken (a step's clocks as measured, MIX_ROUND_US for a round's launch, checkpoints and gap), if it beats one
 // launch in ga lanes by 3%.  Measured (with and without a plan): 4.1 MiB in
 // 15.1 and 18.5 ms, 6 MiB 16.5 and 18.5, 8 MiB 17.6 and 18.7, 1.3 MiB 13.8 and 14.6; RK4 at 5 MiB 70.3 and
-// 88.9; the fused map at 1.3 MiB 11.3 and 12.0.  From 10 MiB on the gain would be under 3%.
+// 88.9; the fused map at 1.3 MiB 11.3 and 12.0; batches of 5.2 MiB 16.1 and 18.5, 7.7 MiB 17.7 and 18.6.  From 10 MiB on
+// the gain would be under 3%.
 MixPlan plan_mix(uint64_t chains, const lz_params &prm, int simds) {
     constexpr double MIX_ROUND_US = 12.0, CLOCKS_PER_US = 2400.0;
     MixPlan best{};
@@ -1541,21 +1601,19 @@ int seg_tile(uint32_t seg_len, int most) {
     return tile;
 }
 
-// The rounds of a mix plan over a's chains; p, n: words to clear first (the tags of a whole message).
-template <bool X>
-hipError_t launch_mix(const KernelShape &shape, const PlainArgs &args, uint32_t integ, const MixPlan &plan,
-                      unsigned long long *p, size_t n, hipStream_t s) {
+// The rounds of a mix plan, each launched by launch(integrator, lanes, lanes, shape, grid, round); p, n: words to
+// clear first (the tags of whole messages).
+template <class Launch>
+hipError_t mix_rounds(const KernelShape &shape, uint32_t integ, const MixPlan &plan, unsigned long long *p, size_t n,
+                      unsigned long long *wide, hipStream_t s, Launch &&launch) {
     KernelShape sh = shape;
-    PlainArgs a = args;
     sh.tile = seg_tile(plan.lb, sh.tile);
-    a.tile = (uint32_t)sh.tile;
     const uint32_t waves = plan.a + (plan.units - plan.a) * (plan.gb / plan.ga), wpw = sh.wg / WAVE;
     const unsigned grid = (waves + wpw - 1) / wpw;
-    hipError_t e = launch_claim(sh, grid, p, n, a.tag_acc + TAG_WIDE, s);
+    hipError_t e = launch_claim(sh, grid, p, n, wide, s);
     for (uint32_t r = 0; r < plan.rounds && e == hipSuccess; ++r) {
         auto run = [&](auto ic, auto ac, auto bc) {
-            constexpr int I = decltype(ic)::value, GA = decltype(ac)::value, GB = decltype(bc)::value;
-            hipLaunchKernelGGL((mix_kernel<I, X, GA, GB>), dim3(grid), dim3(sh.wg), lds_bytes(sh), s, a, plan, r);
+            launch(ic, ac, bc, sh, grid, r);
             return hipGetLastError();
         };
         if (integ == LZ_INTEGRATOR_EULER && plan.ga == 1) e = run(Int<0>{}, Int<1>{}, Int<4>{});
@@ -1564,6 +1622,18 @@ hipError_t launch_mix(const KernelShape &shape, const PlainArgs &args, uint32_t 
         else e = run(Int<2>{}, Int<1>{}, Int<4>{});
     }
     return e;
+}
+
+template <bool X>
+hipError_t launch_mix(const KernelShape &shape, const PlainArgs &args, uint32_t integ, const MixPlan &plan,
+                      unsigned long long *p, size_t n, hipStream_t s) {
+    return mix_rounds(shape, integ, plan, p, n, args.tag_acc + TAG_WIDE, s,
+                      [&](auto ic, auto ac, auto bc, const KernelShape &sh, unsigned grid, uint32_t r) {
+        constexpr int I = decltype(ic)::value, GA = decltype(ac)::value, GB = decltype(bc)::value;
+        PlainArgs a = args;
+        a.tile = (uint32_t)sh.tile;
+        hipLaunchKernelGGL((mix_kernel<I, X, GA, GB>), dim3(grid), dim3(sh.wg), lds_bytes(sh), s, a, plan, r);
+    });
 }
 
 hipError_t launch_plain(const KernelShape &sh, const lz_key &key, const lz_params &prm, int decrypt,
@@ -1639,7 +1709,7 @@ hipError_t launch_plain_finalize(int decrypt, const unsigned long long *tag_acc,
 }
 
 hipError_t launch_batch(const KernelShape &sh, const DevInfo &dev, const lz_params &prm, const BatchDev &b,
-                        const SegPlan &plan, hipStream_t s) {
+                        const SegPlan &plan, const MixPlan &mix, hipStream_t s) {
     BatchArgs a;
     a.b = b;
     a.dt = prm.dt;
@@ -1654,6 +1724,13 @@ hipError_t launch_batch(const KernelShape &sh, const DevInfo &dev, const lz_para
     const uint64_t need = grid_of(sh, a.n_chains);
     if (need < grid) grid = need;
     const size_t words = 3 * (size_t)b.n_msg + 1;  // tags and the work-queue counter
+    if (mix.rounds)
+        return mix_rounds(sh, prm.integrator, mix, b.tag_acc, words, b.wide, s,
+                          [&](auto ic, auto ac, auto bc, const KernelShape &ms, unsigned g, uint32_t r) {
+            constexpr int I = decltype(ic)::value, GA = decltype(ac)::value, GB = decltype(bc)::value;
+            a.tile = (uint32_t)ms.tile;
+            hipLaunchKernelGGL((batch_mix_kernel<I, GA, GB>), dim3(g), dim3(ms.wg), lds_bytes(ms), s, a, mix, r);
+        });
     hipError_t e = sh.g > 1 ? launch_claim(sh, grid, b.tag_acc, words, b.wide, s)
                             : launch_fill_u64(b.tag_acc, words, s);
     if (e != hipSuccess) return e;

@@ -425,6 +425,9 @@ int batch_create(lz_ctx *c, const lz_params &prm, int decrypt, size_t n_msg, con
         }
         plan = plan_segments(n_chains, longest.data(), prm, sh.simds);
     }
+    MixPlan mix{};  // made for whole blocks: partial ones end early in it
+    if (sh.m == 1 && prefix[n_msg] >= tails.size()) mix = plan_mix(n_chains, prm, sh.simds);
+    const size_t n_state = std::max((size_t)plan.waves * WAVE_LANES, mix.rounds ? (size_t)mix.units * mix.unit : 0);
     lz_batch *b = new (std::nothrow) lz_batch();
     if (!b) return fail(LZ_E_NOMEM, "host allocation failed");
     b->ctx = c;
@@ -436,7 +439,7 @@ int batch_create(lz_ctx *c, const lz_params &prm, int decrypt, size_t n_msg, con
     const size_t o_slot = align_up(o_tail + std::max<size_t>(tails.size(), 1) * sizeof(uint32_t), 256);
     const size_t o_tag = o_slot + 256;
     const size_t o_seg = align_up(o_tag + (3 * n_msg + 2) * sizeof(unsigned long long), 256);  // tags, counter, wide
-    const size_t total = o_seg + (size_t)plan.waves * WAVE_LANES * sizeof(ChainState);
+    const size_t total = o_seg + n_state * sizeof(ChainState);
     hipError_t e = hipMalloc(&b->dmem, total);
     if (e != hipSuccess) {
         batch_free(b);
@@ -462,7 +465,7 @@ int batch_create(lz_ctx *c, const lz_params &prm, int decrypt, size_t n_msg, con
     d.n_msg = (uint32_t)n_msg;
     d.n_tail = (uint32_t)tails.size();
     d.n_full = prefix[n_msg];
-    plan.state = reinterpret_cast<ChainState *>(base + o_seg);
+    plan.state = mix.state = reinterpret_cast<ChainState *>(base + o_seg);
     d.tag_acc = reinterpret_cast<unsigned long long *>(base + o_tag);
     d.counter = d.tag_acc + 3 * n_msg;
     d.wide = d.counter + 1;
@@ -477,7 +480,7 @@ int batch_create(lz_ctx *c, const lz_params &prm, int decrypt, size_t n_msg, con
     }
     e = hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal);
     if (e == hipSuccess) {
-        hipError_t e1 = launch_batch(sh, c->dev, prm, d, plan, cap);
+        hipError_t e1 = launch_batch(sh, c->dev, prm, d, plan, mix, cap);
         hipError_t e2 = e1 == hipSuccess ? launch_batch_finalize(d, b->decrypt, cap) : e1;
         e = hipStreamEndCapture(cap, &b->graph);
         if (e2 != hipSuccess) e = e2;

@@ -117,3 +117,47 @@ def test_long_blocks(lz, per, block):
     C = ctx.encrypt(to_dev(P), b"mix")
     assert np.array_equal(host(C), oracle.encrypt(b"mix", P, nthreads=ORACLE_THREADS, **prm))
     assert np.array_equal(host(ctx.decrypt(C, b"mix")), P)
+
+
+@pytest.mark.parametrize("integ,per,tails", [("euler", 20, 40), ("euler", 33, 5000), ("euler", 5, 9), ("euler_fma", 6, 700),
+                                             ("rk4", 18, 100), ("euler", 6, 3072)])
+@pytest.mark.parametrize("room", [True, False])
+def test_batch(lz, integ, per, tails, room):
+    """Messages with partial last blocks and an empty one; replays, also beside work that leaves no room."""
+    import torch
+
+    rng = np.random.default_rng(per + tails)
+    n_full = per * simds() - tails
+    whole = rng.multinomial(n_full, np.ones(tails) / tails)
+    lens = [int(w) * B + int(t) for w, t in zip(whole, rng.integers(1, B, tails))] + [0]
+    pws = [b"m%d" % (i % 7) for i in range(len(lens))]
+    data = rng.integers(0, 256, sum(lens), dtype=np.uint8)
+    in_off, out_off = np.concatenate([[0], np.cumsum(lens)[:-1]]), lz.packed_offsets(lens, 24)
+    prm = dict(n_it=N_IT[integ], block_len=B, integrator=integ)
+    ctx = lz.Context(0, lz.params(**prm))
+    big = torch.zeros((4 * simds() * 64 * B,), dtype=torch.uint8, device="cuda")
+    out = torch.zeros(out_off[1], dtype=torch.uint8, device="cuda")
+    say(integ, n_full, tails, room)
+    b = lz.Batch(ctx, False, lens, pws, to_dev(data), in_off, out, out_off[0])
+    s1, s2 = torch.cuda.Stream(), torch.cuda.Stream()
+    for replay in range(3):
+        out.zero_()
+        torch.cuda.synchronize()
+        if not room:
+            lz.Context(0, lz.params(**prm)).encrypt(big, b"big", stream=s1)
+        b.encrypt(stream=s2)
+        torch.cuda.synchronize()
+        got = host(out)
+        if replay == 0:
+            first = got
+            for i in sorted({*range(min(300, len(lens))), *range(max(0, len(lens) - 300), len(lens))}):
+                n = lens[i]
+                want = oracle.encrypt(pws[i], data[in_off[i]:in_off[i] + n], nthreads=ORACLE_THREADS if n > 4096 else 1, **prm)
+                o = int(out_off[0][i])
+                assert np.array_equal(got[o:o + n + 24], want), (i, n)
+        assert np.array_equal(got, first), replay
+    plain = torch.zeros(len(data), dtype=torch.uint8, device="cuda")
+    st = torch.full((len(lens),), 99, dtype=torch.int32, device="cuda")
+    d = lz.Batch(ctx, True, lens, pws, out, out_off[0], plain, in_off)
+    d.decrypt(st)
+    assert np.array_equal(host(plain), data) and not host(st).any()
