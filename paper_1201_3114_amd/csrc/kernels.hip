@@ -198,7 +198,7 @@ __device__ __forceinline__ void lorenz_steps(double (&x)[M], double (&y)[M], dou
     if constexpr (M == 1 && I != LZ_INTEGRATOR_RK4) return lane_steps<I>(x[0], y[0], z[0], dt, n_it);
     const double h2 = dt * 0.5, h6 = I == LZ_INTEGRATOR_RK4 ? dt / 6.0 : 0.0;
     // Steps per loop iteration: 60 / M Euler steps for M chains (a divisor of the default 3000, about 6.7 KB
-    // of code); RK4's 68-operation step gains nothing from more.
+    // of code); RK4's 65-operation step gains nothing from more.
     constexpr int U = I == LZ_INTEGRATOR_RK4 ? 2 : 60 / M;
     const uint32_t q = n_it / U;
     for (uint32_t i = 0; i < q; ++i) {
