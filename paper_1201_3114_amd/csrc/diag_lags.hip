@@ -563,9 +563,9 @@ __global__ __launch_bounds__(LW_WG) void lagsum_wide_kernel(const uint8_t *data,
 // bytes.  Workgroup b takes lags kb = FIX_LAGS b .. kb + FIX_LAGS - 1, a lag per thread: it adds
 // up the first and the last min(kb, n) bytes (16-byte loads where aligned), then scans
 // x_j + x_{n-1-j} over its own lags (a wave scan by shuffles, the wave totals through LDS); every
-// load of a thread is issued before the first is used.  Every workgroup also adds up lag 0 and the
-// byte total, which r_k needs and the last one clears.  It writes the sums and the normalised coefficients where asked for
-// (a kernel of its own for these, scanning the bytes again, took 3 us more a call).
+// load of a thread is issued before the first is used.  It writes the sums and the normalised coefficients where asked for
+// (a kernel of its own for these, scanning the bytes again, took 3 us more a call).  For the coefficients every
+// workgroup also adds up lag 0 and the byte total, and the last one clears these; that costs 1.3 us, so the sums alone go without.
 constexpr int FIX_LAGS = DIAG_WG;
 
 // True in the launch's last workgroup to come here; the word it is counted in, the merge buffer's last, is 0 again for
@@ -624,7 +624,7 @@ __global__ __launch_bounds__(DIAG_WG) void lagsum_fix_kernel(const uint8_t *data
     unsigned long long part[DIAG_MERGE], raw0 = 0, tc = 0;
 #pragma unroll
     for (int c = 0; c < DIAG_MERGE; ++c) part[c] = k <= L ? merge[c * cs + k] : 0ull;
-    if (t < DIAG_MERGE) {
+    if (r && t < DIAG_MERGE) {
         raw0 = merge[t * cs];
         tc = merge[t * cs + L + 1];
     }
@@ -659,14 +659,18 @@ __global__ __launch_bounds__(DIAG_WG) void lagsum_fix_kernel(const uint8_t *data
 #pragma unroll
         for (int c = 0; c < DIAG_MERGE; ++c) {
             raw += part[c];
-            if (k > 0) merge[c * cs + k] = 0;
+            if (k > 0 || !r) merge[c * cs + k] = 0;
         }
         const unsigned long long mk = k < n ? n - k : 0, sk = raw - 128ull * pq - 16384ull * mk;
         if (sums) sums[k] = sk;
         if (r) r[k] = autocorr_r(n, k, sk, s0t[0], s0t[1], pq);
     }
-    // the words that every workgroup reads are cleared when all have read them
-    if (last_workgroup(merge) && t < DIAG_MERGE) merge[t * cs] = merge[t * cs + L + 1] = 0;
+    // the words that every workgroup has read are cleared when all have
+    if (!r) {
+        if (blockIdx.x == 0 && t < DIAG_MERGE) merge[t * cs + L + 1] = 0;
+    } else if (last_workgroup(merge) && t < DIAG_MERGE) {
+        merge[t * cs] = merge[t * cs + L + 1] = 0;
+    }
 }
 
 // The lag sums into sums[0..max_lag] and the normalised coefficients into r[0..max_lag], each unless NULL.
