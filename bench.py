@@ -432,16 +432,13 @@ def bench_diag(lz, torch, reps=5):
     ms = timed(lambda: lz.power_spectrum_2d(ctx, img_m))
     res["power_spectrum_1000x1000"] = dict(ms=ms, route="mixed-radix fft",
                                            hbm_GBps=spectrum_bytes(N, N) / ms / 1e6)
-    # other sides (1009 is prime): the direct DFT, dense matrix products on the binary64 matrix cores:
-    # the first pass real data times complex twiddles (2 FMA = 4 flops per term) for h/2 + 1 outputs
-    # of each column, the second complex times complex (8 flops per term) for those h/2 + 1 columns
+    # other sides from 80 to 2048 (1009 is prime): FFT convolutions with a chirp
     N = 1009
     img_d = x[:N * N].view(N, N)
-    hh = N // 2 + 1
-    flops = 4 * N * hh * N + 8 * N * N * hh
     ms = timed(lambda: lz.power_spectrum_2d(ctx, img_d))
-    res["power_spectrum_1009x1009"] = dict(ms=ms, route="direct", TFLOPs=flops / ms / 1e9,
-                                           frac_of_fp64_matrix_peak=flops / ms * 1e3 / FP64_FMA_COUNTED_PEAK)
+    res["power_spectrum_1009x1009"] = dict(ms=ms, route="chirp convolution", hbm_GBps=spectrum_bytes(N, N) / ms / 1e6)
+    ms = timed(lambda: lz.autocorrelation_2d(ctx, img_d))
+    res["autocorrelation_2d_1009x1009"] = dict(ms=ms, route="chirp convolution")
     ctx.close()
     return res
 
