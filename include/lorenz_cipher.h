@@ -172,7 +172,8 @@ int lz_context_params(const lz_ctx *ctx, lz_params *out);
  * batches created later, after validating it; LZ_E_INVAL if out of range.
  * The plain path takes chains_per_lane > 1 only for a message of at least
  * 2 x chains_per_lane waves' worth of blocks per SIMD (more chains per lane
- * lengthen each chain's latency); smaller messages run one chain per lane. */
+ * lengthen each chain's latency); smaller messages run one chain per lane, or
+ * in 4 or 16 lanes where that leaves at most one wave on every SIMD. */
 int lz_context_set_launch(lz_ctx *ctx, const lz_launch *shape);
 int lz_context_get_launch(const lz_ctx *ctx, lz_launch *out);
 

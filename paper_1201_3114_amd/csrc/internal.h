@@ -147,7 +147,7 @@ hipError_t launch_plain(const KernelShape &sh, const lz_key &key, const lz_param
                         const uint8_t *in, uint8_t *out, uint64_t n, unsigned long long *tag_acc, const SegPlan &plan,
                         const MixPlan &mix, hipStream_t s);
 // One stream update: its full whole blocks from in / out at global block index
-// block_base, plus x's head and tail chains, in one launch of one chain per lane.
+// block_base, plus x's head and tail chains, in one launch or the rounds of a mix plan.
 hipError_t launch_stream_step(const KernelShape &shape, const lz_key &key, const lz_params &prm, int decrypt,
                               const uint8_t *in, uint8_t *out, uint64_t full, uint64_t block_base,
                               const StreamExtra &x, unsigned long long *tag_acc, const MixPlan &mix, hipStream_t s);

@@ -358,12 +358,56 @@ __device__ __forceinline__ void quad_steps(double &x, double &y, double &z, doub
 // which keeps two instructions between a write and a DPP instruction that reads it, s1's two
 // masked additions among them.  Measured with one wave per SIMD: 40.6 clocks per step, against 44.6 in a quad.  A
 // wave holds 4 chains.
+//
+// RK4 takes the quad's field with each bank's coordinate in v: a 64-bit move of a broadcast, masked to the banks that read
+// it, takes the place of a quad's two 32-bit moves, and P1 comes in two of them (y for banks 0 and 2, z for bank 1), so
+// a field is 8 instructions and a step 43, 173.5 clocks against 190.
+
+// The vector field of the value V into OUT, banks as lanes of a quad (see LZ_QUAD_FIELD).
+#define LZ_ROW_FIELD(V, OUT)                                                                   \
+    "v_fma_f64 %[q0], %[m], " V ", %[c]\n"                                                     \
+    "v_mul_f64 %[u], %[k], " V "\n"                                                            \
+    "v_mov_b64_dpp %[p1], " V " row_newbcast:4 row_mask:0xf bank_mask:0x5\n"                   \
+    "v_mov_b64_dpp %[p2], " V " row_newbcast:0 row_mask:0xf bank_mask:0x6\n"                   \
+    "v_mov_b64_dpp %[p1], " V " row_newbcast:8 row_mask:0xf bank_mask:0x2\n"                   \
+    "v_fma_f64 " OUT ", %[s], %[p1], %[q0]\n"                                                  \
+    "v_mul_f64 " OUT ", " OUT ", %[p2]\n"                                                      \
+    "v_add_f64 " OUT ", " OUT ", -%[u]\n"
 
 template <int I>
 __device__ __forceinline__ void row_steps(double &x, double &y, double &z, double dt, uint32_t n_it,
                                           const LaneRole<16> &role, int lane) {
     const int r = (lane >> 2) & 3;
     double w = r == 0 ? x : (r == 1 ? y : (r == 2 ? z : 0.0));
+    if constexpr (I == LZ_INTEGRATOR_RK4) {
+        const double h2 = dt * 0.5, h6 = dt / 6.0, c = r == 1 ? RHO : 0.0;
+        double p1 = 0.0, p2 = r == 0 ? SIGMA : 0.0, q0, u, a, b, d, e, v;
+        uint32_t q = n_it / RK4_U - 1, rest = n_it % RK4_U;
+        asm volatile(LZ_STEP_LOOP(60,
+                         LZ_ROW_FIELD("%[w]", "%[a]")
+                         "v_mul_f64 %[v], %[a], %[h2]\n"
+                         "v_add_f64 %[v], %[w], %[v]\n"
+                         LZ_ROW_FIELD("%[v]", "%[b]")
+                         "v_mul_f64 %[v], %[b], %[h2]\n"
+                         "v_add_f64 %[v], %[w], %[v]\n"
+                         LZ_ROW_FIELD("%[v]", "%[e]")
+                         "v_mul_f64 %[v], %[e], %[dt]\n"
+                         "v_add_f64 %[v], %[w], %[v]\n"
+                         "v_add_f64 %[b], %[b], %[e]\n"
+                         LZ_ROW_FIELD("%[v]", "%[d]")
+                         "v_add_f64 %[a], %[a], %[d]\n"
+                         "v_fma_f64 %[a], 2.0, %[b], %[a]\n"
+                         "v_mul_f64 %[a], %[a], %[h6]\n"
+                         "v_add_f64 %[w], %[w], %[a]\n")
+                     : [w] "+v"(w), [p1] "+v"(p1), [p2] "+v"(p2), [q0] "=&v"(q0), [u] "=&v"(u), [a] "=&v"(a), [b] "=&v"(b),
+                       [d] "=&v"(d), [e] "=&v"(e), [v] "=&v"(v), [q] "+s"(q), [r] "+s"(rest)
+                     : [m] "v"(role.m), [c] "v"(c), [k] "v"(role.k), [s] "v"(role.s), [dt] "v"(dt), [h2] "v"(h2), [h6] "v"(h6)
+                     : "scc");
+        x = dpp_f64<0x150>(w);  // row_newbcast of lanes 0, 4, 8
+        y = dpp_f64<0x154>(w);
+        z = dpp_f64<0x158>(w);
+        return;
+    }
     double s1 = r == 1 ? z : (r == 3 ? 0.0 : y);
     double c = r == 0 ? SIGMA : (r == 3 ? 0.0 : x);
     double s2 = r == 0 ? -x : (r == 1 ? RHO : 0.0);
@@ -385,7 +429,6 @@ __device__ __forceinline__ void row_steps(double &x, double &y, double &z, doubl
                      : [k] "v"(role.k), [s] "v"(role.s), [dt] "v"(dtv), [mdt] "v"(mdt)
                      : "scc");
     } else {
-        static_assert(I == LZ_INTEGRATOR_EULER, "this integrator has no row form");
         asm volatile(LZ_STEP_LOOP(120,
                          "v_fma_f64 %[t], %[s], %[s1], %[s2]\n"
                          "v_mul_f64 %[t], %[t], %[c]\n"
@@ -1384,6 +1427,7 @@ template <typename F>
 hipError_t dispatch_wide(int g, uint32_t integ, F f) {
     if (g == 16 && integ == LZ_INTEGRATOR_EULER) return f(Int<1>{}, Int<0>{}, Int<16>{});
     if (g == 16 && integ == LZ_INTEGRATOR_EULER_FMA) return f(Int<1>{}, Int<1>{}, Int<16>{});
+    if (g == 16) return f(Int<1>{}, Int<2>{}, Int<16>{});
     if (g == 4 && integ == LZ_INTEGRATOR_EULER) return f(Int<1>{}, Int<0>{}, Int<4>{});
     if (g == 4 && integ == LZ_INTEGRATOR_RK4) return f(Int<1>{}, Int<2>{}, Int<4>{});
     return hipErrorInvalidValue;
@@ -1408,15 +1452,15 @@ size_t lds_bytes(const KernelShape &sh) { return (size_t)(sh.wg / WAVE) * wave_l
 // Lanes per chain of a launch of `chains` chains with m per lane on `simds` SIMDs: the most that still
 // make at most one wave per SIMD of all the chains.  Such a launch takes one chain's serial time, and
 // a step takes 40.6 clocks with 16 lanes (8 instructions instead of 9 for the fused Euler map), 44.6 with
-// 4 (RK4: 190 instead of 262) and 56.6 with one; with a second wave on a SIMD even two waves of 16 lanes'
+// 4 (RK4: 173.5 with 16, 190 with 4 and 262 with one) and 56.6 with one; with a second wave on a SIMD even two waves of 16 lanes'
 // 81 clocks would be more than the 56.6 of one chain per lane.  Four lanes gain nothing for the fused Euler map (9
-// instructions either way), 16 nothing for RK4, whose stages need copies of what the broadcasts add to.
+// instructions either way).
 // Measured, 16 / 4 / 1 lanes: 64 KiB in 13.2 / 14.5 / 18.3 ms; 3 MB in - / 14.6 / 18.5; 256 KiB of the
-// RK4 format in - / 60.7 / 92.0; 2048 sequential messages in 211 / 230 / 292.
+// RK4 format in 56.0 / 60.7 / 92.0; 2048 sequential messages in 211 / 230 / 292.
 int lanes_per_chain(uint64_t chains, int m, uint32_t integ, int simds) {
     const uint64_t lanes = (uint64_t)simds * WAVE;
     if (m != 1) return 1;
-    if (integ != LZ_INTEGRATOR_RK4 && chains * 16 <= lanes) return 16;
+    if (chains * 16 <= lanes) return 16;
     if (integ != LZ_INTEGRATOR_EULER_FMA && chains * 4 <= lanes) return 4;
     return 1;
 }
@@ -1471,7 +1515,7 @@ SegPlan plan_segments(uint64_t chains, const uint32_t *lens, const lz_params &pr
 
 // Clocks of a step with one wave per SIMD, g lanes per chain.
 static double step_clocks(uint32_t integ, int g) {
-    if (integ == LZ_INTEGRATOR_RK4) return g == 4 ? 190 : 262;
+    if (integ == LZ_INTEGRATOR_RK4) return g == 16 ? 173.5 : (g == 4 ? 190 : 262);
     if (integ == LZ_INTEGRATOR_EULER_FMA) return g == 16 ? 32.6 : 36.6;
     return g == 16 ? 40.6 : (g == 4 ? 44.6 : 56.6);
 }
@@ -1483,14 +1527,14 @@ static double step_clocks(uint32_t integ, int g) {
 // round is la bytes in ga lanes and lb in gb, chosen to take the same time.  The plan with the least predicted time is
 // taken (a step's clocks as measured, MIX_ROUND_US for a round's launch, checkpoints and gap), if it beats one
 // launch in ga lanes by 3%.  Measured (with and without a plan): 4.1 MiB in
-// 15.1 and 18.5 ms, 6 MiB 16.5 and 18.5, 8 MiB 17.6 and 18.7, 1.3 MiB 13.8 and 14.6; RK4 at 5 MiB 70.3 and
+// 15.1 and 18.5 ms, 6 MiB 16.5 and 18.5, 8 MiB 17.6 and 18.7, 1.3 MiB 13.8 and 14.6; RK4 at 1.2 MB 58.0 and 61.2, 5 MiB 70.3 and
 // 88.9; the fused map at 1.3 MiB 11.3 and 12.0; batches of 5.2 MiB 16.1 and 18.5, 7.7 MiB 17.7 and 18.6.  From 10 MiB on
 // the gain would be under 3%.
 MixPlan plan_mix(uint64_t chains, const lz_params &prm, int simds) {
     constexpr double MIX_ROUND_US = 12.0, CLOCKS_PER_US = 2400.0;
     MixPlan best{};
     const int ga = lanes_per_chain(chains, 1, prm.integrator, simds);
-    const int gb = prm.integrator == LZ_INTEGRATOR_EULER ? 4 * ga : (prm.integrator == LZ_INTEGRATOR_RK4 ? 4 : 16);
+    const int gb = prm.integrator == LZ_INTEGRATOR_EULER_FMA ? 16 : 4 * ga;
     if (ga >= gb || gb > 16 || chains * ga > (uint64_t)simds * WAVE) return best;
     MixPlan p{};
     p.ga = ga;
@@ -1619,7 +1663,8 @@ hipError_t mix_rounds(const KernelShape &shape, uint32_t integ, const MixPlan &p
         if (integ == LZ_INTEGRATOR_EULER && plan.ga == 1) e = run(Int<0>{}, Int<1>{}, Int<4>{});
         else if (integ == LZ_INTEGRATOR_EULER) e = run(Int<0>{}, Int<4>{}, Int<16>{});
         else if (integ == LZ_INTEGRATOR_EULER_FMA) e = run(Int<1>{}, Int<1>{}, Int<16>{});
-        else e = run(Int<2>{}, Int<1>{}, Int<4>{});
+        else if (plan.ga == 1) e = run(Int<2>{}, Int<1>{}, Int<4>{});
+        else e = run(Int<2>{}, Int<4>{}, Int<16>{});
     }
     return e;
 }

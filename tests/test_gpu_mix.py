@@ -30,7 +30,8 @@ def simds():
 # chains per SIMD, and a few more: between 16 and 64 the layouts of 1 and 4 lanes meet (1 and 16 lanes for the fused
 # map, from 4), between 4 and 16 those of 4 and 16
 CASES = [("euler", 16, 5), ("euler", 24, 0), ("euler", 41, 33), ("euler", 60, -1), ("euler", 4, 3), ("euler", 6, -2),
-         ("euler", 9, 7), ("euler_fma", 4, 9), ("euler_fma", 7, 1), ("euler_fma", 20, 0), ("rk4", 17, 3), ("rk4", 30, -7)]
+         ("euler", 9, 7), ("euler_fma", 4, 9), ("euler_fma", 7, 1), ("euler_fma", 20, 0), ("rk4", 17, 3), ("rk4", 30, -7),
+         ("rk4", 4, 5), ("rk4", 7, -1)]
 
 
 @pytest.mark.parametrize("integ,per,more", CASES)
