@@ -48,15 +48,15 @@ def test_threads_on_one_context(lz):
 
     done = []
 
-    def work(ctx, i):
-        data = np.random.default_rng(i).integers(0, 2 + 50 * i, 5000, dtype=np.uint8)
-        want, s = entropy64(data), torch.cuda.Stream()
-        with torch.cuda.stream(s):
-            hist = lz.histogram(ctx, to_dev(data), stream=s)
-            done.append(all(abs(lz.entropy(ctx, hist, stream=s) - want) <= TOL for _ in range(50)))
+    def work(ctx, hist, want):
+        s = torch.cuda.Stream()
+        done.append(all(abs(lz.entropy(ctx, hist, stream=s) - want) <= TOL for _ in range(50)))
 
     with closing(lz.Context(0)) as ctx:
-        threads = [threading.Thread(target=work, args=(ctx, i)) for i in range(4)]
+        data = [np.random.default_rng(i).integers(0, 2 + 50 * i, 5000, dtype=np.uint8) for i in range(4)]
+        hists = [lz.histogram(ctx, to_dev(d)) for d in data]
+        torch.cuda.synchronize()
+        threads = [threading.Thread(target=work, args=(ctx, h, entropy64(d))) for h, d in zip(hists, data)]
         for t in threads:
             t.start()
         for t in threads:
