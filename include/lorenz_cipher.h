@@ -366,7 +366,9 @@ int lz_stream_close(lz_stream *st);
  * order, each with all of its unfinished chains or none, and later requests
  * that fit fill the room an earlier one leaves (the first request with work
  * always joins, so one larger than the cap still runs).  Policy
- * LZ_SERVE_ALL_CHAINS: every tick runs every admitted chain.  Results are
+ * LZ_SERVE_ALL_CHAINS: every tick runs every admitted chain.  A tick that
+ * leaves SIMDs idle may advance some of its requests by fewer bytes than the
+ * others (never more than tick_bytes), in less time.  Results are
  * bit-identical to the plain path whatever the policy. */
 enum { LZ_SERVE_ADAPTIVE = 0, LZ_SERVE_ALL_CHAINS = 1 };
 typedef struct {

@@ -182,10 +182,16 @@ struct TickDev {
     const uint32_t *list;         // active chain slot indices
     uint32_t n_list;
     uint32_t tick_bytes;
+    uint32_t n_narrow, narrow_bytes;  // a mixed tick (narrow_bytes > 0): the list's first n_narrow run a lane each, by this
     uint32_t *done_queue;         // request slots completed in this tick
     uint32_t *done_count;
 };
 hipError_t launch_tick(const KernelShape &sh, const lz_params &prm, const TickDev &t, hipStream_t s);
+// Bytes a lane-per-chain chain runs while one of TICK_MIX_LANES lanes runs tick_bytes, or 0: no mixed ticks.
+constexpr int TICK_MIX_LANES = 4;
+uint32_t tick_narrow_bytes(const lz_params &prm, uint32_t tick_bytes);
+// How much faster a tick of n chains gets on when w of them run wide by tick_bytes and the rest by narrow_bytes.
+double tick_mix_gain(const lz_params &prm, uint32_t tick_bytes, uint32_t narrow_bytes, uint64_t n, uint64_t w);
 hipError_t launch_install(ReqDesc *reqs, ChainSlot *slots, const ReqDesc *staged, const uint32_t *meta,
                           const uint32_t *idx, uint32_t n_new, uint32_t block_len, hipStream_t s);
 hipError_t launch_req_zero(const ReqDesc *reqs, const uint32_t *req_ids, uint32_t n, hipStream_t s);

@@ -1239,18 +1239,11 @@ struct TickArgs {
     uint32_t n_it, block_len, tile;
 };
 
-// A tick has the device to itself as a rule, so a short one runs wide without a claim.
+// Advances the chains of list entries base, base + 1, ... below end, a wave's worth, by up to tick_bytes bytes.
 template <int M, int I, int G>
-__global__ __launch_bounds__(256) void tick_kernel(TickArgs a) {
-    extern __shared__ char lds[];
-    constexpr int ROWS = WAVE * M / G;
+__device__ __forceinline__ void tick_body(const TickArgs &a, const WaveLds &w, uint64_t base, uint64_t end,
+                                          uint32_t tick_bytes) {
     const int lane = threadIdx.x % WAVE;
-    const int wid = threadIdx.x / WAVE;
-    const int wpw = blockDim.x / WAVE;
-    count_waves(wpw);
-    const WaveLds w = wave_lds<ROWS>(lds + (size_t)wid * wave_lds_bytes(ROWS, a.tile), a.tile);
-    const uint64_t base = ((uint64_t)blockIdx.x * wpw + wid) * ROWS;
-
     Chains<M> c;
     const uint8_t *in[M];
     uint8_t *out[M];
@@ -1259,7 +1252,7 @@ __global__ __launch_bounds__(256) void tick_kernel(TickArgs a) {
 #pragma unroll
     for (int m = 0; m < M; ++m) {
         const uint64_t e = base + (uint64_t)m * WAVE + lane / G;
-        valid[m] = e < a.t.n_list;
+        valid[m] = e < end;
         slot[m] = valid[m] ? a.t.list[e] : 0u;
         cnt[m] = 0;
         in[m] = nullptr;
@@ -1288,7 +1281,7 @@ __global__ __launch_bounds__(256) void tick_kernel(TickArgs a) {
             c.dec[m] = md.decrypt;
         }
         const uint32_t left = s.len - s.pos;
-        cnt[m] = left < a.t.tick_bytes ? left : a.t.tick_bytes;
+        cnt[m] = left < tick_bytes ? left : tick_bytes;
         const uint64_t off = (uint64_t)s.blk * a.block_len + s.pos;
         in[m] = md.in + off;
         out[m] = md.out + off;
@@ -1301,7 +1294,6 @@ __global__ __launch_bounds__(256) void tick_kernel(TickArgs a) {
         s.mu[0] = (uint8_t)c.mu0[m]; s.mu[1] = (uint8_t)c.mu1[m]; s.mu[2] = (uint8_t)c.mu2[m];
         s.om[0] = (uint8_t)c.om0[m]; s.om[1] = (uint8_t)c.om1[m]; s.om[2] = (uint8_t)c.om2[m];
     });
-    count_waves(-wpw);
 #pragma unroll
     for (int m = 0; m < M; ++m) {
         if (!valid[m] || lane % G != 0) continue;
@@ -1330,6 +1322,38 @@ __global__ __launch_bounds__(256) void tick_kernel(TickArgs a) {
         const uint32_t at = atomicAdd(a.t.done_count, 1u);
         a.t.done_queue[at] = (s.req << 1) | (st != LZ_OK ? 1u : 0u);
     }
+}
+
+// A tick has the device to itself as a rule, so a short one runs wide without a claim.
+template <int M, int I, int G>
+__global__ __launch_bounds__(256) void tick_kernel(TickArgs a) {
+    extern __shared__ char lds[];
+    constexpr int ROWS = WAVE * M / G;
+    const int wid = threadIdx.x / WAVE, wpw = blockDim.x / WAVE;
+    count_waves(wpw);
+    const WaveLds w = wave_lds<ROWS>(lds + (size_t)wid * wave_lds_bytes(ROWS, a.tile), a.tile);
+    tick_body<M, I, G>(a, w, ((uint64_t)blockIdx.x * wpw + wid) * ROWS, a.t.n_list, a.t.tick_bytes);
+    count_waves(-wpw);
+}
+
+// A tick between the chain counts of two layouts (see plan_mix): its list's first n_narrow chains run a lane each
+// by narrow_bytes, the others in G lanes by tick_bytes, which takes the same time; the server gives the
+// wide places to the requests with the most bytes left.  A burst of 88,000 chains, 22,272 of them behind 65,536: 37.2 ms of
+// ticks instead of 40.3; requests arriving at 0.3 and 0.5 of capacity have a median latency of 16.0 and 18.6 ms, 18.7 and
+// 20.4 without mixed ticks.
+template <int I, int G>
+__global__ __launch_bounds__(256) void tick_mix_kernel(TickArgs a) {
+    extern __shared__ char lds[];
+    const int wid = threadIdx.x / WAVE, wpw = blockDim.x / WAVE;
+    count_waves(wpw);
+    char *p = lds + (size_t)wid * wave_lds_bytes(WAVE, a.tile);
+    const uint32_t v = __builtin_amdgcn_readfirstlane(blockIdx.x * wpw + wid), narrow = (a.t.n_narrow + WAVE - 1) / WAVE;
+    if (v < narrow)
+        tick_body<1, I, 1>(a, wave_lds<WAVE>(p, a.tile), (uint64_t)v * WAVE, a.t.n_narrow, a.t.narrow_bytes);
+    else
+        tick_body<1, I, G>(a, wave_lds<WAVE / G>(p, a.tile), a.t.n_narrow + (uint64_t)(v - narrow) * (WAVE / G), a.t.n_list,
+                           a.t.tick_bytes);
+    count_waves(-wpw);
 }
 
 // ---- streaming ----------------------------------------------------------------------------
@@ -1566,6 +1590,18 @@ MixPlan plan_mix(uint64_t chains, const lz_params &prm, int simds) {
         best.rounds = r;
     }
     return best;
+}
+
+// Four lanes gain nothing for the fused Euler map, and 16 beside four too little for a tick.
+uint32_t tick_narrow_bytes(const lz_params &prm, uint32_t tick_bytes) {
+    if (prm.integrator == LZ_INTEGRATOR_EULER_FMA) return 0;
+    return (uint32_t)(tick_bytes * step_clocks(prm.integrator, TICK_MIX_LANES) / step_clocks(prm.integrator, 1));
+}
+
+double tick_mix_gain(const lz_params &prm, uint32_t tick_bytes, uint32_t narrow_bytes, uint64_t n, uint64_t w) {
+    const double ca = step_clocks(prm.integrator, 1), cb = step_clocks(prm.integrator, TICK_MIX_LANES);
+    const double time = narrow_bytes * ca > tick_bytes * cb ? narrow_bytes * ca : tick_bytes * cb;
+    return ((double)(n - w) * narrow_bytes + (double)w * tick_bytes) * ca / (time * (double)n);
 }
 
 bool shape_valid(const KernelShape &sh, const DevInfo &dev) {
@@ -1820,8 +1856,18 @@ hipError_t launch_tick(const KernelShape &sh, const lz_params &prm, const TickDe
     a.n_it = prm.n_it;
     a.block_len = prm.block_len;
     a.tile = (uint32_t)sh.tile;
-    const uint64_t grid = grid_of(sh, t.n_list);
     const size_t lds = lds_bytes(sh);
+    if (t.narrow_bytes) {
+        constexpr int G = TICK_MIX_LANES;
+        const uint32_t per = WAVE / G, wpw = sh.wg / WAVE;
+        const uint32_t waves = (t.n_narrow + WAVE - 1) / WAVE + (t.n_list - t.n_narrow + per - 1) / per;
+        const dim3 grid((waves + wpw - 1) / wpw), wg(sh.wg);
+        if (prm.integrator == LZ_INTEGRATOR_EULER) hipLaunchKernelGGL((tick_mix_kernel<0, G>), grid, wg, lds, s, a);
+        else if (prm.integrator == LZ_INTEGRATOR_RK4) hipLaunchKernelGGL((tick_mix_kernel<2, G>), grid, wg, lds, s, a);
+        else return hipErrorInvalidValue;
+        return hipGetLastError();
+    }
+    const uint64_t grid = grid_of(sh, t.n_list);
     return dispatch(sh.m, sh.g, prm.integrator, [&](auto mc, auto ic, auto gc) {
         constexpr int M = decltype(mc)::value;
         constexpr int I = decltype(ic)::value;

@@ -20,6 +20,11 @@
 // its unfinished chains or not at all, and fills the room a large request
 // leaves with later ones that fit.  The all-chains policy runs every admitted
 // chain in every tick.
+//
+// A tick whose chains do not fill the SIMDs with a lane each, and are too many for
+// four lanes each, runs some requests one way and the rest the other, in the
+// time that tick_bytes bytes take in four lanes: the requests with the most
+// bytes left by tick_bytes, the others by fewer.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -106,8 +111,9 @@ struct Request {
     std::vector<uint32_t> slots;  // chain slot of block b
     bool released = false;    // resources returned; leaves the active list at the next compaction
     uint64_t arena_off = 0, arena_bytes = 0;
-    uint32_t ticks_full = 0, ticks_tail = 0;  // ticks until full / tail chains finish
-    uint32_t ticks_run = 0;
+    uint64_t tail = 0;        // bytes of the last block
+    uint64_t pos = 0;         // bytes that ticks have given each of its chains (one that ended earlier excepted)
+    bool wide = false;        // in this tick, several lanes per chain
     bool cancelled = false;   // lz_server_cancel: no further ticks; released once no tick in flight lists it
     uint64_t last_tick = 0;   // sequence number of the last tick that listed its chains
 };
@@ -170,7 +176,7 @@ struct TickSlot {
     uint64_t bytes = 0;
     uint64_t seq = 0;     // tick sequence number (1, 2, ...)
     uint32_t waves = 0;   // waves per SIMD of the tick's chains, at most
-    int g = 1;            // lanes per chain of the tick
+    int kind = 0;         // 0, 1, 2: a tick of 1, 4, 16 lanes per chain, 3: of 1 and 4
     bool late = false;    // queued while the tick before it ran: its start shows whether in time
 };
 
@@ -200,13 +206,14 @@ struct lz_server {
     std::vector<uint32_t> free_reqs;
     std::vector<Request *> by_slot;
     std::vector<Request *> active;  // admitted, in admission order
+    std::vector<Request *> join, by_left;  // a tick's requests, in admission order and by bytes left
     std::deque<Request *> waiting;  // arrived, not admitted (FIFO); their chains: waiting_chains
     uint64_t hbm_fixed = 0;
     uint64_t tick_seq = 0, done_seq = 0;  // last tick queued, last tick completed (ticks complete in order)
     // late admission (server thread only): a tick's duration per wave per SIMD (a running mean of
-    // the measured ticks, apart for 1, 4 and 16 lanes per chain), when the last completed tick was seen to end, and when the next step
+    // the measured ticks, apart for each kind), when the last completed tick was seen to end, and when the next step
     // may start
-    double tick_ns_per_wave[3] = {0, 0, 0}, late_margin_ns = LATE_MARGIN_START_NS;
+    double tick_ns_per_wave[4] = {0, 0, 0, 0}, late_margin_ns = LATE_MARGIN_START_NS;
     uint64_t tick_end_ns = 0, next_step_ns = 0;
     // shared with submitters / pollers
     std::mutex mu;
@@ -273,11 +280,8 @@ void admit(lz_server *s, std::vector<Request *> &admitted) {
         s->free_reqs.pop_back();
         s->by_slot[r->req_slot] = r;
         r->admit_ns = lz_now_ns();
-        const uint32_t T = s->cfg.tick_bytes;
-        const uint64_t tail = r->n == 0 ? 0 : r->n - (uint64_t)(nb - 1) * B;
-        r->ticks_full = nb > 1 ? (uint32_t)((B + (uint64_t)T - 1) / T) : 0;
-        r->ticks_tail = tail == 0 ? 1 : (uint32_t)((tail + T - 1) / T);
-        r->ticks_run = 0;
+        r->tail = r->n == 0 ? 0 : r->n - (uint64_t)(nb - 1) * B;
+        r->pos = 0;
         admitted.push_back(r);
     }
     const uint64_t inuse = s->arena.used() + s->hbm_fixed;
@@ -302,7 +306,7 @@ int complete_tick(lz_server *s, TickSlot &t) {
     const bool timed = hipEventElapsedTime(&ms, t.ev_start, t.ev_end) == hipSuccess;
     if (timed && t.waves) {
         const double per = (double)ms * 1e6 / t.waves;
-        double &mean = s->tick_ns_per_wave[t.g == 1 ? 0 : (t.g == 4 ? 1 : 2)];
+        double &mean = s->tick_ns_per_wave[t.kind];
         mean = mean > 0 ? 0.75 * mean + 0.25 * per : per;
     }
     {
@@ -493,11 +497,12 @@ int server_step(lz_server *s) {
         LZ_HIP(launch_install(s->reqs, s->slots, t.d_req, t.d_meta, t.d_idx, (uint32_t)k, s->ctx->prm.block_len, pre));
     }
     // the chains that still have bytes to process: each request's full chains until they end,
-    // its last chain until it ends (the tick count of each is known at admission)
+    // its last chain until it ends (an empty message's takes part in one tick)
     const uint32_t T = s->cfg.tick_bytes, B = s->ctx->prm.block_len;
+    auto full_left = [&](const Request *r) { return r->nb > 1 && r->pos < B; };
+    auto tail_left = [&](const Request *r) { return r->pos == 0 || r->pos < r->tail; };
     auto unfinished = [&](const Request *r) -> uint32_t {
-        const uint32_t tr = r->ticks_run;
-        return (tr < r->ticks_full ? r->nb - 1 : 0) + (tr < r->ticks_tail ? 1 : 0);
+        return (full_left(r) ? r->nb - 1 : 0) + (tail_left(r) ? 1 : 0);
     };
     // waves per SIMD of this tick, from the backlog
     uint64_t backlog = s->waiting_chains;
@@ -509,30 +514,60 @@ int server_step(lz_server *s) {
                                                                 : std::min<uint64_t>(k * s->simd_chains, s->max_chains);
     // requests join in admission order, all their unfinished chains or none, up to the cap; the
     // first request with work always joins, so one larger than the cap still runs
-    uint32_t n_list = 0;
+    uint32_t n_join = 0, n_list = 0, n_wide = 0;
     uint64_t tick_bytes = 0;
     const uint64_t seq = s->tick_seq + 1;
+    std::vector<Request *> &join = s->join;
+    join.clear();
     for (Request *r : s->active) {
         if (r->cancelled) continue;
-        const uint32_t tr = r->ticks_run;
         const uint32_t want = unfinished(r);
-        if (want == 0 || (n_list && (uint64_t)n_list + want > cap)) continue;
-        if (tr < r->ticks_full) {
-            std::memcpy(t.h_list + n_list, r->slots.data(), (r->nb - 1) * sizeof(uint32_t));
-            n_list += r->nb - 1;
-            tick_bytes += (uint64_t)(r->nb - 1) * std::min<uint64_t>(T, (uint64_t)B - (uint64_t)tr * T);
+        if (want == 0 || (n_join && (uint64_t)n_join + want > cap)) continue;
+        join.push_back(r);
+        r->wide = false;
+        n_join += want;
+    }
+    KernelShape sh = s->shape;
+    sh.g = lanes_per_chain(n_join, sh.m, s->ctx->prm.integrator, (int)(s->simd_chains / WAVE_LANES));
+    // a tick that leaves SIMDs idle with a lane per chain gives some requests, those with the most left, more lanes:
+    // w chains of these keep the waves, n - w over 64 and w over 16, at one per SIMD
+    uint32_t narrow = 0;
+    if (sh.g == 1 && sh.m == 1 && n_join < s->simd_chains) narrow = tick_narrow_bytes(s->ctx->prm, T);
+    if (narrow) {
+        const uint64_t room = (s->simd_chains - n_join) / (TICK_MIX_LANES - 1);
+        auto left = [&](const Request *r) { return (r->nb > 1 ? (uint64_t)B : r->tail) - r->pos; };
+        std::vector<Request *> &by_left = s->by_left;
+        by_left = join;
+        std::stable_sort(by_left.begin(), by_left.end(), [&](const Request *a, const Request *b) { return left(a) > left(b); });
+        for (Request *r : by_left) {
+            const uint32_t want = unfinished(r);
+            if ((uint64_t)n_wide + want + 2 * WAVE_LANES > room) continue;  // with room for two part waves
+            r->wide = true;
+            n_wide += want;
         }
-        if (tr < r->ticks_tail) {
-            t.h_list[n_list++] = r->slots[r->nb - 1];
-            const uint64_t tail = r->n - (uint64_t)(r->nb - 1) * B;
-            const uint64_t done = (uint64_t)tr * T;
-            tick_bytes += tail > done ? std::min<uint64_t>(T, tail - done) : 0;
-        }
-        if (tr < r->ticks_full || tr < r->ticks_tail) {
-            r->ticks_run++;
-            r->last_tick = seq;
+        if (tick_mix_gain(s->ctx->prm, T, narrow, n_join, n_wide) < 1.03) {
+            for (Request *r : join) r->wide = false;
+            narrow = n_wide = 0;
         }
     }
+    auto list = [&](Request *r, uint64_t step) {
+        if (full_left(r)) {
+            std::memcpy(t.h_list + n_list, r->slots.data(), (r->nb - 1) * sizeof(uint32_t));
+            n_list += r->nb - 1;
+            tick_bytes += (uint64_t)(r->nb - 1) * std::min<uint64_t>(step, B - r->pos);
+        }
+        if (tail_left(r)) {
+            t.h_list[n_list++] = r->slots[r->nb - 1];
+            tick_bytes += r->tail > r->pos ? std::min<uint64_t>(step, r->tail - r->pos) : 0;
+        }
+        r->pos += step;
+        r->last_tick = seq;
+    };
+    for (Request *r : join)
+        if (!r->wide) list(r, narrow ? narrow : T);
+    const uint32_t n_narrow = n_list;
+    for (Request *r : join)
+        if (r->wide) list(r, T);
     if (n_list) {
         LZ_HIP(hipMemcpyAsync(t.d_list, t.h_list, n_list * sizeof(uint32_t), hipMemcpyHostToDevice, pre));
         LZ_HIP(launch_fill_u64(reinterpret_cast<unsigned long long *>(t.d_done), 1, pre));
@@ -544,17 +579,17 @@ int server_step(lz_server *s) {
         td.list = t.d_list;
         td.n_list = n_list;
         td.tick_bytes = T;
+        td.n_narrow = n_narrow;
+        td.narrow_bytes = narrow;
         td.done_count = t.d_done;
         td.done_queue = t.d_done + 2;
         LZ_HIP(hipEventRecord(t.ev_start, st));
-        KernelShape sh = s->shape;
-        sh.g = lanes_per_chain(n_list, sh.m, s->ctx->prm.integrator, (int)(s->simd_chains / WAVE_LANES));
         LZ_HIP(launch_tick(sh, s->ctx->prm, td, st));
         LZ_HIP(hipEventRecord(t.ev_end, st));
         t.bytes = tick_bytes;
         t.seq = seq;
         t.waves = (uint32_t)((n_list + s->simd_chains - 1) / s->simd_chains);
-        t.g = sh.g;
+        t.kind = narrow ? 3 : (sh.g == 1 ? 0 : (sh.g == 4 ? 1 : 2));
         t.late = s->ts[s->cur ^ 1].in_flight;
         s->tick_seq = seq;
         t.in_flight = true;
@@ -567,7 +602,7 @@ int server_step(lz_server *s) {
         // the tick queued above started when the previous one ended: the next step waits until
         // shortly before it is expected to end, so that the tick after it takes the requests
         // that arrive meanwhile (and not one tick later)
-        const double est = s->tick_ns_per_wave[t.g == 1 ? 0 : (t.g == 4 ? 1 : 2)] * t.waves;
+        const double est = s->tick_ns_per_wave[t.kind] * t.waves;
         if (t.in_flight && est > s->late_margin_ns)
             s->next_step_ns = s->tick_end_ns + (uint64_t)(est - s->late_margin_ns);
     }
