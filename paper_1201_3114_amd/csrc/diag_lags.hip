@@ -385,7 +385,7 @@ __global__ __launch_bounds__(DIAG_WG) __attribute__((amdgpu_waves_per_eu(2))) vo
 
 // ---- the lag sums past lag 256: windows of lags on 32-byte rows ---------------------------------
 //
-// One launch per window of lags k_lo .. k_lo + Lw (k_lo a multiple of 32, Lw < LW_WINDOW): the
+// blockIdx.y takes the window of lags k_lo .. k_lo + Lw (k_lo = y W, W a multiple of 32 and at most LW_WINDOW): the
 // products of the kernel above, B taken from the rows k_lo / 32 further on.  A task stages its own
 // LW_ROWS rows (region A) and, apart, the rows from k_lo / 32 on that its shifted operands read
 // (region B, LW_ROWS + LW_BHALO rows), so a window's LDS does not grow with k_lo.  A window has up
@@ -399,6 +399,7 @@ constexpr uint32_t LW_ROWS = 1024;
 constexpr int LW_WG = 512;
 constexpr uint32_t LW_IT = 4;                                 // tiles per item
 constexpr uint32_t LW_WINDOW = 4096;                          // lags per window at most
+constexpr uint32_t LW_LEAST = 256;                            // lags per window at least, when split for more workgroups
 constexpr uint32_t LW_MAX_NT = LW_WINDOW / 32 + 1;            // 129 tiles
 constexpr uint32_t LW_MAX_F = (LW_MAX_NT + 3) / 4;            // tiles of one residue mod 4
 // B bytes read by an item at f0 (a multiple of 4): 4 f0 + 16 h + up to 32 past the row block
@@ -465,9 +466,9 @@ __device__ __forceinline__ void lw_item(const uint8_t *ap, const uint8_t *bp, ui
         for (int i = 0; i < 16; ++i) atomicAdd(diag + (128 * q - 8 * (i / 4) - i % 4), (unsigned long long)(long long)d[q][i]);
 }
 
-__global__ __launch_bounds__(LW_WG) void lagsum_wide_kernel(const uint8_t *data, uint64_t n, uint32_t Lw,
-                                                              uint32_t k_lo, uint32_t L_all,
-                                                              unsigned long long *merge) {
+__global__ __launch_bounds__(LW_WG) void lagsum_wide_kernel(const uint8_t *data, uint64_t n, uint32_t W,
+                                                              uint32_t L_all, unsigned long long *merge) {
+    const uint32_t k_lo = blockIdx.y * W, Lw = L_all - k_lo < W - 1 ? L_all - k_lo : W - 1;
     __shared__ __align__(16) uint8_t la[32 * LW_ASTRIDE];
     __shared__ __align__(16) uint8_t lb[32 * LW_BSTRIDE];
     __shared__ unsigned long long cnt_all[32 * LW_MAX_NT + 32];
@@ -707,17 +708,18 @@ int lag_sums(lz_ctx *c, const uint8_t *d_data, size_t n, uint32_t max_lag, unsig
             LZ_HIP(hipGetLastError());
             return diag_end(c, s);
         }
-        // windows of at most LW_WINDOW lags, as even as 32-lag steps allow, one launch each
-        const uint64_t lags = (uint64_t)max_lag + 1, nwin = (lags + LW_WINDOW - 1) / LW_WINDOW;
-        const uint32_t W = (uint32_t)(((lags + nwin - 1) / nwin + 31) / 32 * 32);
+        // windows of at most LW_WINDOW lags, as even as 32-lag steps allow; of fewer, LW_LEAST at least, where the
+        // tasks alone leave compute units idle.  All in one launch: with one after the other and LW_WINDOW lags each,
+        // 16384 lags of 20 kB took 160 us, now 21.5; of 1 MiB 161 and 35, of 16 MiB 336 and 309; 1000 lags of 100 kB 30.4 and 23.7
         if (int rc = grid(reinterpret_cast<const void *>(&lagsum_wide_kernel), LW_WG,
                           ((n + 31) / 32 + LW_ROWS - 1) / LW_ROWS, &blocks))
             return rc;
-        for (uint32_t k_lo = 0; k_lo <= max_lag; k_lo += W) {
-            const uint32_t Lw = max_lag - k_lo < W - 1 ? max_lag - k_lo : W - 1;
-            hipLaunchKernelGGL(lagsum_wide_kernel, dim3(blocks), dim3(LW_WG), 0, s, d_data, (uint64_t)n, Lw, k_lo,
-                               max_lag, c->diag_merge);
-        }
+        const uint64_t lags = (uint64_t)max_lag + 1, idle = (uint64_t)c->dev.cus / blocks;
+        const uint64_t least = (lags + LW_WINDOW - 1) / LW_WINDOW, most = (lags + LW_LEAST - 1) / LW_LEAST;
+        const uint64_t nwin = idle > least ? (idle < most ? idle : most) : least;
+        const uint32_t W = (uint32_t)(((lags + nwin - 1) / nwin + 31) / 32 * 32);
+        hipLaunchKernelGGL(lagsum_wide_kernel, dim3(blocks, (unsigned)((lags + W - 1) / W)), dim3(LW_WG), 0, s, d_data,
+                           (uint64_t)n, W, max_lag, c->diag_merge);
         hipLaunchKernelGGL(lagsum_fix_kernel, dim3(max_lag / FIX_LAGS + 1), dim3(DIAG_WG), 0, s, d_data,
                            (uint64_t)n, max_lag, c->diag_merge, sums, r);
         LZ_HIP(hipGetLastError());

@@ -29,7 +29,8 @@ def coefficients(x, L):
 
 
 @pytest.mark.parametrize("n,L", [(1, 0), (2, 3), (100, 256), (16383, 31), (16384, 256), (16385, 256), (32769, 32),
-                                 (300, 300), (5000, 257), (32769, 1000), (20001, 4500)])
+                                 (300, 300), (5000, 257), (32769, 1000), (20001, 4500), (9000, 16384), (70001, 5000),
+                                 (600000, 520)])
 @pytest.mark.parametrize("skip", [0, 3], ids=["aligned", "odd"])
 def test_against_exact(lz, n, L, skip):
     x = np.random.default_rng(n + L).integers(0, 256, n + skip, dtype=np.uint8)
