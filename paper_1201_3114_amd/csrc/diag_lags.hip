@@ -399,7 +399,7 @@ constexpr uint32_t LW_ROWS = 1024;
 constexpr int LW_WG = 512;
 constexpr uint32_t LW_IT = 4;                                 // tiles per item
 constexpr uint32_t LW_WINDOW = 4096;                          // lags per window at most
-constexpr uint32_t LW_LEAST = 256;                            // lags per window at least, when split for more workgroups
+constexpr uint32_t LW_LEAST = 64;  // lags per window at least, when split for more workgroups (256: 1 to 1.5 us slower to 100 kB)
 constexpr uint32_t LW_MAX_NT = LW_WINDOW / 32 + 1;            // 129 tiles
 constexpr uint32_t LW_MAX_F = (LW_MAX_NT + 3) / 4;            // tiles of one residue mod 4
 // B bytes read by an item at f0 (a multiple of 4): 4 f0 + 16 h + up to 32 past the row block
@@ -710,7 +710,7 @@ int lag_sums(lz_ctx *c, const uint8_t *d_data, size_t n, uint32_t max_lag, unsig
         }
         // windows of at most LW_WINDOW lags, as even as 32-lag steps allow; of fewer, LW_LEAST at least, where the
         // tasks alone leave compute units idle.  All in one launch: with one after the other and LW_WINDOW lags each,
-        // 16384 lags of 20 kB took 160 us, now 21.5; of 1 MiB 161 and 35, of 16 MiB 336 and 309; 1000 lags of 100 kB 30.4 and 23.7
+        // 16384 lags of 20 kB took 160 us, now 19.9; of 1 MiB 161 and 34, of 16 MiB 336 and 309; 1000 lags of 100 kB 30.4 and 22.1
         if (int rc = grid(reinterpret_cast<const void *>(&lagsum_wide_kernel), LW_WG,
                           ((n + 31) / 32 + LW_ROWS - 1) / LW_ROWS, &blocks))
             return rc;
