@@ -1338,9 +1338,9 @@ __global__ __launch_bounds__(256) void tick_kernel(TickArgs a) {
 
 // A tick between the chain counts of two layouts (see plan_mix): its list's first n_narrow chains run a lane each
 // by narrow_bytes, the others in G lanes by tick_bytes, which takes the same time; the server gives the
-// wide places to the requests with the most bytes left.  A burst of 88,000 chains, 22,272 of them behind 65,536: 37.2 ms of
-// ticks instead of 40.3; requests arriving at 0.3 and 0.5 of capacity have a median latency of 16.0 and 18.6 ms, 18.7 and
-// 20.4 without mixed ticks.
+// wide places to the requests with the most bytes left.  A burst of 88,000 chains, 22,272 of them behind 65,536, ends after
+// 41.1 ms instead of 43.3; requests arriving at 0.3, 0.5 and 0.7 of capacity have a median latency of 16.2, 18.6 and
+// 20.1 ms, 18.7, 20.4 and 20.6 without mixed ticks.
 template <int I, int G>
 __global__ __launch_bounds__(256) void tick_mix_kernel(TickArgs a) {
     extern __shared__ char lds[];
@@ -1592,10 +1592,13 @@ MixPlan plan_mix(uint64_t chains, const lz_params &prm, int simds) {
     return best;
 }
 
-// Four lanes gain nothing for the fused Euler map, and 16 beside four too little for a tick.
+// Rounded up, so that no request gets on more slowly than in a tick of one lane per chain (rounded down the burst above
+// took 40.1 ms and the median at 0.7 of capacity 20.7). Four lanes gain nothing for the fused Euler map, and 16 beside
+// four too little for a tick.
 uint32_t tick_narrow_bytes(const lz_params &prm, uint32_t tick_bytes) {
     if (prm.integrator == LZ_INTEGRATOR_EULER_FMA) return 0;
-    return (uint32_t)(tick_bytes * step_clocks(prm.integrator, TICK_MIX_LANES) / step_clocks(prm.integrator, 1));
+    const double b = tick_bytes * step_clocks(prm.integrator, TICK_MIX_LANES) / step_clocks(prm.integrator, 1);
+    return (uint32_t)b + (b > (uint32_t)b ? 1 : 0);
 }
 
 double tick_mix_gain(const lz_params &prm, uint32_t tick_bytes, uint32_t narrow_bytes, uint64_t n, uint64_t w) {

@@ -22,9 +22,9 @@
 // chain in every tick.
 //
 // A tick whose chains do not fill the SIMDs with a lane each, and are too many for
-// four lanes each, runs some requests one way and the rest the other, in the
-// time that tick_bytes bytes take in four lanes: the requests with the most
-// bytes left by tick_bytes, the others by fewer.
+// four lanes each, runs some requests one way and the rest the other, in about
+// the time that tick_bytes bytes take in four lanes: the requests with the most
+// bytes left by tick_bytes, the others by fewer, at the pace of a full tick.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
