@@ -778,31 +778,36 @@ struct BluFft {
     }
 
     // v[j] = x[t + T j] -> v[i R + d] = X[i T + t + 256 d].  Each stage's twiddles are loaded before its
-    // DFTs; TW gives them (BluTable from memory, or computed).
+    // DFTs; TW gives them (BluTable from memory, or computed).  Every thread of the workgroup calls it, for its barriers;
+    // one that is not live leaves L alone.
     template <typename TW>
     static __device__ __forceinline__ void forward(double2 (&v)[16], uint32_t t, double2 *L, const TW &tw,
-                                                   double2 (&wa)[16]) {
+                                                   double2 (&wa)[16], bool live = true) {
         double2 w[16];
 #pragma unroll
         for (int k1 = 1; k1 < 16; ++k1) wa[k1] = tw.a(k1, t);
         dft16(v, -1.0);
+        if (live)
 #pragma unroll
-        for (int k1 = 0; k1 < 16; ++k1) L[k1 * S1 + t] = k1 ? cmul(v[k1], wa[k1]) : v[0];
+            for (int k1 = 0; k1 < 16; ++k1) L[k1 * S1 + t] = k1 ? cmul(v[k1], wa[k1]) : v[0];
         const uint32_t k1 = t / R, a = t % R;
 #pragma unroll
         for (int c = 1; c < 16; ++c) w[c] = tw.b(a, c);
         __syncthreads();
+        if (live)
 #pragma unroll
-        for (int b = 0; b < 16; ++b) v[b] = L[k1 * S1 + a + R * b];
+            for (int b = 0; b < 16; ++b) v[b] = L[k1 * S1 + a + R * b];
         __syncthreads();
         dft16(v, -1.0);
+        if (live)
 #pragma unroll
-        for (int c = 0; c < 16; ++c) L[a * S2 + 16 * c + k1] = c ? cmul(v[c], w[c]) : v[0];
+            for (int c = 0; c < 16; ++c) L[a * S2 + 16 * c + k1] = c ? cmul(v[c], w[c]) : v[0];
         __syncthreads();
 #pragma unroll
         for (int i = 0; i < 16 / R; ++i) {
+            if (live)
 #pragma unroll
-            for (int a2 = 0; a2 < R; ++a2) v[i * R + a2] = L[a2 * S2 + i * T + t];
+                for (int a2 = 0; a2 < R; ++a2) v[i * R + a2] = L[a2 * S2 + i * T + t];
             dft_r(&v[i * R], -1.0);
         }
     }
@@ -896,21 +901,15 @@ __device__ __forceinline__ void blu_tables(double2 *p, uint32_t N, uint32_t part
         const uint32_t n = t + F::T * j, m = n < N ? n : F::M - n;  // b is even
         v[j] = t < F::T && m < N ? conj2(cl[m]) : make_double2(0.0, 0.0);
     }
-    // the threads past the column have no place in L: they take part in the barriers alone
-    if (t < F::T) {
-        double2 wa[16];
-        F::forward(v, t, lds, typename F::Quarter{q}, wa);
+    // the threads past the column take part in the barriers, all of them outside any branch, and have no place in L
+    double2 wa[16];
+    F::forward(v, t, lds, typename F::Quarter{q}, wa, t < F::T);
+    if (t >= F::T) return;
 #pragma unroll
-        for (int i = 0; i < 16 / R; ++i)
+    for (int i = 0; i < 16 / R; ++i)
 #pragma unroll
-            for (int d = 0; d < R; ++d)
-                tab.b[i * F::T + t + 256 * d] =
-                    make_double2(v[i * R + d].x * (1.0 / F::M), v[i * R + d].y * (1.0 / F::M));
-    } else {
-        __syncthreads();
-        __syncthreads();
-        __syncthreads();
-    }
+        for (int d = 0; d < R; ++d)
+            tab.b[i * F::T + t + 256 * d] = make_double2(v[i * R + d].x * (1.0 / F::M), v[i * R + d].y * (1.0 / F::M));
 }
 
 __host__ __device__ constexpr size_t blu_table_lds(uint32_t N) {
