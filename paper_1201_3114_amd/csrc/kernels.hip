@@ -115,30 +115,43 @@ __device__ __forceinline__ void step(double &x, double &y, double &z, double dt,
     else euler_step(x, y, z, dt);
 }
 
-// A counted loop of STEP: %[q] + 1 iterations of U steps (none if %[q] is -1), then %[r] single steps.  A
-// wave alone on its SIMD pays four clocks for each scalar instruction too: U = 120 (a divisor of the default
-// 3000; 8 to 13 KB of code) and two scalar instructions an iteration, instead of 60 and three, are 0.3% at four waves
-// per SIMD; 20 steps an iteration cost 2%.
-#define LZ_STEP_LOOP(U, STEP)                                                  \
+// A counted loop of STEP (N instructions, 8 bytes each), U steps an iteration and %[q] + 1 iterations, none if %[q]
+// is -1.  The first iteration is entered %[at] bytes on, where the steps are left to run that U does not divide.  A wave
+// alone on its SIMD pays four clocks for each scalar instruction too: U = 120 (8 to 13 KB of code) and two scalar
+// instructions an iteration, instead of 60 and three, are 0.3% at four waves per SIMD; 20 steps an iteration
+// cost 2%.  With the entry every step count costs its steps: 16 MiB at 100 steps a byte take 0.91 ms (fused map
+// 0.70), 1.25 (1.03) with the remainder in a loop of single steps, 0.94 (0.73) in one of twelve.
+#define LZ_STEP_LOOP(U, N, STEP)                                               \
     "s_nop 4\n"                                                                \
     "s_cmp_lt_i32 %[q], 0\n"                                                   \
-    "s_cbranch_scc1 2f\n"                                                      \
-    ".p2align 6\n"                                                             \
-    "1:\n"                                                                     \
-    ".rept " #U "\n" STEP ".endr\n"                                            \
-    "s_sub_u32 %[q], %[q], 1\n"                                                \
-    "s_cbranch_scc0 1b\n"                                                      \
-    "2:\n"                                                                     \
-    "s_cmp_eq_u32 %[r], 0\n"                                                   \
     "s_cbranch_scc1 4f\n"                                                      \
+    "s_getpc_b64 s[40:41]\n"                                                   \
+    "1:\n"                                                                     \
+    "s_add_u32 s40, s40, %[at]\n"                                              \
+    "s_addc_u32 s41, s41, 0\n"                                                 \
+    "s_add_u32 s40, s40, 2f-1b\n"                                              \
+    "s_addc_u32 s41, s41, 0\n"                                                 \
+    "s_setpc_b64 s[40:41]\n"                                                   \
     ".p2align 6\n"                                                             \
-    "3:\n" STEP                                                                \
-    "s_sub_u32 %[r], %[r], 1\n"                                                \
-    "s_cmp_lg_u32 %[r], 0\n"                                                   \
-    "s_cbranch_scc1 3b\n"                                                      \
+    "2:\n"                                                                     \
+    ".rept " #U "\n" STEP ".endr\n"                                            \
+    "3:\n"                                                                     \
+    ".if (3b - 2b) != " #U " * " #N " * 8\n"                                   \
+    ".error \"a step of another length\"\n"                                    \
+    ".endif\n"                                                                 \
+    "s_sub_u32 %[q], %[q], 1\n"                                                \
+    "s_cbranch_scc0 2b\n"                                                      \
     "4:\n"                                                                     \
     "s_nop 1\n"
-constexpr uint32_t STEP_U = 120, RK4_U = 60;  // RK4: 22 KB, a step is 47 instructions
+#define LZ_STEP_CLOBBER "scc", "s40", "s41"
+constexpr uint32_t STEP_U = 120, RK4_U = 60;  // RK4: 22 KB, a step is 43 or 47 instructions
+
+// The operands for n_it steps of n instructions, u an iteration.
+struct StepCount {
+    uint32_t q, at;
+    __device__ StepCount(uint32_t n_it, uint32_t u, uint32_t n)
+        : q(n_it / u + (n_it % u != 0) - 1), at(n_it % u ? (u - n_it % u) * n * 8 : 0) {}
+};
 
 // F^(n_it) of one chain per lane, for the two Euler maps: the instructions of euler_step and euler_fma_step in
 // an order of our own.  With all SIMDs busy the part's power decides the clock, and the order of a step's
@@ -151,9 +164,9 @@ constexpr uint32_t STEP_U = 120, RK4_U = 60;  // RK4: 22 KB, a step is 47 instru
 template <int I>
 __device__ __forceinline__ void lane_steps(double &x, double &y, double &z, double dt, uint32_t n_it) {
     double d, e, f, g;
-    uint32_t q = n_it / STEP_U - 1, r = n_it % STEP_U;
+    StepCount n(n_it, STEP_U, I == LZ_INTEGRATOR_EULER_FMA ? 9 : 14);
     if constexpr (I == LZ_INTEGRATOR_EULER_FMA) {
-        asm volatile(LZ_STEP_LOOP(120,
+        asm volatile(LZ_STEP_LOOP(120, 9,
                          "v_add_f64 %[e], -%[z], %[rho]\n"
                          "v_add_f64 %[d], %[y], -%[x]\n"
                          "v_mul_f64 %[d], %[d], %[sigma]\n"
@@ -164,12 +177,12 @@ __device__ __forceinline__ void lane_steps(double &x, double &y, double &z, doub
                          "v_fma_f64 %[y], %[dt], %[e], %[y]\n"
                          "v_fma_f64 %[z], %[dt], %[f], %[z]\n")
                      : [x] "+v"(x), [y] "+v"(y), [z] "+v"(z), [d] "=&v"(d), [e] "=&v"(e), [f] "=&v"(f), [g] "=&v"(g),
-                       [q] "+s"(q), [r] "+s"(r)
-                     : [dt] "s"(dt), [sigma] "s"(SIGMA), [rho] "s"(RHO), [beta] "s"(BETA)
-                     : "scc");
+                       [q] "+s"(n.q)
+                     : [at] "s"(n.at), [dt] "s"(dt), [sigma] "s"(SIGMA), [rho] "s"(RHO), [beta] "s"(BETA)
+                     : LZ_STEP_CLOBBER);
     } else {
         static_assert(I == LZ_INTEGRATOR_EULER, "the two Euler maps");
-        asm volatile(LZ_STEP_LOOP(120,
+        asm volatile(LZ_STEP_LOOP(120, 14,
                          "v_add_f64 %[e], -%[z], %[rho]\n"
                          "v_add_f64 %[d], %[y], -%[x]\n"
                          "v_mul_f64 %[f], %[x], %[y]\n"
@@ -185,9 +198,9 @@ __device__ __forceinline__ void lane_steps(double &x, double &y, double &z, doub
                          "v_add_f64 %[y], %[y], %[e]\n"
                          "v_add_f64 %[z], %[z], %[f]\n")
                      : [x] "+v"(x), [y] "+v"(y), [z] "+v"(z), [d] "=&v"(d), [e] "=&v"(e), [f] "=&v"(f), [g] "=&v"(g),
-                       [q] "+s"(q), [r] "+s"(r)
-                     : [dt] "s"(dt), [sigma] "s"(SIGMA), [rho] "s"(RHO), [beta] "s"(BETA)
-                     : "scc");
+                       [q] "+s"(n.q)
+                     : [at] "s"(n.at), [dt] "s"(dt), [sigma] "s"(SIGMA), [rho] "s"(RHO), [beta] "s"(BETA)
+                     : LZ_STEP_CLOBBER);
     }
 }
 
@@ -294,14 +307,14 @@ __device__ __forceinline__ void quad_steps(double &x, double &y, double &z, doub
     const int lr = lane & 3;
     double v = lr == 0 ? x : (lr == 1 ? y : (lr == 2 ? z : SIGMA));
     constexpr uint32_t U = I == LZ_INTEGRATOR_RK4 ? RK4_U : STEP_U;
-    uint32_t q = n_it / U - 1, r = n_it % U;
+    StepCount n(n_it, U, I == LZ_INTEGRATOR_RK4 ? 47 : 11);
     double q0, u, t, p1, p2;
     if constexpr (I == LZ_INTEGRATOR_RK4) {
         // the field four times (9 instructions each) and the 11 operations of rk4_step between them:
         // 47 instructions a step against 65
         const double h2 = dt * 0.5, h6 = dt / 6.0;
         double a, b, d, w;
-        asm volatile(LZ_STEP_LOOP(60,
+        asm volatile(LZ_STEP_LOOP(60, 47,
                          LZ_QUAD_FIELD("56", "57", "%[a]")
                          "v_mul_f64 v[58:59], %[a], %[h2]\n"
                          "v_add_f64 v[58:59], v[56:57], v[58:59]\n"
@@ -318,20 +331,20 @@ __device__ __forceinline__ void quad_steps(double &x, double &y, double &z, doub
                          "v_mul_f64 %[a], %[a], %[h6]\n"
                          "v_add_f64 v[56:57], v[56:57], %[a]\n")
                      : "+{v[56:57]}"(v), "=&{v[58:59]}"(w), "=&{v[60:61]}"(p1), "=&{v[62:63]}"(p2), [q0] "=&v"(q0),
-                       [u] "=&v"(u), [t] "=&v"(t), [a] "=&v"(a), [b] "=&v"(b), [d] "=&v"(d), [q] "+s"(q), [r] "+s"(r)
-                     : [m] "v"(role.m), [c] "v"(role.c), [k] "v"(role.k), [s] "v"(role.s), [dt] "s"(dt), [h2] "v"(h2),
+                       [u] "=&v"(u), [t] "=&v"(t), [a] "=&v"(a), [b] "=&v"(b), [d] "=&v"(d), [q] "+s"(n.q)
+                     : [at] "s"(n.at), [m] "v"(role.m), [c] "v"(role.c), [k] "v"(role.k), [s] "v"(role.s), [dt] "s"(dt), [h2] "v"(h2),
                        [h6] "v"(h6)
-                     : "scc");
+                     : LZ_STEP_CLOBBER);
     } else {
         static_assert(I == LZ_INTEGRATOR_EULER, "the quad form of this integrator is no shorter than the one-lane form");
-        asm volatile(LZ_STEP_LOOP(120,
+        asm volatile(LZ_STEP_LOOP(120, 11,
                          LZ_QUAD_FIELD("56", "57", "%[t]")
                          "v_mul_f64 %[t], %[t], %[dt]\n"
                          "v_add_f64 v[56:57], v[56:57], %[t]\n")
                      : "+{v[56:57]}"(v), "=&{v[60:61]}"(p1), "=&{v[62:63]}"(p2), [q0] "=&v"(q0), [u] "=&v"(u),
-                       [t] "=&v"(t), [q] "+s"(q), [r] "+s"(r)
-                     : [m] "v"(role.m), [c] "v"(role.c), [k] "v"(role.k), [s] "v"(role.s), [dt] "s"(dt)
-                     : "scc");
+                       [t] "=&v"(t), [q] "+s"(n.q)
+                     : [at] "s"(n.at), [m] "v"(role.m), [c] "v"(role.c), [k] "v"(role.k), [s] "v"(role.s), [dt] "s"(dt)
+                     : LZ_STEP_CLOBBER);
     }
     x = dpp_f64<0x00>(v);  // quad_perm [0,0,0,0], [1,1,1,1], [2,2,2,2]
     y = dpp_f64<0x55>(v);
@@ -382,8 +395,8 @@ __device__ __forceinline__ void row_steps(double &x, double &y, double &z, doubl
     if constexpr (I == LZ_INTEGRATOR_RK4) {
         const double h2 = dt * 0.5, h6 = dt / 6.0, c = r == 1 ? RHO : 0.0;
         double p1 = 0.0, p2 = r == 0 ? SIGMA : 0.0, q0, u, a, b, d, e, v;
-        uint32_t q = n_it / RK4_U - 1, rest = n_it % RK4_U;
-        asm volatile(LZ_STEP_LOOP(60,
+        StepCount n(n_it, RK4_U, 43);
+        asm volatile(LZ_STEP_LOOP(60, 43,
                          LZ_ROW_FIELD("%[w]", "%[a]")
                          "v_mul_f64 %[v], %[a], %[h2]\n"
                          "v_add_f64 %[v], %[w], %[v]\n"
@@ -400,9 +413,9 @@ __device__ __forceinline__ void row_steps(double &x, double &y, double &z, doubl
                          "v_mul_f64 %[a], %[a], %[h6]\n"
                          "v_add_f64 %[w], %[w], %[a]\n")
                      : [w] "+v"(w), [p1] "+v"(p1), [p2] "+v"(p2), [q0] "=&v"(q0), [u] "=&v"(u), [a] "=&v"(a), [b] "=&v"(b),
-                       [d] "=&v"(d), [e] "=&v"(e), [v] "=&v"(v), [q] "+s"(q), [r] "+s"(rest)
-                     : [m] "v"(role.m), [c] "v"(c), [k] "v"(role.k), [s] "v"(role.s), [dt] "v"(dt), [h2] "v"(h2), [h6] "v"(h6)
-                     : "scc");
+                       [d] "=&v"(d), [e] "=&v"(e), [v] "=&v"(v), [q] "+s"(n.q)
+                     : [at] "s"(n.at), [m] "v"(role.m), [c] "v"(c), [k] "v"(role.k), [s] "v"(role.s), [dt] "v"(dt), [h2] "v"(h2), [h6] "v"(h6)
+                     : LZ_STEP_CLOBBER);
         x = dpp_f64<0x150>(w);  // row_newbcast of lanes 0, 4, 8
         y = dpp_f64<0x154>(w);
         z = dpp_f64<0x158>(w);
@@ -412,10 +425,10 @@ __device__ __forceinline__ void row_steps(double &x, double &y, double &z, doubl
     double c = r == 0 ? SIGMA : (r == 3 ? 0.0 : x);
     double s2 = r == 0 ? -x : (r == 1 ? RHO : 0.0);
     double u = role.k * w, t;
-    uint32_t q = n_it / STEP_U - 1, rest = n_it % STEP_U;
+    StepCount n(n_it, STEP_U, I == LZ_INTEGRATOR_EULER_FMA ? 8 : 10);
     if constexpr (I == LZ_INTEGRATOR_EULER_FMA) {
         const double dtv = dt, mdt = role.m * dt;
-        asm volatile(LZ_STEP_LOOP(120,
+        asm volatile(LZ_STEP_LOOP(120, 8,
                          "v_fma_f64 %[t], %[s], %[s1], %[s2]\n"
                          "v_fma_f64 %[t], %[t], %[c], -%[u]\n"
                          "v_fma_f64 %[w], %[dt], %[t], %[w]\n"
@@ -424,12 +437,11 @@ __device__ __forceinline__ void row_steps(double &x, double &y, double &z, doubl
                          "v_fmac_f64_dpp %[c], %[t], %[dt] row_newbcast:0 row_mask:0xf bank_mask:0x6\n"
                          "v_mul_f64 %[u], %[k], %[w]\n"
                          "v_fmac_f64_dpp %[s1], %[t], %[dt] row_newbcast:8 row_mask:0xf bank_mask:0x2\n")
-                     : [w] "+v"(w), [s1] "+v"(s1), [c] "+v"(c), [s2] "+v"(s2), [u] "+v"(u), [t] "=&v"(t), [q] "+s"(q),
-                       [r] "+s"(rest)
-                     : [k] "v"(role.k), [s] "v"(role.s), [dt] "v"(dtv), [mdt] "v"(mdt)
-                     : "scc");
+                     : [w] "+v"(w), [s1] "+v"(s1), [c] "+v"(c), [s2] "+v"(s2), [u] "+v"(u), [t] "=&v"(t), [q] "+s"(n.q)
+                     : [at] "s"(n.at), [k] "v"(role.k), [s] "v"(role.s), [dt] "v"(dtv), [mdt] "v"(mdt)
+                     : LZ_STEP_CLOBBER);
     } else {
-        asm volatile(LZ_STEP_LOOP(120,
+        asm volatile(LZ_STEP_LOOP(120, 10,
                          "v_fma_f64 %[t], %[s], %[s1], %[s2]\n"
                          "v_mul_f64 %[t], %[t], %[c]\n"
                          "v_add_f64 %[t], %[t], -%[u]\n"
@@ -440,10 +452,9 @@ __device__ __forceinline__ void row_steps(double &x, double &y, double &z, doubl
                          "v_fmac_f64_dpp %[c], %[t], %[one] row_newbcast:0 row_mask:0xf bank_mask:0x6\n"
                          "v_mul_f64 %[u], %[k], %[w]\n"
                          "v_fmac_f64_dpp %[s1], %[t], %[one] row_newbcast:8 row_mask:0xf bank_mask:0x2\n")
-                     : [w] "+v"(w), [s1] "+v"(s1), [c] "+v"(c), [s2] "+v"(s2), [u] "+v"(u), [t] "=&v"(t), [q] "+s"(q),
-                       [r] "+s"(rest)
-                     : [k] "v"(role.k), [s] "v"(role.s), [m] "v"(role.m), [one] "v"(role.one), [dt] "s"(dt)
-                     : "scc");
+                     : [w] "+v"(w), [s1] "+v"(s1), [c] "+v"(c), [s2] "+v"(s2), [u] "+v"(u), [t] "=&v"(t), [q] "+s"(n.q)
+                     : [at] "s"(n.at), [k] "v"(role.k), [s] "v"(role.s), [m] "v"(role.m), [one] "v"(role.one), [dt] "s"(dt)
+                     : LZ_STEP_CLOBBER);
     }
     x = dpp_f64<0x150>(w);  // row_newbcast of lanes 0, 4, 8
     y = dpp_f64<0x154>(w);
