@@ -522,6 +522,13 @@ int lz_unit_theta(lz_ctx *ctx, const uint8_t *d_p, const uint8_t *d_omega3, size
  * (Section 3.1; the loop of Step 2).  n <= 2^31. */
 int lz_unit_lorenz(lz_ctx *ctx, double *d_r, size_t n, uint32_t steps, void *stream);
 
+/* lz_unit_waves: *waves = the waves of cipher kernels in flight on the
+ * context's device, all contexts of the process together, by which a launch
+ * decides how many lanes to give a chain: those running and those that a
+ * queued launch has claimed.  0 when the device has nothing to do.  Waits for
+ * the work queued on stream. */
+int lz_unit_waves(lz_ctx *ctx, uint32_t *waves, void *stream);
+
 /* CLOCK_MONOTONIC now, in ns (the clock of arrival_ns and done_ns). */
 uint64_t lz_now_ns(void);
 

@@ -470,5 +470,12 @@ def unit_lorenz(ctx: Context, r: torch.Tensor, steps: int, stream=None) -> torch
     return r
 
 
+def unit_waves(ctx: Context, stream=None) -> int:
+    """Waves of cipher kernels in flight on the device (running or claimed), after the work queued on the stream."""
+    waves = ctypes.c_uint32()
+    check(B.lib.lz_unit_waves(ctx.handle, ctypes.byref(waves), _stream(stream, ctx.device)))
+    return waves.value
+
+
 def now_ns() -> int:
     return int(B.lib.lz_now_ns())

@@ -222,6 +222,9 @@ hipError_t launch_copy_many(const CopyPiece *pieces, uint32_t n, hipStream_t s);
 constexpr uint32_t COPY_ARG_PIECES = 144;  // with the implicit arguments, under 4 KB of kernel arguments
 hipError_t launch_copy_pieces_host(const CopyPiece *pieces, uint32_t n, hipStream_t s);
 
+// The device's count of waves in flight (those of claimed launches that still have to run among them), once s gets to it.
+hipError_t read_waves(uint32_t *waves, hipStream_t s);
+
 // The method's scalar pieces over device arrays (R, Theta, F^steps), for checking.
 hipError_t launch_unit_r(const double *alpha, const uint8_t *om, size_t n, uint8_t *out, hipStream_t s);
 hipError_t launch_unit_theta(const uint8_t *p, const uint8_t *o3, size_t n, double *out, hipStream_t s);

@@ -684,6 +684,9 @@ __global__ void claim_kernel(unsigned long long *p, size_t n, unsigned long long
     if (t == 0) *wide = atomicAdd(&g_waves, waves) + waves <= simds ? 1 : 0;
 }
 
+// Takes off the waves of a launch that was claimed for and then refused.
+__global__ void give_back_kernel(uint32_t waves) { atomicSub(&g_waves, waves); }
+
 // ---- plain path: one message ---------------------------------------------------------
 
 struct PlainArgs {
@@ -1675,6 +1678,14 @@ hipError_t launch_claim(const KernelShape &sh, uint64_t grid, unsigned long long
     return hipGetLastError();
 }
 
+// After `refused`, the error of a launch whose waves a claim on the stream counts: takes them off, or they would keep
+// later launches of the process narrow.
+hipError_t give_back(hipError_t refused, const KernelShape &sh, uint64_t grid, hipStream_t s) {
+    hipLaunchKernelGGL(give_back_kernel, dim3(1), dim3(1), 0, s, (uint32_t)(grid * sh.wg / WAVE));
+    (void)hipGetLastError();
+    return refused;
+}
+
 // The rounds of a segment plan: launch(grid, lds, first) starts one.
 template <typename F>
 hipError_t seg_rounds(const KernelShape &sh, const SegPlan &p, F launch) {
@@ -1705,7 +1716,8 @@ hipError_t mix_rounds(const KernelShape &shape, uint32_t integ, const MixPlan &p
     const uint32_t waves = plan.a + (plan.units - plan.a) * (plan.gb / plan.ga), wpw = sh.wg / WAVE;
     const unsigned grid = (waves + wpw - 1) / wpw;
     hipError_t e = launch_claim(sh, grid, p, n, wide, s);
-    for (uint32_t r = 0; r < plan.rounds && e == hipSuccess; ++r) {
+    if (e != hipSuccess) return e;
+    for (uint32_t r = 0; r < plan.rounds; ++r) {
         auto run = [&](auto ic, auto ac, auto bc) {
             launch(ic, ac, bc, sh, grid, r);
             return hipGetLastError();
@@ -1715,8 +1727,9 @@ hipError_t mix_rounds(const KernelShape &shape, uint32_t integ, const MixPlan &p
         else if (integ == LZ_INTEGRATOR_EULER_FMA) e = run(Int<1>{}, Int<1>{}, Int<16>{});
         else if (plan.ga == 1) e = run(Int<2>{}, Int<1>{}, Int<4>{});
         else e = run(Int<2>{}, Int<4>{}, Int<16>{});
+        if (e != hipSuccess) return r == 0 ? give_back(e, sh, grid, s) : e;
     }
-    return e;
+    return hipSuccess;
 }
 
 template <bool X>
@@ -1750,7 +1763,7 @@ hipError_t launch_plain(const KernelShape &sh, const lz_key &key, const lz_param
             hipLaunchKernelGGL((plain_kernel<M, I, false, G>), dim3((unsigned)grid), dim3(sh.wg), lds_bytes(sh), s, a);
             return hipGetLastError();
         });
-        if (e != hipSuccess) return e;
+        if (e != hipSuccess) return sh.g > 1 ? give_back(e, sh, grid, s) : e;
     }
     if (!plan.waves) return hipSuccess;
     KernelShape ss = sh;
@@ -1783,12 +1796,13 @@ hipError_t launch_stream_step(const KernelShape &shape, const lz_key &key, const
         if (e != hipSuccess) return e;
     }
     const size_t lds = lds_bytes(sh);
-    return dispatch(1, sh.g, prm.integrator, [&](auto, auto ic, auto gc) {
+    const hipError_t e = dispatch(1, sh.g, prm.integrator, [&](auto, auto ic, auto gc) {
         constexpr int I = decltype(ic)::value;
         constexpr int G = decltype(gc)::value;
         hipLaunchKernelGGL((plain_kernel<1, I, true, G>), dim3((unsigned)grid), dim3(sh.wg), lds, s, a);
         return hipGetLastError();
     });
+    return e != hipSuccess && sh.g > 1 ? give_back(e, sh, grid, s) : e;
 }
 
 hipError_t launch_plain_finalize(int decrypt, const unsigned long long *tag_acc, const uint8_t *stored_tag,
@@ -1837,7 +1851,7 @@ hipError_t launch_batch(const KernelShape &sh, const DevInfo &dev, const lz_para
             hipLaunchKernelGGL((batch_kernel<M, I, G>), dim3((unsigned)grid), dim3(sh.wg), lds_bytes(sh), s, a);
             return hipGetLastError();
         });
-        if (e != hipSuccess) return e;
+        if (e != hipSuccess) return sh.g > 1 ? give_back(e, sh, grid, s) : e;
     }
     if (!plan.waves) return hipSuccess;
     KernelShape ss = sh;
@@ -1889,6 +1903,11 @@ hipError_t launch_tick(const KernelShape &sh, const lz_params &prm, const TickDe
         hipLaunchKernelGGL((tick_kernel<M, I, G>), dim3((unsigned)grid), dim3(sh.wg), lds, s, a);
         return hipGetLastError();
     });
+}
+
+hipError_t read_waves(uint32_t *waves, hipStream_t s) {
+    const hipError_t e = hipMemcpyFromSymbolAsync(waves, HIP_SYMBOL(g_waves), sizeof *waves, 0, hipMemcpyDeviceToHost, s);
+    return e == hipSuccess ? hipStreamSynchronize(s) : e;
 }
 
 hipError_t launch_unit_r(const double *alpha, const uint8_t *om, size_t n, uint8_t *out, hipStream_t s) {

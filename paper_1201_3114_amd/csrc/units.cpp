@@ -1,7 +1,7 @@
 // The method's scalar pieces as entry points of their own: R (Eq. R_nu), Theta
 // (Step 2) and the iterated map F (Section 3.1, Step 2), each evaluated by the
 // same device code as the cipher kernels, so that each can be checked on its
-// own against a reference.
+// own against a reference; and what the launches decide by (the waves in flight).
 #include <hip/hip_runtime.h>
 
 #include "internal.h"
@@ -32,5 +32,12 @@ extern "C" int lz_unit_lorenz(lz_ctx *c, double *d_r, size_t n, uint32_t steps, 
     if (n == 0) return LZ_OK;
     LZ_HIP(hipSetDevice(c->device));
     LZ_HIP(launch_unit_lorenz(c->prm, d_r, n, steps, (hipStream_t)stream));
+    return LZ_OK;
+}
+
+extern "C" int lz_unit_waves(lz_ctx *c, uint32_t *waves, void *stream) {
+    if (!c || !waves) return fail(LZ_E_INVAL, "NULL argument");
+    LZ_HIP(hipSetDevice(c->device));
+    LZ_HIP(read_waves(waves, (hipStream_t)stream));
     return LZ_OK;
 }
