@@ -668,7 +668,8 @@ __device__ __forceinline__ void wave_run(Chains<M> &c, const WaveLds &w, int til
 // its waves to the device's count of waves in flight and lets it run wide if all of them together are
 // at most one per SIMD; otherwise the launch runs one chain per lane (the waves it then does not need
 // end at once).  Calls that overlap on several streams so take the idle SIMDs first and then run as
-// densely as before, whatever runs beside them: every kernel of the cipher counts its waves.
+// densely as before, whatever runs beside them: every kernel of the cipher counts its waves, and a call of several
+// rounds holds its claim from before the first to the end of the last.
 __device__ uint32_t g_waves;
 
 // Adds the waves of a workgroup that no claim counted (n > 0) or takes them off at its end (n < 0).
@@ -685,7 +686,9 @@ __global__ void claim_kernel(unsigned long long *p, size_t n, unsigned long long
 }
 
 // Takes off the waves of a launch that was claimed for and then refused.
-__global__ void give_back_kernel(uint32_t waves) { atomicSub(&g_waves, waves); }
+__global__ void give_back_kernel(uint32_t waves, const unsigned long long *wide) {
+    if (!wide || *wide) atomicSub(&g_waves, waves);
+}
 
 // ---- plain path: one message ---------------------------------------------------------
 
@@ -812,6 +815,12 @@ __global__ __launch_bounds__(256) void plain_kernel(PlainArgs a) {
     count_waves(-waves);
 }
 
+// The rounds' waves are counted by a claim before the launch that comes first, to the end of the last round.
+__device__ __forceinline__ void seg_done(const SegPlan &p, uint64_t first) {
+    const int waves = blockDim.x / WAVE;
+    if (first + (uint64_t)gridDim.x * waves >= p.off[p.segs]) count_waves(-waves);
+}
+
 // One round of a segment plan (see plan_segments): each wave advances 64 chains by one segment of
 // seg_len bytes from the checkpoint that an earlier round left.  The round's waves are tasks
 // first, first + 1, ... of the plan; task off[s] + w is segment s of wave w.
@@ -866,7 +875,6 @@ template <int I>
 __global__ __launch_bounds__(256) void plain_seg_kernel(PlainArgs a, SegPlan p, uint64_t first) {
     extern __shared__ char lds[];
     const int lane = threadIdx.x % WAVE;
-    count_waves(blockDim.x / WAVE);
     uint32_t seg, wave;
     if (seg_task(p, first, seg, wave)) {
         const WaveLds w = wave_lds<WAVE>(lds + (size_t)(threadIdx.x / WAVE) * wave_lds_bytes(WAVE, a.tile), a.tile);
@@ -892,7 +900,7 @@ __global__ __launch_bounds__(256) void plain_seg_kernel(PlainArgs a, SegPlan p, 
             }
         }
     }
-    count_waves(-(int)(blockDim.x / WAVE));
+    seg_done(p, first);
 }
 
 // The byte that a unit of a mix plan starts a round at: it has run n times in GA lanes before round r, n the
@@ -976,13 +984,13 @@ __device__ __forceinline__ void mix_body(const PlainArgs &a, const MixPlan &p, u
 }
 
 // Waves 0 .. p.a - 1 take the round's units in GA lanes, the others the rest of the units in GB, GB / GA waves a
-// unit: body(lanes, unit, first chain of the unit, bytes).  Without room on the device (claim_kernel) the first round
-// runs everything, one chain per lane: all().
+// unit: body(lanes, unit, first chain of the unit, bytes).  The claim is held to the end of the last round, or a
+// claim that comes between two rounds would be granted the SIMDs that the next one takes.  Without room on the device (claim_kernel) the
+// first round runs everything, one chain per lane: all().
 template <int GA, int GB, class Body, class All>
 __device__ __forceinline__ void mix_round(const MixPlan &p, uint32_t round, uint32_t wide, Body &&body, All &&all) {
     const int waves = blockDim.x / WAVE;
     if (wide) {
-        if (round > 0) count_waves(waves);  // the first round's are claimed
         constexpr uint32_t K = GB / GA;
         const uint32_t v = __builtin_amdgcn_readfirstlane(blockIdx.x * waves + threadIdx.x / WAVE);
         const uint32_t start = (round * p.a) % p.units;
@@ -991,7 +999,7 @@ __device__ __forceinline__ void mix_round(const MixPlan &p, uint32_t round, uint
         } else if ((v - p.a) / K < p.units - p.a) {
             body(std::integral_constant<int, GB>{}, (start + p.a + (v - p.a) / K) % p.units, (v - p.a) % K * (WAVE / GB), p.lb);
         }
-        count_waves(-waves);
+        if (round + 1 == p.rounds) count_waves(-waves);  // claimed for all rounds, which have the same workgroups
     } else if (round == 0) {
         all();
         count_waves(-waves);
@@ -1149,7 +1157,6 @@ template <int I>
 __global__ __launch_bounds__(256) void batch_seg_kernel(BatchArgs a, SegPlan p, uint64_t first) {
     extern __shared__ char lds[];
     const int lane = threadIdx.x % WAVE;
-    count_waves(blockDim.x / WAVE);
     uint32_t seg, wave;
     if (seg_task(p, first, seg, wave)) {
         const WaveLds w = wave_lds<WAVE>(lds + (size_t)(threadIdx.x / WAVE) * wave_lds_bytes(WAVE, a.tile), a.tile);
@@ -1177,7 +1184,7 @@ __global__ __launch_bounds__(256) void batch_seg_kernel(BatchArgs a, SegPlan p, 
             atomicXor(t + 2, d[2]);
         }
     }
-    count_waves(-(int)(blockDim.x / WAVE));
+    seg_done(p, first);
 }
 
 // One round of the batch's mix plan: mix_body over its chains.
@@ -1678,23 +1685,27 @@ hipError_t launch_claim(const KernelShape &sh, uint64_t grid, unsigned long long
     return hipGetLastError();
 }
 
-// After `refused`, the error of a launch whose waves a claim on the stream counts: takes them off, or they would keep
-// later launches of the process narrow.
-hipError_t give_back(hipError_t refused, const KernelShape &sh, uint64_t grid, hipStream_t s) {
-    hipLaunchKernelGGL(give_back_kernel, dim3(1), dim3(1), 0, s, (uint32_t)(grid * sh.wg / WAVE));
+// After `refused`, the error of a launch whose waves are counted before it runs (by a claim on the stream, or by the rounds before
+// it): takes them off, or they would keep later launches of the process narrow.  wide: if the claim was granted (a mix
+// plan's first round has given them back otherwise).
+hipError_t give_back(hipError_t refused, const KernelShape &sh, uint64_t grid, hipStream_t s,
+                     const unsigned long long *wide = nullptr) {
+    hipLaunchKernelGGL(give_back_kernel, dim3(1), dim3(1), 0, s, (uint32_t)(grid * sh.wg / WAVE), wide);
     (void)hipGetLastError();
     return refused;
 }
 
-// The rounds of a segment plan: launch(grid, lds, first) starts one.
+// Workgroups of a round of a segment plan: one wave per SIMD, in whole workgroups, so that round r starts at task
+// r * waves.
+uint64_t seg_grid(const KernelShape &sh) { return (sh.simds + sh.wg / WAVE - 1) / (sh.wg / WAVE); }
+
+// The rounds of a segment plan, whose waves a claim counts: launch(grid, first) starts one.
 template <typename F>
-hipError_t seg_rounds(const KernelShape &sh, const SegPlan &p, F launch) {
-    const uint64_t per_wg = (uint64_t)sh.wg / WAVE;
-    const unsigned grid = (unsigned)((sh.simds + per_wg - 1) / per_wg);
-    // a round's waves are one per SIMD: whole workgroups of it, so that round r starts at task r * waves
-    for (uint64_t first = 0; first < p.off[p.segs]; first += grid * per_wg) {
-        const hipError_t e = launch(grid, first);
-        if (e != hipSuccess) return e;
+hipError_t seg_rounds(const KernelShape &sh, const SegPlan &p, hipStream_t s, F launch) {
+    const uint64_t grid = seg_grid(sh);
+    for (uint64_t first = 0; first < p.off[p.segs]; first += grid * (sh.wg / WAVE)) {
+        const hipError_t e = launch((unsigned)grid, first);
+        if (e != hipSuccess) return give_back(e, sh, grid, s);
     }
     return hipSuccess;
 }
@@ -1727,7 +1738,7 @@ hipError_t mix_rounds(const KernelShape &shape, uint32_t integ, const MixPlan &p
         else if (integ == LZ_INTEGRATOR_EULER_FMA) e = run(Int<1>{}, Int<1>{}, Int<16>{});
         else if (plan.ga == 1) e = run(Int<2>{}, Int<1>{}, Int<4>{});
         else e = run(Int<2>{}, Int<4>{}, Int<16>{});
-        if (e != hipSuccess) return r == 0 ? give_back(e, sh, grid, s) : e;
+        if (e != hipSuccess) return give_back(e, sh, grid, s, r == 0 ? nullptr : wide);
     }
     return hipSuccess;
 }
@@ -1752,8 +1763,9 @@ hipError_t launch_plain(const KernelShape &sh, const lz_key &key, const lz_param
     if (mix.rounds) return launch_mix<false>(sh, a, prm.integrator, mix, tag_acc, TAG_WORDS, s);
     if (plan.waves) a.nb = plan.chain0;
     const uint64_t grid = grid_of(sh, a.nb);
-    hipError_t e = sh.g > 1 ? launch_claim(sh, grid, tag_acc, TAG_WORDS, tag_acc + TAG_WIDE, s)
-                            : launch_fill_u64(tag_acc, TAG_WORDS, s);
+    const uint64_t claim = plan.waves ? seg_grid(sh) : (sh.g > 1 ? grid : 0);  // workgroups counted before they run
+    hipError_t e = claim ? launch_claim(sh, claim, tag_acc, TAG_WORDS, tag_acc + TAG_WIDE, s)
+                         : launch_fill_u64(tag_acc, TAG_WORDS, s);
     if (e != hipSuccess) return e;
     if (grid) {
         e = dispatch(sh.m, sh.g, prm.integrator, [&](auto mc, auto ic, auto gc) {
@@ -1763,14 +1775,14 @@ hipError_t launch_plain(const KernelShape &sh, const lz_key &key, const lz_param
             hipLaunchKernelGGL((plain_kernel<M, I, false, G>), dim3((unsigned)grid), dim3(sh.wg), lds_bytes(sh), s, a);
             return hipGetLastError();
         });
-        if (e != hipSuccess) return sh.g > 1 ? give_back(e, sh, grid, s) : e;
+        if (e != hipSuccess) return claim ? give_back(e, sh, claim, s) : e;
     }
     if (!plan.waves) return hipSuccess;
     KernelShape ss = sh;
     ss.tile = seg_tile(plan.seg_len, sh.tile);
     a.nb = nb;
     a.tile = (uint32_t)ss.tile;
-    return seg_rounds(ss, plan, [&](unsigned g, uint64_t first) {
+    return seg_rounds(ss, plan, s, [&](unsigned g, uint64_t first) {
         return dispatch_i<1>(prm.integrator, [&](auto, auto ic, auto) {
             constexpr int I = decltype(ic)::value;
             hipLaunchKernelGGL((plain_seg_kernel<I>), dim3(g), dim3(ss.wg), lds_bytes(ss), s, a, plan, first);
@@ -1840,8 +1852,9 @@ hipError_t launch_batch(const KernelShape &sh, const DevInfo &dev, const lz_para
             a.tile = (uint32_t)ms.tile;
             hipLaunchKernelGGL((batch_mix_kernel<I, GA, GB>), dim3(g), dim3(ms.wg), lds_bytes(ms), s, a, mix, r);
         });
-    hipError_t e = sh.g > 1 ? launch_claim(sh, grid, b.tag_acc, words, b.wide, s)
-                            : launch_fill_u64(b.tag_acc, words, s);
+    const uint64_t claim = plan.waves ? seg_grid(sh) : (sh.g > 1 ? grid : 0);  // workgroups counted before they run
+    hipError_t e = claim ? launch_claim(sh, claim, b.tag_acc, words, b.wide, s)
+                         : launch_fill_u64(b.tag_acc, words, s);
     if (e != hipSuccess) return e;
     if (grid) {
         e = dispatch(sh.m, sh.g, prm.integrator, [&](auto mc, auto ic, auto gc) {
@@ -1851,13 +1864,13 @@ hipError_t launch_batch(const KernelShape &sh, const DevInfo &dev, const lz_para
             hipLaunchKernelGGL((batch_kernel<M, I, G>), dim3((unsigned)grid), dim3(sh.wg), lds_bytes(sh), s, a);
             return hipGetLastError();
         });
-        if (e != hipSuccess) return sh.g > 1 ? give_back(e, sh, grid, s) : e;
+        if (e != hipSuccess) return claim ? give_back(e, sh, claim, s) : e;
     }
     if (!plan.waves) return hipSuccess;
     KernelShape ss = sh;
     ss.tile = seg_tile(plan.seg_len, sh.tile);
     a.tile = (uint32_t)ss.tile;
-    return seg_rounds(ss, plan, [&](unsigned g, uint64_t first) {
+    return seg_rounds(ss, plan, s, [&](unsigned g, uint64_t first) {
         return dispatch_i<1>(prm.integrator, [&](auto, auto ic, auto) {
             constexpr int I = decltype(ic)::value;
             hipLaunchKernelGGL((batch_seg_kernel<I>), dim3(g), dim3(ss.wg), lds_bytes(ss), s, a, plan, first);
