@@ -183,6 +183,7 @@ struct TickDev {
     uint32_t n_list;
     uint32_t tick_bytes;
     uint32_t n_narrow, narrow_bytes;  // a mixed tick (narrow_bytes > 0): the list's first n_narrow run a lane each, by this
+    uint32_t *others;             // 0; receives ~ the waves in flight beside the tick
     uint32_t *done_queue;         // request slots completed in this tick
     uint32_t *done_count;
 };

@@ -70,3 +70,55 @@ def test_rounds_hold_their_claim(lz, streams, n, kind):
         assert len(busy) >= 20  # of some 20 ms
         assert busy == list(range(busy[0], busy[-1] + 1)), [seen[i] for i in range(busy[0], busy[-1] + 1)].index(0)
         assert np.array_equal(host(out), want)
+
+
+def test_ticks_do_not_mix_layouts_beside_other_work(lz, streams):
+    """40,000 chains of 256 bytes are 16 ticks of a lane per chain.  Mixed ticks take 18 or more: most chains get 13 bytes in
+    each.  Beside short messages on another stream at most the first two are mixed."""
+    import time
+
+    import torch
+
+    simds = 4 * torch.cuda.get_device_properties(0).multi_processor_count
+    s1, _ = streams
+    ctx, other = lz.Context(0), lz.Context(0, lz.params(n_it=160))
+    per = simds * 2000 // 1024
+    P = [torch.randint(0, 256, (256 * per,), dtype=torch.uint8, device="cuda") for _ in range(20)]
+    want = [ctx.encrypt(p, b"tick") for p in P]
+    out = [torch.empty(256 * per + 24, dtype=torch.uint8, device="cuda") for _ in P]
+    msg = torch.zeros(simds * 64 * 256, dtype=torch.uint8, device="cuda")
+    msg_out = torch.empty(len(msg) + 24, dtype=torch.uint8, device="cuda")
+    msg_want = other.encrypt(msg, b"message")
+
+    def burst(beside):
+        srv = lz.Server(ctx, hbm_budget=1 << 30)
+        for o in out:
+            o.zero_()
+        torch.cuda.synchronize()
+        for _ in range(beside):
+            other.encrypt(msg, b"message", out=msg_out, stream=s1)
+        srv.submit_many(list(range(20)), [0] * 20, [b"tick"] * 20, [p.data_ptr() for p in P], [len(p) for p in P],
+                        [o.data_ptr() for o in out], [lz.now_ns()] * 20)
+        n, end = 0, time.monotonic() + 30
+        while n < 20 and time.monotonic() < end:
+            n += len(srv.poll(20, 10))
+        assert n == 20
+        ticks = srv.stats()["ticks"]
+        srv.close()
+        for o, x in zip(out, want):
+            assert torch.equal(o, x)
+        return ticks
+
+    alone = burst(0)
+    say("alone", alone)
+    assert alone >= 18
+    beside = []
+    for _ in range(8):  # until a server whose stream's queue is not the messages'
+        beside.append(burst(60))
+        assert torch.equal(msg_out, msg_want)
+        if beside[-1] <= 17:
+            break
+    say("beside", beside)
+    assert beside[-1] <= 17
+    torch.cuda.synchronize()
+    assert lz.unit_waves(ctx) == 0
