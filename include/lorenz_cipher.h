@@ -469,8 +469,9 @@ int lz_lag_sums(lz_ctx *ctx, const uint8_t *d_data, size_t n, uint32_t max_lag, 
 int lz_entropy(lz_ctx *ctx, const uint64_t *d_hist, double *d_S, void *stream);
 
 /* lz_entropy_value: the same into *S in host memory, waiting for it.  The
- * kernel writes into a pinned word of the context, so no copy is launched;
- * calls through one context from several threads take turns. */
+ * kernel writes into a pinned word of the context, so no copy is launched.
+ * May be called through one context from several threads: each waits for its
+ * own stream alone (up to 64 at a time). */
 int lz_entropy_value(lz_ctx *ctx, const uint64_t *d_hist, double *S, void *stream);
 
 /* lz_autocorrelation: d_r (device, max_lag + 1 doubles, overwritten) receives

@@ -183,22 +183,26 @@ extern "C" int lz_entropy(lz_ctx *c, const uint64_t *d_hist, double *d_S, void *
 
 extern "C" int lz_entropy_value(lz_ctx *c, const uint64_t *d_hist, double *S, void *stream) {
     if (!c || !d_hist || !S) return fail(LZ_E_INVAL, "NULL argument");
-    std::lock_guard<std::mutex> turn(c->entropy_mu);
     // the kernel's store is seen here before the runtime would report the stream done (and before the interrupt
     // that a longer wait of the runtime ends with: 10 us); past POLL_NS, or if the launch failed on the way, the
     // runtime waits
     constexpr uint64_t POLL_NS = 2000000, NONE = 0x7ff8c0de00000001ull;  // a NaN: S is a number
-    uint64_t *word = reinterpret_cast<uint64_t *>(c->host_entropy);
-    __atomic_store_n(word, NONE, __ATOMIC_RELEASE);
-    if (int rc = lz_entropy(c, d_hist, c->host_entropy, stream)) return rc;
-    const uint64_t t0 = lz_now_ns();
-    uint64_t v;
-    while ((v = __atomic_load_n(word, __ATOMIC_ACQUIRE)) == NONE && lz_now_ns() - t0 < POLL_NS) {
-    }
-    if (v == NONE) {
-        LZ_HIP(hipStreamSynchronize((hipStream_t)stream));
-        v = __atomic_load_n(word, __ATOMIC_ACQUIRE);
-    }
-    std::memcpy(S, &v, sizeof v);
-    return LZ_OK;
+    uint64_t *word = c->entropy_words.take();
+    auto value = [&]() -> int {
+        __atomic_store_n(word, NONE, __ATOMIC_RELEASE);
+        if (int rc = lz_entropy(c, d_hist, reinterpret_cast<double *>(word), stream)) return rc;
+        const uint64_t t0 = lz_now_ns();
+        uint64_t v;
+        while ((v = __atomic_load_n(word, __ATOMIC_ACQUIRE)) == NONE && lz_now_ns() - t0 < POLL_NS) {
+        }
+        if (v == NONE) {
+            LZ_HIP(hipStreamSynchronize((hipStream_t)stream));
+            v = __atomic_load_n(word, __ATOMIC_ACQUIRE);
+        }
+        std::memcpy(S, &v, sizeof v);
+        return LZ_OK;
+    };
+    const int rc = value();
+    c->entropy_words.give(word);
+    return rc;
 }

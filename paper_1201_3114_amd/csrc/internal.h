@@ -3,6 +3,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <condition_variable>
 #include <cstddef>
 #include <cstdint>
 #include <mutex>
@@ -129,6 +130,30 @@ struct DevInfo {
     int lds_per_wg_max;
 };
 
+// Words of pinned host memory that calls on several threads take and give back; a call that finds none waits for one.
+struct PinnedWords {
+    static constexpr int N = 64;
+    uint64_t *mem = nullptr;
+    std::mutex mu;
+    std::condition_variable freed;
+    uint64_t used = 0;  // a bit per word
+
+    uint64_t *take() {
+        std::unique_lock<std::mutex> g(mu);
+        freed.wait(g, [&] { return used != ~0ull; });
+        const int i = __builtin_ctzll(~used);
+        used |= 1ull << i;
+        return mem + i;
+    }
+    void give(uint64_t *word) {
+        {
+            std::lock_guard<std::mutex> g(mu);
+            used &= ~(1ull << (word - mem));
+        }
+        freed.notify_one();
+    }
+};
+
 constexpr int WAVE_LANES = 64;  // lanes of a gfx950 wavefront
 constexpr int CU_SIMDS = 4;     // SIMDs of a compute unit
 
@@ -253,8 +278,7 @@ struct lz_ctx {
     lz::ChainState *ws_seg;      // plain path checkpoints between rounds (seg_state_bytes, on first use)
     int32_t *ws_status;          // plain path status (synchronous decrypt)
     int32_t *host_status;        // pinned
-    double *host_entropy;        // pinned, beside host_status (lz_entropy_value)
-    std::mutex entropy_mu;       // its users take turns
+    lz::PinnedWords entropy_words;  // one for each lz_entropy_value under way
     hipStream_t last_stream;
     hipEvent_t last_event;
     bool has_last;

@@ -214,8 +214,9 @@ extern "C" int lz_context_create(int device, const lz_params *prm, lz_ctx **out)
     if (!shape_valid(c->shape, c->dev)) c->shape = KernelShape{1, 64, 32, 4};
     hipError_t e = hipMalloc(&c->ws_tag, (TAG_WORDS + 1) * sizeof(unsigned long long));
     if (e == hipSuccess) e = hipMalloc(&c->ws_status, sizeof(int32_t));
-    if (e == hipSuccess) e = hipHostMalloc(&c->host_status, 2 * sizeof(double), hipHostMallocDefault);
-    if (e == hipSuccess) c->host_entropy = reinterpret_cast<double *>(c->host_status) + 1;
+    // the status and the entropy words in one allocation
+    if (e == hipSuccess) e = hipHostMalloc(&c->host_status, (1 + PinnedWords::N) * sizeof(uint64_t), hipHostMallocDefault);
+    if (e == hipSuccess) c->entropy_words.mem = reinterpret_cast<uint64_t *>(c->host_status) + 1;
     if (e == hipSuccess) e = hipEventCreateWithFlags(&c->last_event, hipEventDisableTiming);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&c->diag_event, hipEventDisableTiming);
     if (e == hipSuccess) e = hipMalloc(&c->diag_merge, (DIAG_MERGE_WORDS + 1) * 8);
