@@ -530,6 +530,23 @@ int lz_unit_lorenz(lz_ctx *ctx, double *d_r, size_t n, uint32_t steps, void *str
  * the work queued on stream. */
 int lz_unit_waves(lz_ctx *ctx, uint32_t *waves, void *stream);
 
+/* lz_unit_plan: how a launch of `chains` chains (one per lane group) of up to
+ * prm->block_len bytes would run on a device of `simds` SIMDs.  Host only.
+ * lens (or NULL: all of block_len bytes): the longest chain of each of the
+ * last waves of 64 chains, simds + (waves mod simds) of them, descending. */
+typedef struct {
+    uint32_t lanes;           /* lanes per chain of a launch without a plan, where there is room */
+    uint32_t seg_waves;       /* segment plan (0: none): the last seg_waves waves ... */
+    uint32_t seg_rounds;      /* ... advance in seg_rounds rounds of simds waves ... */
+    uint32_t segs, seg_len;   /* ... each by one of segs segments of seg_len bytes; */
+    uint32_t seg_off[33];     /* task seg_off[s] + w is segment s of wave w */
+    uint32_t mix_rounds;      /* mix plan (0: none): in each of mix_rounds rounds ... */
+    uint32_t mix_lanes[2];    /* ... mix_first units advance by mix_bytes[0] bytes in mix_lanes[0] lanes per chain */
+    uint32_t mix_bytes[2];    /* and the others by mix_bytes[1] in mix_lanes[1], of mix_units units of mix_unit chains */
+    uint32_t mix_unit, mix_units, mix_first;
+} lz_launch_plan;
+int lz_unit_plan(const lz_params *prm, uint32_t simds, uint64_t chains, const uint32_t *lens, lz_launch_plan *out);
+
 /* CLOCK_MONOTONIC now, in ns (the clock of arrival_ns and done_ns). */
 uint64_t lz_now_ns(void);
 

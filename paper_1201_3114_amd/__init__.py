@@ -6,5 +6,5 @@ Importing the package loads the library and fails if it is not built.
 """
 from .cipher import (TAG_BYTES, Batch, Context, IntegrityError, LaunchShape, LorenzError, Server, Stream,  # noqa: F401
                      autocorrelation, autocorrelation_2d, decrypt_noalloc, entropy, histogram, key_setup, lag_sums, now_ns,
-                     packed_offsets, params, power_spectrum_2d, unit_lorenz, unit_r, unit_theta,
+                     packed_offsets, params, power_spectrum_2d, unit_lorenz, unit_plan, unit_r, unit_theta,
                      unit_waves)

@@ -53,6 +53,13 @@ class ServerStats(ctypes.Structure):
                 ("admitted", ctypes.c_uint64), ("completed", ctypes.c_uint64), ("busy_ms", ctypes.c_double)]
 
 
+class LaunchPlan(ctypes.Structure):
+    _fields_ = [("lanes", ctypes.c_uint32), ("seg_waves", ctypes.c_uint32), ("seg_rounds", ctypes.c_uint32),
+                ("segs", ctypes.c_uint32), ("seg_len", ctypes.c_uint32), ("seg_off", ctypes.c_uint32 * 33),
+                ("mix_rounds", ctypes.c_uint32), ("mix_lanes", ctypes.c_uint32 * 2), ("mix_bytes", ctypes.c_uint32 * 2),
+                ("mix_unit", ctypes.c_uint32), ("mix_units", ctypes.c_uint32), ("mix_first", ctypes.c_uint32)]
+
+
 # name -> (restype, argtypes); the exported surface of include/lorenz_cipher.h
 SIGNATURES = {
     "lz_params_default": (ctypes.c_int, [ctypes.POINTER(Params)]),
@@ -99,6 +106,8 @@ SIGNATURES = {
     "lz_unit_theta": (ctypes.c_int, [vp, vp, vp, ctypes.c_size_t, vp, vp]),
     "lz_unit_lorenz": (ctypes.c_int, [vp, vp, ctypes.c_size_t, ctypes.c_uint32, vp]),
     "lz_unit_waves": (ctypes.c_int, [vp, ctypes.POINTER(ctypes.c_uint32), vp]),
+    "lz_unit_plan": (ctypes.c_int, [ctypes.POINTER(Params), ctypes.c_uint32, ctypes.c_uint64, ctypes.POINTER(ctypes.c_uint32),
+                                    ctypes.POINTER(LaunchPlan)]),
     "lz_histogram": (ctypes.c_int, [vp, vp, ctypes.c_size_t, vp, vp]),
     "lz_lag_sums": (ctypes.c_int, [vp, vp, ctypes.c_size_t, ctypes.c_uint32, vp, vp]),
     "lz_entropy": (ctypes.c_int, [vp, vp, vp, vp]),

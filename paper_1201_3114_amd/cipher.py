@@ -477,5 +477,19 @@ def unit_waves(ctx: Context, stream=None) -> int:
     return waves.value
 
 
+def unit_plan(prm: B.Params, simds: int, chains: int, lens=None) -> B.LaunchPlan:
+    """How a launch of `chains` chains would run on a device of `simds` SIMDs (host only); lens: the longest chain of each
+    of its last simds + waves mod simds waves, descending, where they differ."""
+    out = B.LaunchPlan()
+    arr = None
+    if lens is not None:
+        waves = (chains + 63) // 64
+        if len(lens) != simds + waves % simds:
+            raise ValueError("expected simds + (waves mod simds) lengths")
+        arr = np.ascontiguousarray(lens, dtype=np.uint32).ctypes.data_as(ctypes.POINTER(ctypes.c_uint32))
+    check(B.lib.lz_unit_plan(ctypes.byref(prm), simds, chains, arr, ctypes.byref(out)))
+    return out
+
+
 def now_ns() -> int:
     return int(B.lib.lz_now_ns())

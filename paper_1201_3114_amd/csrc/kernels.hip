@@ -1540,17 +1540,17 @@ SegPlan plan_segments(uint64_t chains, const uint32_t *lens, const lz_params &pr
     const uint32_t P = (uint32_t)(S + W % S);
     const double insts = prm.integrator == LZ_INTEGRATOR_RK4 ? 65 : (prm.integrator == LZ_INTEGRATOR_EULER_FMA ? 9 : 14);
     const double byte_us = insts * 4.0 * prm.n_it / CLOCKS_PER_US;
-    const uint32_t B = prm.block_len;
+    const uint64_t B = prm.block_len;  // up to 2^32 - 1: the sequential version
     // without a plan: S waves of full length, then the longest of the others beside them
     double best_us = 0.98 * byte_us * ((double)B + (lens ? lens[S] : B));
     for (uint32_t n = 4; n <= SEG_MAX; n *= 2) {
         SegPlan p{};
-        p.seg_len = (B + n - 1) / n;
-        p.segs = (B + p.seg_len - 1) / p.seg_len;
+        p.seg_len = (uint32_t)((B + n - 1) / n);
+        p.segs = (uint32_t)((B + p.seg_len - 1) / p.seg_len);
         bool apart = true;
         for (uint32_t s = 0; s < p.segs; ++s) {
             uint32_t k = P;
-            while (lens && k > 0 && s > 0 && lens[k - 1] <= s * p.seg_len) --k;
+            while (lens && k > 0 && s > 0 && lens[k - 1] <= (uint64_t)s * p.seg_len) --k;
             apart = apart && k >= S;
             p.off[s + 1] = p.off[s] + k;
         }
@@ -1608,7 +1608,7 @@ MixPlan plan_mix(uint64_t chains, const lz_params &prm, int simds) {
         // the units with the most turns in ga lanes are the last to end
         uint32_t r = prm.block_len / p.lb;
         auto reached = [&](uint32_t rr) {
-            const uint32_t turns = (rr * p.a + p.units - 1) / p.units;
+            const uint64_t turns = ((uint64_t)rr * p.a + p.units - 1) / p.units;
             return turns * p.la + (rr - turns) * p.lb >= prm.block_len;
         };
         while (!reached(r)) ++r;
