@@ -161,7 +161,7 @@ constexpr int CU_SIMDS = 4;     // SIMDs of a compute unit
 // which a launch with several lanes per chain is told whether the device has room for it.
 constexpr size_t TAG_WORDS = 3, TAG_WIDE = 3;
 int lanes_per_chain(uint64_t chains, int m, uint32_t integ, int simds);
-SegPlan plan_segments(uint64_t chains, const uint32_t *lens, const lz_params &prm, int simds);
+SegPlan plan_segments(uint64_t chains, const uint32_t *lens, uint32_t last, const lz_params &prm, int simds);
 MixPlan plan_mix(uint64_t chains, const lz_params &prm, int simds);
 
 // ---- kernel launchers (kernels.hip) --------------------------------------------------

@@ -1525,14 +1525,15 @@ int lanes_per_chain(uint64_t chains, int m, uint32_t integ, int simds) {
 // two of them and a round finds the checkpoints of the one before.  The P waves then take P / S waves' time
 // and a launch per round.  The other waves, a multiple of S, run at once before them.
 //
-// `lens` gives the longest chain of each of the P waves (descending; NULL: all block_len).  Waves past
+// `lens` gives the longest chain of each of the P waves (descending; NULL: all block_len, but `last` in the last
+// wave: a message one block over a full wave may end in a short one, and 16 MiB + 1 byte took 19.8 ms by a plan, 18.7 without).  Waves past
 // a short chain's end have no tasks, so off[] counts the waves that have a segment s.  The segment
 // count is the one of 4, 8, 16, 32 with the least predicted time, clocks per step as measured (4 per
 // instruction) and SEG_ROUND_US for a launch, its checkpoints and the gap before it; without 2% of
 // gain (short steps, or W just below a multiple of S) no plan is made.  Measured: 24 MB in 27.1 ms,
 // 39.0 without a plan; 512 files of 79 MB in 89.1 and 93.0.  A round of one wave per SIMD takes 1.18 ms
 // per 16 bytes, the rate of 64 MiB in one launch: the part's clock under a full load.
-SegPlan plan_segments(uint64_t chains, const uint32_t *lens, const lz_params &prm, int simds) {
+SegPlan plan_segments(uint64_t chains, const uint32_t *lens, uint32_t last, const lz_params &prm, int simds) {
     constexpr double SEG_ROUND_US = 10.0, CLOCKS_PER_US = 2400.0;
     SegPlan best{};
     const uint64_t W = (chains + WAVE - 1) / WAVE, S = (uint64_t)simds;
@@ -1541,8 +1542,9 @@ SegPlan plan_segments(uint64_t chains, const uint32_t *lens, const lz_params &pr
     const double insts = prm.integrator == LZ_INTEGRATOR_RK4 ? 65 : (prm.integrator == LZ_INTEGRATOR_EULER_FMA ? 9 : 14);
     const double byte_us = insts * 4.0 * prm.n_it / CLOCKS_PER_US;
     const uint64_t B = prm.block_len;  // up to 2^32 - 1: the sequential version
+    auto longest = [&](uint32_t w) { return lens ? lens[w] : (w + 1 == P ? last : prm.block_len); };
     // without a plan: S waves of full length, then the longest of the others beside them
-    double best_us = 0.98 * byte_us * ((double)B + (lens ? lens[S] : B));
+    double best_us = 0.98 * byte_us * ((double)B + longest((uint32_t)S));
     for (uint32_t n = 4; n <= SEG_MAX; n *= 2) {
         SegPlan p{};
         p.seg_len = (uint32_t)((B + n - 1) / n);
@@ -1550,7 +1552,7 @@ SegPlan plan_segments(uint64_t chains, const uint32_t *lens, const lz_params &pr
         bool apart = true;
         for (uint32_t s = 0; s < p.segs; ++s) {
             uint32_t k = P;
-            while (lens && k > 0 && s > 0 && lens[k - 1] <= (uint64_t)s * p.seg_len) --k;
+            while (k > 0 && s > 0 && longest(k - 1) <= (uint64_t)s * p.seg_len) --k;
             apart = apart && k >= S;
             p.off[s + 1] = p.off[s] + k;
         }

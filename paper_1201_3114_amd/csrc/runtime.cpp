@@ -91,13 +91,15 @@ KernelShape plain_shape(const lz_ctx *c, uint64_t nb) {
     return sh;
 }
 
-// Segment or mix plan of a message of nb blocks, with the context's checkpoints, allocated for the first
+// Segment or mix plan of a message of n bytes in nb blocks, with the context's checkpoints, allocated for the first
 // message that has a plan.  Without them the message runs without one.
-void plain_plan(lz_ctx *c, const KernelShape &sh, uint64_t nb, SegPlan &seg, MixPlan &mix) {
+void plain_plan(lz_ctx *c, const KernelShape &sh, uint64_t n, uint64_t nb, SegPlan &seg, MixPlan &mix) {
     seg = SegPlan{};
     mix = MixPlan{};
     if (sh.m != 1) return;
-    if (sh.g == 1) seg = plan_segments(nb, nullptr, c->prm, sh.simds);
+    // the last wave's longest chain: its one chain may be the partial block
+    const uint64_t B = c->prm.block_len, last = nb % WAVE_LANES == 1 ? n - (nb - 1) * B : B;
+    if (sh.g == 1) seg = plan_segments(nb, nullptr, (uint32_t)last, c->prm, sh.simds);
     mix = plan_mix(nb, c->prm, sh.simds);
     if ((seg.waves || mix.rounds) && !c->ws_seg) c->ws_seg = alloc_checkpoints(sh.simds);
     seg.state = mix.state = c->ws_seg;
@@ -282,7 +284,7 @@ extern "C" int lz_encrypt_key(lz_ctx *c, const lz_key *key, const uint8_t *d_P, 
     const KernelShape sh = plain_shape(c, nb);
     SegPlan seg;
     MixPlan mix;
-    plain_plan(c, sh, nb, seg, mix);
+    plain_plan(c, sh, n, nb, seg, mix);
     LZ_HIP(launch_plain(sh, *key, c->prm, 0, d_P, d_C, n, c->ws_tag, seg, mix, s));
     LZ_HIP(launch_plain_finalize(0, c->ws_tag, nullptr, d_C + n, nullptr, nullptr, n, s));
     return record(s, c->last_stream, c->last_event, c->has_last);
@@ -303,7 +305,7 @@ extern "C" int lz_decrypt_key(lz_ctx *c, const lz_key *key, const uint8_t *d_C, 
     const KernelShape sh = plain_shape(c, nb);
     SegPlan seg;
     MixPlan mix;
-    plain_plan(c, sh, nb, seg, mix);
+    plain_plan(c, sh, n, nb, seg, mix);
     LZ_HIP(launch_plain(sh, *key, c->prm, 1, d_C, d_P, n, c->ws_tag, seg, mix, s));
     LZ_HIP(launch_plain_finalize(1, c->ws_tag, d_C + n, nullptr, st, d_P, n, s));
     if (d_status) return record(s, c->last_stream, c->last_event, c->has_last);
@@ -424,7 +426,7 @@ int batch_create(lz_ctx *c, const lz_params &prm, int decrypt, size_t n_msg, con
             const uint64_t g = (waves - longest.size() + w) * WAVE_LANES;
             longest[w] = g < prefix[n_msg] ? B : (uint32_t)(lens[tails[g - prefix[n_msg]]] % B);
         }
-        plan = plan_segments(n_chains, longest.data(), prm, sh.simds);
+        plan = plan_segments(n_chains, longest.data(), B, prm, sh.simds);
     }
     MixPlan mix{};  // made for whole blocks: partial ones end early in it
     if (sh.m == 1 && prefix[n_msg] >= tails.size()) mix = plan_mix(n_chains, prm, sh.simds);

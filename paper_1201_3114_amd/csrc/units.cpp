@@ -51,7 +51,7 @@ extern "C" int lz_unit_plan(const lz_params *prm, uint32_t simds, uint64_t chain
     *out = lz_launch_plan{};
     out->lanes = (uint32_t)lanes_per_chain(chains, 1, prm->integrator, (int)simds);
     if (out->lanes == 1) {
-        const SegPlan s = plan_segments(chains, lens, *prm, (int)simds);
+        const SegPlan s = plan_segments(chains, lens, prm->block_len, *prm, (int)simds);
         if (s.waves) {
             out->seg_waves = s.waves;
             out->seg_rounds = s.rounds;

@@ -121,3 +121,22 @@ def test_ticks_do_not_mix_layouts_beside_other_work(lz):
     assert beside[-1] <= 17
     torch.cuda.synchronize()
     assert lz.unit_waves(ctx) == 0
+
+
+@pytest.mark.parametrize("over,rounds", [(1, False), (256, True), (64 * 256 + 1, True)])
+def test_a_short_last_block_needs_no_rounds(lz, streams, over, rounds):
+    """A message of one block over a wave per SIMD: where that block is short, it runs beside the others in one launch, whose
+    waves are one more workgroup than a round's."""
+    import torch
+
+    simds = 4 * torch.cuda.get_device_properties(0).multi_processor_count
+    n = simds * 64 * 256 + over
+    ctx = lz.Context(0)
+    P = to_dev(np.random.default_rng(over).integers(0, 256, n, dtype=np.uint8))
+    out = torch.empty(n + 24, dtype=torch.uint8, device="cuda")
+    seen = samples(lz, ctx, lambda s: ctx.encrypt(P, b"last", out=out, stream=s), *streams)
+    say(over, max(seen))
+    assert max(seen) == (simds if rounds else simds + 4)
+    assert torch.equal(ctx.decrypt(out, b"last"), P)
+    # the same blocks as in a message without the last ones
+    assert torch.equal(ctx.encrypt(P[:-over], b"last")[:-24], out[:n - over])
