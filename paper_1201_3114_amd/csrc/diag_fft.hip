@@ -530,8 +530,8 @@ __global__ __launch_bounds__(DIAG_WG) void fft1k_pass_kernel(const In *src, uint
 //
 // The mixed-radix and the chirp pass over real columns (bytes, or the inverse passes' real spectrum) transform
 // z = x1 + i x2 for columns 2p and 2p + 1; X1 and X2 are the even and odd parts of Z, of which only the indices
-// up to N/2 are kept.  That halves the transforms: 1000 x 1000 takes 43 and 79 us (spectrum and correlation
-// matrix), 52 and 104 with a transform per column.  The two columns share their rounding errors; without the mean
+// up to N/2 are kept.  That halves the transforms: 1000 x 1000 takes 41 and 76 us (spectrum and correlation
+// matrix, calls back to back), 52 and 104 with a transform per column.  The two columns share their rounding errors; without the mean
 // (see Sums) these are no larger than they were with it in a transform per column.
 template <typename In>
 constexpr uint32_t per_transform() { return std::is_same_v<In, double2> ? 1 : 2; }
@@ -720,8 +720,8 @@ __global__ __launch_bounds__(DIAG_WG) void fft_mixed_pass_kernel(const In *src, 
 // of a 128-byte LDS cycle on distinct banks in every exchange.  Real columns go in pairs.
 // Against the transform in extended precision the error is below the direct pass's from 80 up: 1.15e-15 of the
 // correlation matrix at 1009 x 1009 (direct 3.3e-15), 7.2e-16 at 131 x 137 (1.6e-15), 1.1e-15 at 2039 x
-// 2011 (4.5e-15).  Measured, spectrum and correlation matrix: 1009 x 1009 in 41 and 76 us (direct 189
-// and 325), 131 x 137 in 28 and 45 (40 and 72), 2039 x 2011 in 107 and 190 (975 and 1606); a pass at 1009
+// 2011 (4.5e-15).  Spectrum and correlation matrix, calls back to back: 1009 x 1009 in 40 and 73 us (direct
+// 189 and 325), 131 x 137 in 28 and 45 (40 and 72), 2039 x 2011 in 100 and 183 (975 and 1606); a pass at 1009
 // takes 14 to 18 us, the tables 8.  83 x 89 in 26 and 42 (30 and 53); at 61 x 67 the direct
 // passes take 26 and 42, as long as the convolution at 83.
 constexpr uint32_t BLU_MIN = 80, BLU_MAX = 2048;
@@ -1192,9 +1192,8 @@ int launch_tables(const lz_ctx *c, Dft2 &d, const uint8_t *img, uint32_t h, uint
     return LZ_OK;
 }
 
-// The twiddles stay in registers (KEEP) where the grid leaves room for one workgroup a CU at most: 1009 x 1009 in 40
-// and 77 us instead of 42 and 81; at 2039 x 2011, four workgroups a CU, it would be 133 and 252 instead of
-// 106 and 203.
+// The twiddles stay in registers (KEEP) where the grid leaves room for one workgroup a CU at most: 2 and 4 us of
+// 1009 x 1009's; at 2039 x 2011, four workgroups a CU, it would be 133 and 252 us instead of 106 and 203 (the same run).
 template <typename In, int E, int R>
 int launch_blu(const lz_ctx *c, const In *src, uint32_t N, uint32_t M, const double2 *table, double sign, PassOut out,
                hipStream_t s) {

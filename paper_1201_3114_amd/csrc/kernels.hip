@@ -161,9 +161,10 @@ struct StepCount {
 // instructions decides the power: like operations next to each other, the three products with dt in a row, draw
 // less than the compiler's interleaving.  Of 160 random valid orders of the 14 instructions (24 ms launches of
 // four waves per SIMD, three times each) the times ran from 36.97 to 38.08 ms per 384000 steps; the
-// compiler's order took 37.83, this one 37.00 (35.84 at 2.4 GHz).  For the fused map, 80 orders ran
-// from 37.85 (this one) to 39.69.  64 MiB in 74.0 ms, 76.2 in the order of the compiler (97% and 94% of the issue rate
-// at 2.4 GHz).
+// compiler's order took 37.83, this one 37.00 (35.84 at 2.4 GHz).  64 MiB, the two orders in turn on three cards: 77.0 to 78.1 ms
+// in the compiler's and 74.7 to 75.1 in this one, 76.0 to 76.7 and 74.0 to 74.2, 74.3 to 74.6 and 73.7 to 73.8.  For the
+// fused map 80 orders ran from 37.85 (this one) to 39.69, and the compiler's is one of the fast ones: 51.3 to 52.0 ms
+// for 64 MiB, 51.4 to 52.2 in this one.
 template <int I>
 __device__ __forceinline__ void lane_steps(double &x, double &y, double &z, double dt, uint32_t n_it) {
     double d, e, f, g;
