@@ -591,8 +591,8 @@ __device__ inline unsigned long long fix_range_part(const uint8_t *data, uint64_
     const uintptr_t base = reinterpret_cast<uintptr_t>(data);
     uint64_t a = ((base + lo + 15) & ~(uintptr_t)15) - base;  // first 16-byte aligned index >= lo
     if (a > hi) a = hi;
-    uint64_t z = ((base + hi) & ~(uintptr_t)15) - base;        // last aligned index <= hi
-    if (z < a) z = a;
+    const uintptr_t down = (base + hi) & ~(uintptr_t)15;       // may lie before the data, where these are a few bytes
+    const uint64_t z = down > base + a ? down - base : a;      // last aligned index <= hi
     unsigned long long s = 0;
     const uint32_t t = threadIdx.x;
     if (t < a - lo) s += data[lo + t];   // head, under 16 bytes
